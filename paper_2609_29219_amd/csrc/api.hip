@@ -55,12 +55,13 @@ hipError_t launch_fwd(const FwdPlan& p, const void* q, const void* k, const void
     a.v = static_cast<const uint16_t*>(v);
     a.o = o;
     a.lse = lse;
-    a.Sq = Sq;
+    a.Sq = Sq * p.fold;
     a.Skv = Skv;
     a.n_qtiles = p.n_qtiles;
     a.n_wg = (int)p.grid;
     a.num_xcds = num_xcds;
-    a.group = group;
+    a.sq_pos = Sq;
+    a.group = group / p.fold;
     a.out_bf16 = out_bf16;
     a.scale_log2 = (float)s;
     a.q_sign = scale < 0.f ? 0x80008000u : 0u;
@@ -71,7 +72,12 @@ hipError_t launch_fwd(const FwdPlan& p, const void* q, const void* k, const void
     a.ws_o = n > 1 ? workspace : nullptr;
     a.ws_m = n > 1 ? workspace + rows * n * p.d : nullptr;
     a.ws_l = n > 1 ? a.ws_m + rows * n : nullptr;
-    if (n > 1 && (p.causal || p.pipe == 2 || !workspace || p.kv_chunk % p.block_n != 0 ||
+    // a chunk kernel's rows must be allowed the first key of every split
+    const long long last0 = (long long)(n - 1) * a.kv_chunk;
+    if (p.fold < 1 || (p.fold > 1 && p.fold != group) ||
+        (p.chunk ? !p.causal || last0 > Skv - Sq : p.causal && (n > 1 || p.fold > 1)))
+        return hipErrorInvalidValue;
+    if (n > 1 && (p.pipe == 2 || !workspace || p.kv_chunk % p.block_n != 0 ||
                   (long long)(n - 1) * p.kv_chunk >= Skv))
         return hipErrorInvalidValue;
     hipError_t e = hipErrorInvalidValue;
@@ -257,14 +263,16 @@ int device_state(DeviceState** out) {
 }
 
 // Optional fixed tile choice for the block-size ablation only:
-// ATTN_FORCE_PLAN="bn=64,waves=8,pipe=2" (optionally ",splits=4").  Never
-// used to select tiles.
-bool forced_fwd(int* bn, int* waves, int* pipe, int* splits) {
+// ATTN_FORCE_PLAN="bn=64,waves=8,pipe=2" (optionally ",splits=4", and then
+// ",fold=4", the query heads folded into the rows).  Never used to select
+// tiles.
+bool forced_fwd(int* bn, int* waves, int* pipe, int* splits, int* fold) {
     const char* s = getenv("ATTN_FORCE_PLAN");
     if (!s || !*s) return false;
-    *splits = 1;
-    const int n = sscanf(s, "bn=%d,waves=%d,pipe=%d,splits=%d", bn, waves, pipe, splits);
-    return n == 3 || n == 4;
+    *splits = *fold = 1;
+    const int n =
+        sscanf(s, "bn=%d,waves=%d,pipe=%d,splits=%d,fold=%d", bn, waves, pipe, splits, fold);
+    return n >= 3;
 }
 
 // The per-stream workspace (decode partials, split-key prefill partials) of
@@ -369,7 +377,7 @@ int attn_get_plan_for(const attn_device_desc* desc, int kind, int B, int H, int 
     if (kind == ATTN_KIND_FWD) {
         if (causal && Sq > Skv) return fail(ATTN_EUNSUPPORTED, "causal needs Sq <= Skv");
         FwdPlan p;
-        if (!plan_fwd(*desc, B, H, Sq, Skv, d, causal ? 1 : 0, &p, res))
+        if (!plan_prefill(*desc, B, H, Sq, Skv, d, causal ? 1 : 0, 1, &p, res))
             return fail(ATTN_EUNSUPPORTED, "no feasible prefill plan");
         return format_fwd_plan(p, buf, buflen);
     }
@@ -487,6 +495,39 @@ int attn_get_plan(int kind, int B, int H, int Sq, int Skv, int d, int causal, in
     return attn_get_plan_for(nullptr, kind, B, H, Sq, Skv, d, causal, n_splits, buf, buflen);
 }
 
+// Plan of one prefill call (cached per shape): looked up under the lock,
+// planned (which queries the runtime for the compiled kernels' footprint)
+// outside it.  group: query heads per key/value head; 0: the plain form only
+// (no chunk kernel, no folded heads).
+static int prefill_plan(DeviceState* st, int B, int Hq, int Sq, int Skv, int d, int causal,
+                        int group, FwdPlan* plan) {
+    const auto key = std::make_tuple(B, Hq, Sq, Skv, d, causal, st->desc.num_cus, group);
+    {
+        std::lock_guard<std::mutex> lk(g_mu);
+        auto it = g_fwd_cache.find(key);
+        if (it != g_fwd_cache.end()) {
+            *plan = it->second;
+            return ATTN_OK;
+        }
+    }
+    if (!(group ? plan_prefill(st->desc, B, Hq, Sq, Skv, d, causal, group, plan, fwd_resources)
+                : plan_fwd(st->desc, B, Hq, Sq, Skv, d, causal, plan, fwd_resources)))
+        return fail(ATTN_EUNSUPPORTED, "no feasible prefill plan for this shape");
+    std::lock_guard<std::mutex> lk(g_mu);
+    g_fwd_cache[key] = *plan;
+    return ATTN_OK;
+}
+
+// Whether work enqueued on the stream now goes into a graph.
+static bool capturing(hipStream_t stream) {
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(stream, &status) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    return status != hipStreamCaptureStatusNone;
+}
+
 int attn_fwd_ex(const void* q, const void* k, const void* v, void* o, float* lse, int B, int Hq,
                 int Hkv, int Sq, int Skv, int d, float scale, int causal, int flags) {
     int rc = validate_common(q, k, v, o, B, Hq, Skv, d);
@@ -508,36 +549,36 @@ int attn_fwd_ex(const void* q, const void* k, const void* v, void* o, float* lse
 
     const int c = causal ? 1 : 0;
     FwdPlan plan;
-    int fbn, fw, fpipe, fsplits;
-    if (forced_fwd(&fbn, &fw, &fpipe, &fsplits)) {
-        if (!plan_fwd_fixed(st->desc, B, Hq, Sq, Skv, d, c, fbn, fw, fpipe, &plan,
-                            fwd_resources_forced, fsplits))
+    const int group = Hq / Hkv;
+    int fbn, fw, fpipe, fsplits, ffold;
+    if (forced_fwd(&fbn, &fw, &fpipe, &fsplits, &ffold)) {
+        if ((ffold != 1 && ffold != group) ||
+            !plan_fwd_fixed(st->desc, B, Hq, Sq, Skv, d, c, fbn, fw, fpipe, &plan,
+                            fwd_resources_forced, fsplits, ffold))
             return fail(ATTN_EINVAL, "ATTN_FORCE_PLAN names an infeasible or unknown tile");
     } else {
-        // looked up under the lock; planned (which queries the runtime for the
-        // compiled kernels' footprint) outside it
-        const auto key = std::make_tuple(B, Hq, Sq, Skv, d, c, st->desc.num_cus, 0);
-        bool hit = false;
-        {
-            std::lock_guard<std::mutex> lk(g_mu);
-            auto it = g_fwd_cache.find(key);
-            if ((hit = it != g_fwd_cache.end())) plan = it->second;
-        }
-        if (!hit) {
-            if (!plan_fwd(st->desc, B, Hq, Sq, Skv, d, c, &plan, fwd_resources))
-                return fail(ATTN_EUNSUPPORTED, "no feasible prefill plan for this shape");
-            std::lock_guard<std::mutex> lk(g_mu);
-            g_fwd_cache[key] = plan;
-        }
+        rc = prefill_plan(st, B, Hq, Sq, Skv, d, c, group, &plan);
+        // A causal chunk's or folded call's key splits need the workspace, which
+        // a later call may replace: a graph keeps its kernels' pointers, so a
+        // captured call takes the plain form, whose causal plans need none.
+        if (!rc && plan.kv_splits > 1 && (plan.chunk || plan.fold > 1) && capturing(t_stream))
+            rc = prefill_plan(st, B, Hq, Sq, Skv, d, c, 0, &plan);
+        if (rc) return rc;
     }
     const long long rows = (long long)B * Hq * Sq;
     void* ws = nullptr;
     std::unique_lock<std::mutex> ws_lock;  // held until the kernels are enqueued
     if (plan.kv_splits > 1) {
         rc = stream_workspace(st, (size_t)fwd_workspace_bytes(plan, rows), &ws_lock, &ws);
+        // without memory for them a chunk's or folded call's splits are given up
+        if (rc && (plan.chunk || plan.fold > 1)) {
+            rc = prefill_plan(st, B, Hq, Sq, Skv, d, c, 0, &plan);
+            if (!rc && plan.kv_splits > 1)
+                rc = stream_workspace(st, (size_t)fwd_workspace_bytes(plan, rows), &ws_lock, &ws);
+        }
         if (rc) return rc;
     }
-    hipError_t e = launch_fwd(plan, q, k, v, o, lse, Hq / Hkv, (flags & ATTN_OUT_BF16) ? 1 : 0,
+    hipError_t e = launch_fwd(plan, q, k, v, o, lse, group, (flags & ATTN_OUT_BF16) ? 1 : 0,
                               rows, Sq, Skv, scale, st->desc.num_xcds, static_cast<float*>(ws),
                               t_stream);
     if (e != hipSuccess) return fail_hip(e, "prefill launch");

@@ -23,8 +23,10 @@ struct FwdPlan {
     int wg_per_cu = 0;  // modelled occupancy
     long long grid = 0;
     int n_qtiles = 0;
-    int kv_splits = 1;  // key splits per head (non-causal only), with a combine kernel
+    int kv_splits = 1;  // key splits per head (not with q-tile pairs), with a combine kernel
     int kv_chunk = 0;   // keys per split (a multiple of block_n; Skv when unsplit)
+    int fold = 1;       // query heads folded into the rows of one head (1, or the whole group)
+    int chunk = 0;      // causal chunk kernel: single q-tiles (splits, fold) instead of pairs
     double modeled_us = 0.0;
     const char* bound = "";  // resource that binds the modelled time
 };
@@ -122,15 +124,16 @@ struct FwdArgs {
     const uint16_t* v;
     void* o;            // [B][Hq][Sq][D], fp32 or bf16 (out_bf16)
     float* lse;         // [B][Hq][Sq] natural-log log-sum-exp, or null
-    int Sq, Skv;
+    int Sq, Skv;        // rows per (folded) head, keys
+    int sq_pos;         // queries per unfolded head: row i is query i % sq_pos
     int n_qtiles;       // q-tiles per head
     int n_wg;           // grid size
     int num_xcds;
-    int group;          // query heads per key/value head
+    int group;          // (folded) query heads per key/value head
     int out_bf16;
     float scale_log2;   // |scale| * log2(e), > 0
     uint32_t q_sign;    // sign bits xor-ed into Q (negative scale)
-    // Split key range (non-causal): kv_splits > 1 gives each workgroup the keys
+    // Split key range (non-causal, causal chunks): kv_splits > 1 gives each workgroup the keys
     // [s*kv_chunk, min(Skv, (s+1)*kv_chunk)) of split s, and it writes the
     // unnormalised partials of each row r to index r*kv_splits + s of ws_m
     // (running max, log2 units with the scale), ws_l (sum) and ws_o (d values)
@@ -150,19 +153,34 @@ struct KernelRes {
     int scratch_bytes = 0;
     int vgprs = 0;
 };
+// causal: 0 no mask, 1 causal q-tile pairs, 2 the causal chunk kernel
 typedef bool (*FwdResFn)(int d, int bn, int waves, int pipe, int causal, KernelRes* out);
+
+// Tiles of the causal chunk kernel (the others would only add code: these are
+// the ones that the non-causal key splits choose, with 8 and with 4 waves).
+constexpr bool fwd_chunk_tile(int bn, int waves, int pipe) {
+    return (bn == 64 && waves == 8 && pipe == 3) || (bn == 64 && waves == 4 && pipe == 1) ||
+           (bn == 32 && waves == 4 && pipe == 1);
+}
 
 // Planner (host only, pure arithmetic on the device description).  With
 // res == nullptr (no device) the register footprint is estimated.
 void default_desc(attn_device_desc* out);
 bool plan_fwd(const attn_device_desc& desc, int B, int H, int Sq, int Skv, int d, int causal,
               FwdPlan* out, FwdResFn res = nullptr);
+// The plan of a call: the fastest of plan_fwd's candidates, causal chunks, and
+// (H query heads, group of them to a key/value head) folded heads.
+bool plan_prefill(const attn_device_desc& desc, int B, int H, int Sq, int Skv, int d, int causal,
+                  int group, FwdPlan* out, FwdResFn res = nullptr);
+// fold: query heads folded into the rows (1, or the group).  A causal plan
+// with splits or folded heads is one of the chunk kernel.
 bool plan_fwd_fixed(const attn_device_desc& desc, int B, int H, int Sq, int Skv, int d,
                     int causal, int bn, int waves, int pipe, FwdPlan* out,
-                    FwdResFn res = nullptr, int kv_splits = 1);
-// Key-split counts tried for non-causal prefill (each must leave every split
-// non-empty with a chunk that is a multiple of the tile width, and the split
-// grid must stay within kFwdSplitRounds rounds of the CUs).
+                    FwdResFn res = nullptr, int kv_splits = 1, int fold = 1);
+// Key-split counts tried for prefill without a mask and for causal chunks
+// (each must leave every split non-empty with a chunk that is a multiple of
+// the tile width, and the split grid must stay within kFwdSplitRounds rounds
+// of the CUs).
 constexpr int kFwdKvSplits[] = {1, 2, 3, 4, 6, 8, 12, 16, 24, 32, 48, 64, 96, 128, 192, 256};
 // GEMM K splits (hand-scheduled tiles) and the workspace they may use
 constexpr int kGemmKSplits[] = {1, 2, 3, 4, 6, 8};

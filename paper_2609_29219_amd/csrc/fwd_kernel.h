@@ -171,7 +171,16 @@ constexpr int fwd_waves_per_eu() {
     return (wgs * NW / 4) >= 2 ? 2 : 1;
 }
 
-template <int D, int BN, int NW, int PIPE, bool CAUSAL>
+// CHUNK (causal only): the kernel of a chunk of queries behind a longer cache
+// (Skv >= 2 Sq).  Its work is almost a rectangle, so instead of q-tile pairs it
+// takes single q-tiles, may split the keys (every row is allowed at least
+// the first key of each split: the diagonal lies in the last one), and may
+// fold the query heads of a key/value head into the rows (row i of the folded
+// head is query i % sq_pos of head i / sq_pos), so that a short chunk fills
+// its q-tiles and the group reads each K/V tile once.  Bound: MFMA, once the
+// splits fill the CUs.  B1 Hq32 Hkv8 Sq512 Skv16384 d128 (64 q-tiles of 256
+// rows): unsplit pairs 643 us, 4 splits 137 us with the combine.
+template <int D, int BN, int NW, int PIPE, bool CAUSAL, bool CHUNK = false>
 __global__ __launch_bounds__(NW * 64, (fwd_waves_per_eu<D, BN, NW, PIPE>())) void fwd_kernel(
     const FwdArgs args) {
     const uint16_t* __restrict__ Q = args.q;
@@ -183,6 +192,8 @@ __global__ __launch_bounds__(NW * 64, (fwd_waves_per_eu<D, BN, NW, PIPE>())) voi
     const uint32_t q_sign = args.q_sign;
     static_assert(PIPE != 2 || NW == 8, "the ping-pong schedule pairs 4 waves with 4 waves");
     static_assert(PIPE != 3 || BN <= 64, "two score tiles in registers");
+    static_assert(!CHUNK || (CAUSAL && PIPE != 2), "chunks are causal");
+    constexpr bool PAIRS = CAUSAL && !CHUNK;  // q-tile pairs
     constexpr int BM = NW * 32;
     constexpr int NT = NW * 64;
     constexpr int KD = D / 16;   // MFMA k-steps over the head dimension
@@ -230,24 +241,41 @@ __global__ __launch_bounds__(NW * 64, (fwd_waves_per_eu<D, BN, NW, PIPE>())) voi
     // holds n+1 tiles of work (heavy one first).  Non-causal: one q-tile,
     // of one key split (logical = (head, split, q-tile), q-tile fastest, so
     // the workgroups reading one K/V chunk are neighbours on one XCD).
-    const int units = CAUSAL ? (n_qtiles + 1) / 2 : n_qtiles;
-    const int kv_splits = (CAUSAL || PIPE == 2) ? 1 : args.kv_splits;
+    const int units = PAIRS ? (n_qtiles + 1) / 2 : n_qtiles;
+    const int kv_splits = (PAIRS || PIPE == 2) ? 1 : args.kv_splits;
     const int bh = logical / (units * kv_splits);
     const int within = logical - bh * units * kv_splits;
     const int split = within / units;
     const int unit = within - split * units;
-    const int n_pass = (CAUSAL && n_qtiles - 1 - unit != unit) ? 2 : 1;
+    const int n_pass = (PAIRS && n_qtiles - 1 - unit != unit) ? 2 : 1;
     // this workgroup's keys: [k0, k0 + Skv) of the head's args.Skv keys
     const int k0 = split * args.kv_chunk;
-    const int Skv = CAUSAL ? args.Skv : min(args.kv_chunk, args.Skv - k0);
-    const int diag = Skv - Sq;  // causal: key j allowed iff j <= row + diag
+    const int Skv = PAIRS ? args.Skv : min(args.kv_chunk, args.Skv - k0);
+    // causal: key j of this workgroup's allowed iff j <= position + diag (a
+    // row's position is its index, or modulo sq_pos where heads are folded)
+    const int sq_pos = CHUNK ? args.sq_pos : Sq;
+    const int diag = CHUNK ? args.Skv - sq_pos - k0 : Skv - Sq;
+    // least and greatest position of the rows [first, last]
+    auto pos_range = [&](int first, int last, int& lo, int& hi) __attribute__((always_inline)) {
+        lo = first;
+        hi = last;
+        if constexpr (CHUNK) {
+            const int head = first / sq_pos;
+            lo = first - head * sq_pos;
+            hi = last - head * sq_pos;
+            if (hi >= sq_pos) {  // the rows reach into the next folded head
+                lo = 0;
+                hi = sq_pos - 1;
+            }
+        }
+    };
     // grouped-query heads: query head bh reads key/value head bh / group
     const long long kv_base = ((long long)(bh / args.group) * args.Skv + k0) * D;
     const uint16_t* Kb = K + kv_base;
     const uint16_t* Vb = V + kv_base;
 
     auto qt_of = [&](int pass) __attribute__((always_inline)) {
-        return CAUSAL ? (pass == 0 ? n_qtiles - 1 - unit : unit) : unit;
+        return PAIRS ? (pass == 0 ? n_qtiles - 1 - unit : unit) : unit;
     };
     // ---- Q tile into VGPRs, as the B operand (16 dims x 32 queries) ----------
     // The loads are issued without touching the data, so nothing waits for
@@ -275,21 +303,25 @@ __global__ __launch_bounds__(NW * 64, (fwd_waves_per_eu<D, BN, NW, PIPE>())) voi
     const int qt = qt_of(pass);
     const int q_wave0 = qt * BM + wave * 32;  // first query row of this wave
     const int qrow = q_wave0 + l32;
+    const int qpos = CHUNK ? qrow % sq_pos : qrow;
+    int wave_lo, wave_hi;  // positions of this wave's rows
+    pos_range(q_wave0, q_wave0 + 31, wave_lo, wave_hi);
 
     // ---- key range of this workgroup ------------------------------------
     int kv_end = Skv;
     if (CAUSAL) {
-        const int last_q = min(qt * BM + BM - 1, Sq - 1);
+        int first_q, last_q;
+        pos_range(qt * BM, min(qt * BM + BM - 1, Sq - 1), first_q, last_q);
         kv_end = min(Skv, last_q + diag + 1);
     }
     const int n_tiles = (kv_end + BN - 1) / BN;
     // causal: a tile entirely above this wave's diagonal is skipped
-    auto wave_active = [&](int t) __attribute__((always_inline)) { return !CAUSAL || t * BN <= q_wave0 + 31 + diag; };
+    auto wave_active = [&](int t) __attribute__((always_inline)) { return !CAUSAL || t * BN <= wave_hi + diag; };
     // tiles before first_masked need no mask for any row of this wave.  The
     // split is per wave (on the diagonal, the waves of lower rows start
     // masking earlier); every wave still runs one barrier per tile.
     int first_masked = Skv / BN;  // the ragged tail tile, if any
-    if (CAUSAL) first_masked = min(first_masked, (q_wave0 + diag + 1) / BN);
+    if (CAUSAL) first_masked = min(first_masked, (wave_lo + diag + 1) / BN);
 
     // Rows past the end of the key range are loaded from the last valid row
     // (clamped, never out of bounds): their scores are masked to weight 0,
@@ -480,7 +512,7 @@ __global__ __launch_bounds__(NW * 64, (fwd_waves_per_eu<D, BN, NW, PIPE>())) voi
     auto tile_max = [&](f32x16 (&s)[KB], int t, auto mask_tag) __attribute__((always_inline)) -> float {
         constexpr bool MASK = decltype(mask_tag)::value;
         if (MASK) {
-            const int lim = CAUSAL ? min(Skv - 1, qrow + diag) : Skv - 1;
+            const int lim = CAUSAL ? min(Skv - 1, qpos + diag) : Skv - 1;
             const int room = lim - t * BN - 16 * hh;
 #pragma unroll
             for (int kb = 0; kb < KB; ++kb)
@@ -648,7 +680,7 @@ __global__ __launch_bounds__(NW * 64, (fwd_waves_per_eu<D, BN, NW, PIPE>())) voi
             }
         }
         // causal / ragged-end bound for tile t+1 (MASK_NEXT)
-        const int room = (CAUSAL ? min(Skv - 1, qrow + diag) : Skv - 1) - (t + 1) * BN - 16 * hh;
+        const int room = (CAUSAL ? min(Skv - 1, qpos + diag) : Skv - 1) - (t + 1) * BN - 16 * hh;
         if (HAS_S) {
 #pragma unroll
             for (int kb = 0; kb < KB; ++kb)
@@ -855,7 +887,7 @@ __global__ __launch_bounds__(NW * 64, (fwd_waves_per_eu<D, BN, NW, PIPE>())) voi
         // Two loops, one per masking mode of the next tile, each running two
         // tiles per trip (score sets A and B alternate).  The second loop, and
         // the last active tile, start with the current scores in set A.
-        const int t_last = CAUSAL ? min(n_tiles - 1, (q_wave0 + 31 + diag) / BN) : n_tiles - 1;
+        const int t_last = CAUSAL ? min(n_tiles - 1, (wave_hi + diag) / BN) : n_tiles - 1;
         const int split = max(0, min(first_masked - 1, t_last));
         auto run = [&](int t0, int t1, auto mask_tag) __attribute__((always_inline)) {
             for (int t = t0; t < t1; t += 2) {

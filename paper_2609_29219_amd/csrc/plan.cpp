@@ -114,7 +114,7 @@ int fwd_vgprs(int d, int bn, int waves, int pipe) {
 // 0 the load latency is exposed, shared by the g resident workgroups.  A
 // q-tile adds one exposed latency (Q and the first tile) to its loop.
 //
-// Split keys (non-causal, not with the ping-pong schedule; the Flash Decode
+// Split keys (no mask or a causal chunk, not with the ping-pong schedule; the Flash Decode
 // split of the reduction dimension, Evaluation, applied to prefill): with n
 // splits every (head, q-tile) becomes n workgroups over chunks of ceil(Skv/n) keys rounded up to whole
 // tiles, which fills the CUs when B*H*q-tiles is small; the price is Q read n
@@ -147,8 +147,22 @@ static double fwd_prim_scale(int d, int bn, int waves, int pipe, int causal) {
 
 bool plan_fwd_fixed(const attn_device_desc& desc, int B, int H, int Sq, int Skv, int d,
                     int causal, int bn, int waves, int pipe, FwdPlan* out, FwdResFn res,
-                    int kv_splits) {
+                    int kv_splits, int fold) {
     FwdPlan p;
+    // The causal chunk kernel (single q-tiles: key splits, folded heads) where
+    // the cache before the chunk is at least as long as the chunk, so that the
+    // work is nearly a rectangle; shorter, the pairs balance the triangle and
+    // skip more of it.
+    const bool chunk = causal && (kv_splits > 1 || fold > 1);
+    if (chunk && (!fwd_chunk_tile(bn, waves, pipe) || Skv - Sq < Sq)) return false;
+    // fold query heads into the rows (contiguous in Q, O and the log-sum-exp)
+    const int diag = Skv - Sq;
+    if (fold < 1 || H % fold != 0 || (fold > 1 && (long long)fold * Sq > 0x7fffffffLL - 512))
+        return false;
+    H /= fold;
+    Sq *= fold;
+    p.fold = fold;
+    p.chunk = chunk ? 1 : 0;
     p.d = d;
     p.block_n = bn;
     p.waves = waves;
@@ -170,7 +184,7 @@ bool plan_fwd_fixed(const attn_device_desc& desc, int B, int H, int Sq, int Skv,
     wg = std::min(wg, (desc.max_waves_per_simd * simds) / waves);
     if (res) {  // the compiled kernel's real footprint overrides the estimate
         KernelRes kr;
-        if (!res(d, bn, waves, pipe, causal, &kr)) return false;
+        if (!res(d, bn, waves, pipe, chunk ? 2 : causal, &kr)) return false;
         if (kr.scratch_bytes > 0) return false;  // spills: not a valid primitive
         wg = kr.wg_per_cu;
         if (kr.vgprs > 0) p.vgprs = kr.vgprs;
@@ -179,7 +193,7 @@ bool plan_fwd_fixed(const attn_device_desc& desc, int B, int H, int Sq, int Skv,
     p.wg_per_cu = wg;
     p.n_qtiles = (Sq + p.block_m - 1) / p.block_m;
     // key splits: every split non-empty, chunks of whole tiles
-    if (kv_splits < 1 || (kv_splits > 1 && (causal || pipe == 2))) return false;
+    if (kv_splits < 1 || (kv_splits > 1 && pipe == 2)) return false;
     const long long rows = (long long)B * H * Sq;
     p.kv_splits = kv_splits;
     p.kv_chunk = Skv;
@@ -187,10 +201,14 @@ bool plan_fwd_fixed(const attn_device_desc& desc, int B, int H, int Sq, int Skv,
         const int per = (Skv + kv_splits - 1) / kv_splits;
         p.kv_chunk = (per + bn - 1) / bn * bn;
         if ((Skv + p.kv_chunk - 1) / p.kv_chunk != kv_splits) return false;
+        // causal: the diagonal within the last split, so that every row is
+        // allowed the first key of each split
+        if (causal && (long long)(kv_splits - 1) * p.kv_chunk > diag) return false;
         if (rows * d > 0xffffffffLL) return false;  // one combine workgroup per row
     }
-    // causal workgroups take q-tile pairs (n-1-u, u)
-    p.grid = (long long)B * H * (causal ? (p.n_qtiles + 1) / 2 : (long long)p.n_qtiles * kv_splits);
+    // causal workgroups take q-tile pairs (n-1-u, u), except in chunks
+    const bool pairs = causal && !chunk;
+    p.grid = (long long)B * H * (pairs ? (p.n_qtiles + 1) / 2 : (long long)p.n_qtiles * kv_splits);
     if (p.grid > 0x7fffffffLL) return false;
     // splits fill the device; beyond a few rounds of it they only add partials
     if (kv_splits > 1 && p.grid > (long long)kFwdSplitRounds * desc.num_cus) return false;
@@ -224,7 +242,7 @@ bool plan_fwd_fixed(const attn_device_desc& desc, int B, int H, int Sq, int Skv,
     const double slots = (double)desc.num_cus * wg;
     const int chunk_tiles = (p.kv_chunk + bn - 1) / bn;
     double cycles;
-    if (!causal) {
+    if (!pairs) {
         // full rounds of wg workgroups per CU, then a last, partial round in
         // which each CU holds only ceil(tail / CUs) of them (they share the
         // CU with fewer others, so each of its tiles costs less)
@@ -291,42 +309,58 @@ bool plan_fwd_fixed(const attn_device_desc& desc, int B, int H, int Sq, int Skv,
     return true;
 }
 
-bool plan_fwd(const attn_device_desc& desc, int B, int H, int Sq, int Skv, int d, int causal,
-              FwdPlan* out, FwdResFn res) {
-    bool found = false;
-    FwdPlan best;
+// Every feasible candidate of one form, in search order: fold 1 is the plain
+// form (no key splits under a causal mask unless chunks are asked for).
+template <typename F>
+static void fwd_for_each(const attn_device_desc& desc, int B, int H, int Sq, int Skv, int d,
+                         int causal, FwdResFn res, bool chunks, int fold, F&& f) {
     for (int bn : kFwdBlockN)
         for (int waves : kFwdWaves)
             for (int pipe : kFwdPipe)
                 for (int ns : kFwdKvSplits) {
+                    if (causal && !chunks && ns > 1) break;
                     FwdPlan p;
-                    if (!plan_fwd_fixed(desc, B, H, Sq, Skv, d, causal, bn, waves, pipe, &p, res,
-                                        ns))
-                        continue;
-                    // strict improvement keeps the first (smallest) candidate on ties
-                    if (!found || p.modeled_us < best.modeled_us * (1.0 - 1e-9)) {
-                        best = p;
-                        found = true;
-                    }
+                    if (plan_fwd_fixed(desc, B, H, Sq, Skv, d, causal, bn, waves, pipe, &p, res,
+                                       ns, fold))
+                        f(p);
                 }
-    if (found) *out = best;
-    return found;
+}
+
+// Keeps the fastest plan; strict improvement keeps the first on ties.
+struct FwdBest {
+    FwdPlan best;
+    bool found = false;
+    void operator()(const FwdPlan& p) {
+        if (found && p.modeled_us >= best.modeled_us * (1.0 - 1e-9)) return;
+        best = p;
+        found = true;
+    }
+};
+
+bool plan_fwd(const attn_device_desc& desc, int B, int H, int Sq, int Skv, int d, int causal,
+              FwdPlan* out, FwdResFn res) {
+    FwdBest b;
+    fwd_for_each(desc, B, H, Sq, Skv, d, causal, res, false, 1, b);
+    if (b.found) *out = b.best;
+    return b.found;
+}
+
+bool plan_prefill(const attn_device_desc& desc, int B, int H, int Sq, int Skv, int d, int causal,
+                  int group, FwdPlan* out, FwdResFn res) {
+    FwdBest b;
+    fwd_for_each(desc, B, H, Sq, Skv, d, causal, res, true, 1, b);
+    if (group > 1) fwd_for_each(desc, B, H, Sq, Skv, d, causal, res, true, group, b);
+    if (b.found) *out = b.best;
+    return b.found;
 }
 
 int plan_fwd_all(const attn_device_desc& desc, int B, int H, int Sq, int Skv, int d, int causal,
                  FwdPlan* out, int cap, FwdResFn res) {
     int n = 0;
-    for (int bn : kFwdBlockN)
-        for (int waves : kFwdWaves)
-            for (int pipe : kFwdPipe)
-                for (int ns : kFwdKvSplits) {
-                    FwdPlan p;
-                    if (!plan_fwd_fixed(desc, B, H, Sq, Skv, d, causal, bn, waves, pipe, &p, res,
-                                        ns))
-                        continue;
-                    if (n < cap) out[n] = p;
-                    ++n;
-                }
+    fwd_for_each(desc, B, H, Sq, Skv, d, causal, res, false, 1, [&](const FwdPlan& p) {
+        if (n < cap) out[n] = p;
+        ++n;
+    });
     return n;
 }
 
@@ -652,10 +686,10 @@ namespace attn {
 int format_fwd_plan(const FwdPlan& p, char* buf, int buflen) {
     return snprintf(buf, buf ? (size_t)buflen : 0,
                     "kind=fwd d=%d BLOCK_M=%d BLOCK_N=%d WAVES=%d PIPE=%d KV_SPLITS=%d "
-                    "KV_CHUNK=%d causal=%d grid=%lld n_qtiles=%d lds_bytes=%d vgprs=%d "
+                    "KV_CHUNK=%d FOLD=%d causal=%d grid=%lld n_qtiles=%d lds_bytes=%d vgprs=%d "
                     "wg_per_cu=%d modeled_us=%.3f bound=%s",
                     p.d, p.block_m, p.block_n, p.waves, p.pipe, p.kv_splits, p.kv_chunk,
-                    p.causal, p.grid, p.n_qtiles, p.lds_bytes, p.vgprs, p.wg_per_cu,
+                    p.fold, p.causal, p.grid, p.n_qtiles, p.lds_bytes, p.vgprs, p.wg_per_cu,
                     p.modeled_us, p.bound);
 }
 

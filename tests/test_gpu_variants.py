@@ -375,3 +375,83 @@ def test_fwd_key_splits_rejected_for_causal(pa):
         with pytest.raises(pa.AttnError) as e:
             pa.attn_fwd(q, q, q, causal=True)
     assert e.value.code == pa.ATTN_EINVAL
+
+
+# ---------------------------------------------------------------- causal chunks
+class forced_chunk_plan(forced_plan):
+    def __init__(self, bn: int, waves: int, pipe: int, splits: int, fold: int):
+        super().__init__(bn, waves, pipe)
+        self.value += f",splits={splits},fold={fold}"
+
+
+# B, Hq, Hkv, Sq, Skv, splits, folded heads: one query; a group whose rows end
+# inside a 32-row wave and wrap within one; a chunk of exactly one q-tile;
+# several q-tiles with a ragged end; the diagonal at the very start of the last
+# split; more splits than tiles a wave is active in
+CHUNKS = [(1, 4, 1, 1, 2, 1, 4), (2, 6, 2, 11, 130, 1, 3), (1, 4, 1, 33, 260, 2, 4),
+          (2, 2, 2, 256, 512, 2, 1), (1, 2, 1, 300, 700, 2, 1), (1, 8, 2, 70, 500, 3, 4),
+          (1, 1, 1, 64, 128, 2, 1), (1, 5, 5, 17, 1100, 6, 1)]
+
+
+@pytest.mark.parametrize("tile", [(64, 8, 3), (64, 4, 1), (32, 4, 1)])
+@pytest.mark.parametrize("d", [64, 128])
+def test_fwd_causal_chunk(pa, tile, d):
+    for i, (B, Hq, Hkv, Sq, Skv, splits, fold) in enumerate(CHUNKS):
+        q, k, v = _qkv(B, Hq, Hkv, Sq, Skv, d, 1500 + 7 * i + d)
+        qd, kd, vd = q.to(DEV), k.to(DEV), v.to(DEV)
+        sc = float(np.float32(1.0 / math.sqrt(d)))
+        announce(f"attn_fwd_ex causal chunk {tile} d={d} {CHUNKS[i]}")
+        with forced_chunk_plan(*tile, splits, fold):
+            o, lse = pa.attn_fwd(qd, kd, vd, causal=True, return_lse=True)
+            o16 = pa.attn_fwd(qd, kd, vd, causal=True, out_dtype=torch.bfloat16)
+        torch.cuda.synchronize()
+        ref, ref_lse = oracle.attn_gqa(q, k, v, B, Hq, Hkv, Sq, Skv, d, sc, True)
+        compare(o, ref, f"chunk {tile} d={d} {CHUNKS[i]}")
+        compare(lse, ref_lse, f"chunk {tile} d={d} {CHUNKS[i]} lse", max_abs=LSE_MAX_ABS,
+                mean_abs=LSE_MEAN_ABS)
+        assert torch.equal(o16.cpu(), o.cpu().to(torch.bfloat16))
+
+
+@pytest.mark.parametrize("causal", [False, True])
+def test_fwd_folded_heads_by_plan(pa, causal):
+    # the planner's own choice where folding the group fills the q-tile
+    B, Hq, Hkv, Sq, Skv, d = 2, 16, 2, 9, 3000, 128
+    q, k, v = _qkv(B, Hq, Hkv, Sq, Skv, d, 1700)
+    announce(f"attn_fwd_ex folded heads causal={causal}")
+    o, lse = pa.attn_fwd(q.to(DEV), k.to(DEV), v.to(DEV), scale=-0.1, causal=causal,
+                         return_lse=True)
+    torch.cuda.synchronize()
+    ref, ref_lse = oracle.attn_gqa(q, k, v, B, Hq, Hkv, Sq, Skv, d, float(np.float32(-0.1)),
+                                   causal)
+    compare(o, ref, f"folded causal={causal}")
+    compare(lse, ref_lse, f"folded causal={causal} lse", max_abs=LSE_MAX_ABS,
+            mean_abs=LSE_MEAN_ABS)
+
+
+def test_fwd_causal_chunk_in_a_graph(pa):
+    # captured, the call needs no workspace: replays stay right after an eager
+    # call of the same stream has grown (replaced) it
+    B, Hq, Hkv, Sq, Skv, d = 1, 4, 1, 64, 4096, 128
+    q, k, v = _qkv(B, Hq, Hkv, Sq, Skv, d, 1800)
+    qd, kd, vd = q.to(DEV), k.to(DEV), v.to(DEV)
+    o = torch.empty((B, Hq, Sq, d), dtype=torch.float32, device=DEV)
+    ref = oracle.attn_gqa(q, k, v, B, Hq, Hkv, Sq, Skv, d, float(np.float32(1 / math.sqrt(d))),
+                          True)[0]
+    announce("attn_fwd causal chunk captured")
+    side = torch.cuda.Stream()
+    with torch.cuda.stream(side):
+        pa.attn_fwd(qd, kd, vd, o=o, causal=True)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=side):
+        pa.attn_fwd(qd, kd, vd, o=o, causal=True)
+    for rows in (64, 512, 1024):
+        o.fill_(float("nan"))
+        with torch.cuda.stream(side):
+            big = torch.zeros((1, 32, rows, d), dtype=torch.bfloat16, device=DEV)
+            kv = torch.zeros((1, 32, 4 * rows, d), dtype=torch.bfloat16, device=DEV)
+            pa.attn_fwd(big, kv, kv, causal=True)
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        compare(o, ref, f"replay after an eager call of {rows} rows")
