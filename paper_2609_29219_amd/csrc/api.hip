@@ -284,15 +284,16 @@ int stream_workspace(DeviceState* st, size_t bytes, std::unique_lock<std::mutex>
 }
 
 // Optional fixed GEMM tile for the block-size ablation only:
-// ATTN_FORCE_GEMM="bm=256,bn=256,bk=64,wm=2,wn=4,pipe=1[,splits=4]".  Never
-// used to select tiles.
-bool forced_gemm(int* bm, int* bn, int* bk, int* wm, int* wn, int* pipe, int* splits) {
+// ATTN_FORCE_GEMM="bm=256,bn=256,bk=64,wm=2,wn=4,pipe=1[,splits=4[,deep=1]]".
+// Never used to select tiles.
+bool forced_gemm(int* bm, int* bn, int* bk, int* wm, int* wn, int* pipe, int* splits, int* deep) {
     const char* s = getenv("ATTN_FORCE_GEMM");
     if (!s || !*s) return false;
     *splits = 1;
-    const int n =
-        sscanf(s, "bm=%d,bn=%d,bk=%d,wm=%d,wn=%d,pipe=%d,splits=%d", bm, bn, bk, wm, wn, pipe, splits);
-    return n == 6 || n == 7;
+    *deep = 0;
+    const int n = sscanf(s, "bm=%d,bn=%d,bk=%d,wm=%d,wn=%d,pipe=%d,splits=%d,deep=%d", bm, bn, bk,
+                         wm, wn, pipe, splits, deep);
+    return n >= 6;
 }
 
 // Forced tiles (ablation only) may run a variant that spills: slow, not wrong.
@@ -763,6 +764,26 @@ int attn__gemm_candidates(const attn_device_desc* desc, int M, int N, int K, int
     return len;
 }
 
+// Plan of one GEMM call (cached per shape); may_split: the deep-pipeline kernel
+// may split K, which needs the workspace.
+static int gemm_call_plan(DeviceState* st, int M, int N, int K, int b_nk, bool may_split,
+                          GemmPlan* plan) {
+    const auto key = std::make_tuple(M, N, K, b_nk + (may_split ? 0 : 2), st->desc.num_cus);
+    {
+        std::lock_guard<std::mutex> lk(g_mu);
+        auto it = g_gemm_cache.find(key);
+        if (it != g_gemm_cache.end()) {
+            *plan = it->second;
+            return ATTN_OK;
+        }
+    }
+    if (!plan_gemm_call(st->desc, M, N, K, b_nk, may_split, plan, gemm_resources))
+        return fail(ATTN_EUNSUPPORTED, "no feasible GEMM plan for this shape");
+    std::lock_guard<std::mutex> lk(g_mu);
+    g_gemm_cache[key] = *plan;
+    return ATTN_OK;
+}
+
 int attn_gemm(const void* a, const void* b, void* c, int M, int N, int K, int flags) {
     if (!a || !b || !c) return fail(ATTN_EINVAL, "null matrix pointer");
     if (!aligned16(a) || !aligned16(b) || !aligned16(c))
@@ -774,30 +795,31 @@ int attn_gemm(const void* a, const void* b, void* c, int M, int N, int K, int fl
     if (rc) return rc;
     const int b_nk = (flags & ATTN_GEMM_B_NK) ? 1 : 0;
     GemmPlan plan;
-    int bm, bn, bk, wm, wn, pipe, splits;
-    if (forced_gemm(&bm, &bn, &bk, &wm, &wn, &pipe, &splits)) {
-        if (!plan_gemm_fixed(st->desc, M, N, K, b_nk, bm, bn, bk, wm, wn, pipe, &plan,
-                             gemm_resources_forced, splits))
+    int bm, bn, bk, wm, wn, pipe, splits, deep;
+    if (forced_gemm(&bm, &bn, &bk, &wm, &wn, &pipe, &splits, &deep)) {
+        if (!(deep ? plan_gemm_deep_fixed(st->desc, M, N, K, b_nk, bm, bn, bk, wm, wn, pipe + 1,
+                                          splits, &plan, gemm_resources_forced)
+                   : plan_gemm_fixed(st->desc, M, N, K, b_nk, bm, bn, bk, wm, wn, pipe, &plan,
+                                     gemm_resources_forced, splits)))
             return fail(ATTN_EINVAL, "ATTN_FORCE_GEMM names an infeasible or unknown tile");
     } else {
-        const auto key = std::make_tuple(M, N, K, b_nk, st->desc.num_cus);
-        bool hit = false;
-        {
-            std::lock_guard<std::mutex> lk(g_mu);
-            auto it = g_gemm_cache.find(key);
-            if ((hit = it != g_gemm_cache.end())) plan = it->second;
-        }
-        if (!hit) {
-            if (!plan_gemm(st->desc, M, N, K, b_nk, &plan, gemm_resources))
-                return fail(ATTN_EUNSUPPORTED, "no feasible GEMM plan for this shape");
-            std::lock_guard<std::mutex> lk(g_mu);
-            g_gemm_cache[key] = plan;
-        }
+        rc = gemm_call_plan(st, M, N, K, b_nk, true, &plan);
+        // the deep-pipeline kernel's K splits need the workspace, which a later
+        // call may replace under a graph: captured, it runs unsplit
+        if (!rc && plan.deep && plan.k_splits > 1 && capturing(t_stream))
+            rc = gemm_call_plan(st, M, N, K, b_nk, false, &plan);
+        if (rc) return rc;
     }
     void* ws = nullptr;
     std::unique_lock<std::mutex> ws_lock;  // held until the kernels are enqueued
     if (plan.k_splits > 1) {
         rc = stream_workspace(st, (size_t)gemm_workspace_bytes(plan, M, N), &ws_lock, &ws);
+        // without memory for them the deep-pipeline kernel's splits are given up
+        if (rc && plan.deep) {
+            rc = gemm_call_plan(st, M, N, K, b_nk, false, &plan);
+            if (!rc && plan.k_splits > 1)
+                rc = stream_workspace(st, (size_t)gemm_workspace_bytes(plan, M, N), &ws_lock, &ws);
+        }
         if (rc) return rc;
     }
     const hipError_t e = launch_gemm(plan, a, b, c, M, N, K, (flags & ATTN_OUT_BF16) ? 1 : 0,

@@ -211,6 +211,28 @@ struct GemmLoader {
             lds_dma16(b_rsrc, dst + L::A_TILE * 2 + (p - L::A_PIECES) * 1024, o,
                       b_tile0 + (uint32_t)t * b_tile_step);
     }
+    // all of this wave's pieces of k-tile t, of n_k, of which tile `ragged`
+    // (or none: -1) may reach past K; past the last tile they read nothing
+    __device__ __forceinline__ void guarded(int t, int s, int n_k, int ragged) const {
+        if (t < n_k && t != ragged) {
+#pragma unroll
+            for (int j = 0; j < NJ; ++j) piece<false>(t, s, j);
+        } else {
+            const bool past = t >= n_k;
+#pragma unroll
+            for (int j = 0; j < NJ; ++j) {
+                const int p = wave + j * NW;
+                if (p >= NP) break;
+                const bool is_a = p < L::A_PIECES;
+                const int o = past || ((past_k >> j) & 1u) ? OOB : off[j];
+                const uint32_t tile = past ? 0u : (uint32_t)t;
+                lds_dma16(is_a ? a_rsrc : b_rsrc,
+                          lds0 + (uint32_t)s * (SLOT * 2) +
+                              (is_a ? p * 1024 : L::A_TILE * 2 + (p - L::A_PIECES) * 1024),
+                          o, is_a ? a_tile0 + tile * (BK * 2) : b_tile0 + tile * b_tile_step);
+            }
+        }
+    }
     // all of this wave's pieces of k-tile t of n_k
     __device__ __forceinline__ void tile(int t, int s, int n_k) const {
         if (t == n_k - 1) {
@@ -735,6 +757,95 @@ __global__ __launch_bounds__(256, 1) void gemm_sched_kernel(const GemmArgs args)
     }
 }
 
+// The deep-pipeline kernel, for GEMMs whose output has few tiles (few rows, or
+// both dimensions small): bound by the latency of the k-tiles, not by the
+// matrix core.  Against the generic kernel it keeps NSLOT - 1 k-tiles in flight
+// instead of at most two, and any tile may split K: the grid fills the CUs and
+// each workgroup's chain of k-tiles gets shorter.  One barrier per k-tile: it
+// publishes tile t (the wave's loads of the NSLOT - 2 younger tiles stay in
+// flight) and frees the slot of tile t-1, into which tile t+NSLOT-1 is then
+// loaded.  Tiles past the end load nothing (offsets past the buffer), so that
+// the count of loads in flight is the same on every k-tile.
+// Bounds: 100 x 4096 x 4096 (weights [N][K]) streams 33.5 MB in about 9 us of
+// 4 splits, then the reduction: 27.9 -> 14.3 us; 64 x 16384 x 16384 181 -> 116
+// us (4.6 TB/s), 157 x 312 x 15504 98 -> 17 us.  Where one round of 128 x 128
+// tiles fills the CUs (16384 x 256 x 2048, 2048^3) it runs as the generic kernel
+// does, 25 us: there the tile's LDS traffic binds, not the latency.
+template <int BM, int BN, int BK, int WM, int WN, bool B_NK, int NSLOT>
+__global__ __launch_bounds__(WM * WN * 64, 2) void gemm_deep_kernel(const GemmArgs args) {
+    constexpr int NW = WM * WN;
+    constexpr int MB = BM / (32 * WM), NB = BN / (32 * WN);
+    constexpr int KS = BK / 16;
+    using Ld = GemmLoader<BM, BN, BK, NW, B_NK>;
+    constexpr int SLOT = Ld::SLOT;
+    static_assert(NSLOT >= 3 && (NSLOT - 2) * Ld::NJ < 64, "vmcnt holds 6 bits");
+    static_assert(NSLOT * SLOT * 2 >= NW * 32 * kStageRow, "the staging regions fit the slots");
+
+    __shared__ __attribute__((aligned(16))) uint16_t lds[NSLOT * SLOT];
+
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const GemmOrigin org = gemm_origin(args, BM, BN);
+    const int wm0 = (wave % WM) * MB * 32, wn0 = (wave / WM) * NB * 32;
+    // this workgroup's K range: its split's chunk (all of K unsplit)
+    const int k0 = org.split * args.k_chunk;
+    const int K = min(args.k_chunk, args.K - k0);
+    const int n_k = (K + BK - 1) / BK;
+    // the k-tile whose chunks may reach past K (only the last split's last one)
+    const int ragged = k0 + K == args.K ? n_k - 1 : -1;
+    const Ld ld(args, lds, wave, lane, org.m0, org.n0, k0);
+    const GemmFrags<BM, BN, BK, B_NK> fr(lane, wm0, wn0);
+    const bool more = wave < Ld::NP - Ld::NJ_MIN * NW;
+
+    g_f32x16 acc[NB][MB];
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[nb][mb][r] = 0.f;
+
+    auto publish = [&]() __attribute__((always_inline)) {
+        if (more)
+            publish_barrier<(NSLOT - 2) * Ld::NJ>();
+        else
+            publish_barrier<(NSLOT - 2) * Ld::NJ_MIN>();
+    };
+#pragma unroll
+    for (int u = 0; u < NSLOT - 1; ++u) ld.guarded(u, u, n_k, ragged);
+    int s = 0, s_load = NSLOT - 1;  // slots of k-tiles t and t + NSLOT - 1
+    for (int t = 0; t < n_k; ++t) {
+        publish();
+        ld.guarded(t + NSLOT - 1, s_load, n_k, ragged);
+        const uint16_t* const st = lds + s * SLOT;
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) {
+            g_bf16x8 af[MB], bf[NB];
+#pragma unroll
+            for (int mb = 0; mb < MB; ++mb) af[mb] = fr.a(st, mb, ks);
+#pragma unroll
+            for (int nb = 0; nb < NB; ++nb) bf[nb] = fr.b(st, nb, ks);
+#pragma unroll
+            for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+                for (int mb = 0; mb < MB; ++mb)
+                    acc[nb][mb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bf[nb], af[mb],
+                                                                          acc[nb][mb], 0, 0, 0);
+        }
+        s = s + 1 == NSLOT ? 0 : s + 1;
+        s_load = s_load + 1 == NSLOT ? 0 : s_load + 1;
+    }
+    // the loads past the end and every wave's reads have completed before the
+    // staging regions overlay the slots
+    publish_barrier<0>();
+    GemmArgs out = args;
+    if (args.k_splits > 1) {  // a split writes its fp32 partial tile to the workspace
+        out.c = args.ws + (long long)org.split * args.M * args.N;
+        out.out_bf16 = 0;
+    }
+    gemm_store<MB, NB>(acc, out, lds, wave, org.m0 + wm0, org.n0 + wn0);
+}
+
 // C = the sum of the K-split partials ws[s] (fp32 [M][N]) in split order,
 // four consecutive values per thread (M N is a multiple of 8, since N is);
 // fp32 or bf16 (round to nearest even) output.
@@ -784,6 +895,14 @@ GemmKernel sched_kernel() {
     return {};
 }
 
+template <int BM, int BN, int BK, int WM, int WN, bool B_NK, int NSLOT>
+GemmKernel deep_kernel() {
+    if constexpr (gemm_lds_fits<BM, BN, BK, B_NK, NSLOT - 1>())
+        return {reinterpret_cast<const void*>(&gemm_deep_kernel<BM, BN, BK, WM, WN, B_NK, NSLOT>),
+                WM * WN * 64};
+    return {};
+}
+
 template <int BM, int BN, int BK, int WM, int WN, bool B_NK>
 GemmKernel tile_kernel(int pipe) {
     switch (pipe) {
@@ -808,6 +927,16 @@ GemmKernel sched_kernel(int pipe) {
 // hand-scheduled kernel, every other tile the generic one.  No kernel (fn
 // null) if that variant is not compiled or its LDS does not fit.
 GemmKernel gemm_variant(const GemmPlan& p) {
+    if (p.deep) {
+#define ATTN_D(BM, BN, BK, WM, WN, NSLOT)                                                        \
+    if (p.block_m == BM && p.block_n == BN && p.block_k == BK && p.waves_m == WM &&              \
+        p.waves_n == WN && p.pipe == NSLOT - 1)                                                \
+        return p.b_nk ? deep_kernel<BM, BN, BK, WM, WN, true, NSLOT>()                           \
+                      : deep_kernel<BM, BN, BK, WM, WN, false, NSLOT>();
+        ATTN_DEEP_TILES(ATTN_D)
+#undef ATTN_D
+        return {};
+    }
 #define ATTN_G(BM, BN, BK, WM, WN)                                                             \
     if (p.block_m == BM && p.block_n == BN && p.block_k == BK && p.waves_m == WM &&              \
         p.waves_n == WN)                                                                       \
@@ -834,7 +963,7 @@ hipError_t launch_gemm(const GemmPlan& p, const void* a, const void* b, void* c,
     const bool sched = gemm_hand_scheduled(p.block_m, p.block_n, p.waves_m, p.waves_n);
     if (sched && K % p.block_k != 0) return hipErrorInvalidValue;
     const int splits = p.k_splits > 1 ? p.k_splits : 1;
-    if (splits > 1 && (!sched || !workspace || p.k_chunk % p.block_k != 0 ||
+    if (splits > 1 && (!(sched || p.deep) || !workspace || p.k_chunk % p.block_k != 0 ||
                        (long long)(splits - 1) * p.k_chunk >= K ||
                        (long long)splits * p.k_chunk < K ||
                        p.grid != (long long)p.tiles_m * p.tiles_n * splits))

@@ -533,6 +533,154 @@ bool plan_gemm_fixed(const attn_device_desc& desc, int M, int N, int K, int b_nk
     return true;
 }
 
+// Deep-pipeline kernel: the latency of a k-tile that L2 does not hold, with
+// operands small enough for the memory-side cache and with a stream from HBM
+// (cycles of the nominal clock), the share of the stream bandwidth that its
+// tile loads reach, and measured / modelled k-tile rounds.  Fitted to 46 shapes
+// drawn over M 64..16384, N and K 256..16384: with them the pick was within 8%
+// of the best of all tiles and splits at 38, and never above 22%.
+static constexpr double kDeepMallCycles = 2000.0, kDeepHbmCycles = 3200.0;
+static constexpr double kDeepMallBytes = 64e6;
+static constexpr double kDeepHbmShare = 0.75;
+static constexpr double kDeepScale = 1.1;
+
+bool plan_gemm_deep_fixed(const attn_device_desc& desc, int M, int N, int K, int b_nk, int bm,
+                          int bn, int bk, int wm, int wn, int slots, int k_splits, GemmPlan* out,
+                          GemmResFn res) {
+    bool known = false;
+#define ATTN_D(BM, BN, BK, WM, WN, NSLOT) \
+    known |= bm == BM && bn == BN && bk == BK && wm == WM && wn == WN && slots == NSLOT;
+    ATTN_DEEP_TILES(ATTN_D)
+#undef ATTN_D
+    if (!known) return false;
+    const int n_k_all = (K + bk - 1) / bk;
+    const int chunk_tiles = (n_k_all + k_splits - 1) / std::max(k_splits, 1);
+    if (k_splits < 1 || (long long)(k_splits - 1) * chunk_tiles >= n_k_all) return false;
+    if (k_splits > 1 && (long long)k_splits * M * N * 4 > kGemmMaxWorkspaceBytes) return false;
+    GemmPlan p;
+    p.deep = 1;
+    p.k_splits = k_splits;
+    p.k_chunk = k_splits > 1 ? chunk_tiles * bk : K;
+    p.block_m = bm;
+    p.block_n = bn;
+    p.block_k = bk;
+    p.waves_m = wm;
+    p.waves_n = wn;
+    p.pipe = slots - 1;
+    p.b_nk = b_nk ? 1 : 0;
+    p.lds_bytes = gemm_lds_bytes(bm, bn, bk, b_nk, p.pipe);
+    if (p.lds_bytes > desc.lds_bytes_per_cu) return false;
+    int g = desc.lds_bytes_per_cu / p.lds_bytes;
+    if (res) {
+        KernelRes kr;
+        if (!res(p, &kr) || kr.scratch_bytes > 0) return false;
+        g = kr.wg_per_cu;
+        p.vgprs = kr.vgprs;
+    }
+    if (g < 1) return false;
+    p.wg_per_cu = g;
+    p.tiles_m = (M + bm - 1) / bm;
+    p.tiles_n = (N + bn - 1) / bn;
+    p.grid = (long long)p.tiles_m * p.tiles_n * k_splits;
+    if (p.grid > 0x7fffffffLL) return false;
+
+    // One k-tile round of g workgroups on a CU, as in plan_gemm_fixed, with the
+    // LDS bound counting the tile's writes, and the latency of an HBM-served
+    // tile spread over the slots - 1 tiles in flight.
+    const int waves = wm * wn, mb = bm / (32 * wm), nb = bn / (32 * wn);
+    const double mfma = 2.0 * bm * bn * bk / desc.mfma_bf16_flops_per_clk_cu;
+    const double lds = (waves * (double)(mb + nb) * 64.0 * bk + (double)(bm + bn) * bk * 2.0) /
+                       desc.lds_bytes_per_clk_cu;
+    const double body = std::max(mfma, lds);
+    const double a_bytes = (double)bm * bk * 2.0, b_bytes = (double)bn * bk * 2.0;
+    const double cu_bw = kDeepHbmShare * desc.hbm_bytes_per_s / desc.num_cus / (desc.clock_ghz * 1e9);
+    const double far_cycles =
+        2.0 * ((double)M * K + (double)K * N) > kDeepMallBytes ? kDeepHbmCycles : kDeepMallCycles;
+    // HBM bytes of one round of the whole grid: the tiles of an XCD share panels
+    auto round_of = [&](int r) {
+        const double xcd_tiles =
+            std::max(1.0, std::min((double)p.grid / desc.num_xcds,
+                                   (double)desc.num_cus / desc.num_xcds * r));
+        const double dn =
+            std::max(1.0, std::min((double)p.tiles_n, ceil(xcd_tiles / kGemmGroupM)));
+        const double dm = std::max(1.0, std::min((double)p.tiles_m, ceil(xcd_tiles / dn)));
+        const double hbm_per_wg =
+            std::min(a_bytes + b_bytes, (dm * a_bytes + dn * b_bytes) / xcd_tiles);
+        const double f_hbm = hbm_per_wg / (a_bytes + b_bytes);
+        const double load = (1.0 - f_hbm) * desc.tile_latency_cycles + f_hbm * far_cycles;
+        double t = heg_pipe(load / (slots - 1), r * body + desc.tile_sync_cycles, 0.0, 1, 0);
+        return kDeepScale * std::max(t, r * hbm_per_wg / cu_bw);
+    };
+    const int n_k = chunk_tiles;
+    const double cu_full = desc.hbm_bytes_per_s / desc.num_cus / (desc.clock_ghz * 1e9);
+    auto pass_of = [&](int r) {
+        return far_cycles + heg_for(n_k, round_of(r)) + r * (double)bm * bn * 4.0 / cu_full;
+    };
+    // full rounds of g workgroups per CU, then a round as full as is left
+    const double slots_all = (double)desc.num_cus * g;
+    const double full = floor((double)p.grid / slots_all);
+    const double tail = (double)p.grid - full * slots_all;
+    double cycles = full * pass_of(g);
+    if (tail > 0.0) cycles += pass_of((int)std::min<double>(g, ceil(tail / desc.num_cus)));
+    double us = cycles / (desc.clock_ghz * 1e3);
+    const double c_bytes = (double)M * N * 4.0 * (k_splits > 1 ? 2.0 * k_splits + 1.0 : 1.0);
+    const double hbm_us =
+        ((double)M * K * 2.0 + (double)K * N * 2.0 + c_bytes) / desc.hbm_bytes_per_s * 1e6;
+    p.bound = round_of(std::min(g, std::max(1, (int)(p.grid / desc.num_cus)))) > kDeepScale * body * 1.5
+                  ? "latency"
+                  : (lds > mfma ? "lds" : "mfma");
+    if (hbm_us > us) {
+        us = hbm_us;
+        p.bound = "hbm";
+    }
+    const double reduce_us =
+        k_splits > 1 ? desc.launch_us + 0.5 +
+                           (double)M * N * 4.0 * (k_splits + 1.0) / desc.hbm_bytes_per_s * 1e6
+                     : 0.0;
+    p.modeled_us = us + desc.launch_us + reduce_us;
+    *out = p;
+    return true;
+}
+
+bool plan_gemm_call(const attn_device_desc& desc, int M, int N, int K, int b_nk, bool may_split,
+                    GemmPlan* out, GemmResFn res) {
+    GemmPlan best;
+    bool found = false;
+    auto consider = [&](const GemmPlan& p) {
+        if (found && p.modeled_us >= best.modeled_us * (1.0 - 1e-9)) return;
+        best = p;
+        found = true;
+    };
+    // The generic 64 x 64 tile stands aside over a long K: its model knows no HBM latency
+    // that two k-tiles in flight cannot hide, and the same tile with three in
+    // flight was faster wherever K was over 16 k-tiles (64 x 16384 x 16384:
+    // modelled 82 us, measured 181, deep 116; 173 x 4976 x 3904: 27.7 against
+    // 19.7).  At 16 k-tiles and fewer the generic one is as fast or faster
+    // (701 x 656 x 864: 8.6 against 9.4).
+    for (const GemmTile& t : kGemmTiles)
+        for (int pipe = t.pipe_min; pipe <= t.pipe_max; ++pipe)
+            for (int splits : kGemmKSplits) {
+                GemmPlan p;
+                if (!(t.bm == 64 && K > 16 * t.bk) &&
+                    plan_gemm_fixed(desc, M, N, K, b_nk, t.bm, t.bn, t.bk, t.wm, t.wn, pipe, &p,
+                                    res, splits))
+                    consider(p);
+            }
+    for (int ks : kGemmDeepKSplits) {
+        if (ks > 1 && !may_split) break;
+        GemmPlan p;
+#define ATTN_D(BM, BN, BK, WM, WN, NSLOT)                                                       \
+    if (plan_gemm_deep_fixed(desc, M, N, K, b_nk, BM, BN, BK, WM, WN, NSLOT, ks, &p, res))       \
+        consider(p);
+        ATTN_DEEP_TILES(ATTN_D)
+#undef ATTN_D
+    }
+    // (a device that none of these fit may still fit that tile)
+    if (!found) found = plan_gemm(desc, M, N, K, b_nk, &best, res);
+    if (found) *out = best;
+    return found;
+}
+
 int plan_gemm_all(const attn_device_desc& desc, int M, int N, int K, int b_nk, GemmPlan* out,
                   int cap, GemmResFn res) {
     int n = 0;
@@ -572,10 +720,10 @@ bool plan_gemm(const attn_device_desc& desc, int M, int N, int K, int b_nk, Gemm
 int format_gemm_plan(const GemmPlan& p, char* buf, int buflen) {
     return snprintf(buf, buf ? (size_t)buflen : 0,
                     "kind=gemm BLOCK_M=%d BLOCK_N=%d BLOCK_K=%d WAVES_M=%d WAVES_N=%d PIPE=%d "
-                    "K_SPLITS=%d k_chunk=%d b_nk=%d grid=%lld tiles_m=%d tiles_n=%d lds_bytes=%d "
+                    "DEEP=%d K_SPLITS=%d k_chunk=%d b_nk=%d grid=%lld tiles_m=%d tiles_n=%d lds_bytes=%d "
                     "vgprs=%d wg_per_cu=%d modeled_us=%.3f bound=%s",
-                    p.block_m, p.block_n, p.block_k, p.waves_m, p.waves_n, p.pipe, p.k_splits,
-                    p.k_chunk, p.b_nk, p.grid, p.tiles_m, p.tiles_n, p.lds_bytes, p.vgprs,
+                    p.block_m, p.block_n, p.block_k, p.waves_m, p.waves_n, p.pipe, p.deep,
+                    p.k_splits, p.k_chunk, p.b_nk, p.grid, p.tiles_m, p.tiles_n, p.lds_bytes, p.vgprs,
                     p.wg_per_cu, p.modeled_us, p.bound);
 }
 

@@ -299,3 +299,73 @@ def test_gemm_sweep(pa, case):
     want, absc = oracle.gemm(a, b, M, N, K, b_nk=b_nk, with_abs=True)
     _check(c, want, absc, K, f"sweep gemm {case}")
     assert torch.equal(c16.cpu(), c.cpu().to(torch.bfloat16)), f"bf16 sweep {case}"
+
+
+# ------------------------------------------------- deep-pipeline kernel
+class forced_deep(forced_gemm):
+    def __init__(self, bm, bn, bk, wm, wn, slots, splits):
+        self.value = (f"bm={bm},bn={bn},bk={bk},wm={wm},wn={wn},pipe={slots - 1},"
+                      f"splits={splits},deep=1")
+
+
+# M, N, K, splits: one k-tile; fewer k-tiles than slots; a ragged last k-tile
+# (alone in the last split, too); a tile's edge and one past it; K not of whole
+# 8-value MFMA halves beyond the ragged end; many splits
+DEEP_SHAPES = [(1, 8, 8, 1), (33, 72, 40, 1), (64, 64, 128, 2), (65, 136, 200, 1),
+               (129, 128, 264, 2), (100, 264, 1032, 3), (128, 8, 2056, 17)]
+
+
+@pytest.mark.parametrize("b_nk", [False, True])
+@pytest.mark.parametrize("tile", [(64, 64, 64, 2, 2, 4), (128, 64, 64, 2, 2, 3),
+                                  (64, 128, 64, 2, 2, 3), (128, 128, 64, 2, 4, 4)],
+                         ids=["64x64", "128x64", "64x128", "128x128"])
+def test_gemm_deep_kernel(pa, tile, b_nk):
+    for M, N, K, splits in DEEP_SHAPES:
+        a, b = _inputs(M, N, K, b_nk, 4700 + M)
+        announce(f"attn_gemm deep {tile} {(M, N, K)} splits={splits} b_nk={b_nk}")
+        ad, bd = a.to(DEV), b.to(DEV)
+        with forced_deep(*tile, splits):
+            c = torch.full((M, N), float("nan"), device=DEV)
+            pa.gemm(ad, bd, c=c, b_nk=b_nk)
+            c16 = pa.gemm(ad, bd, b_nk=b_nk, out_dtype=torch.bfloat16)
+        torch.cuda.synchronize()
+        want, absc = oracle.gemm(a, b, M, N, K, b_nk=b_nk, with_abs=True)
+        _check(c, want, absc, K, f"deep {tile} {(M, N, K)} splits={splits} b_nk={b_nk}")
+        assert torch.equal(c16.cpu(), c.cpu().to(torch.bfloat16))
+
+
+def test_gemm_deep_refuses_an_empty_split(pa):
+    a = torch.zeros((64, 128), dtype=torch.bfloat16, device=DEV)
+    b = torch.zeros((128, 64), dtype=torch.bfloat16, device=DEV)
+    announce("attn_gemm deep, 2 k-tiles over 3 splits refused")
+    with forced_deep(64, 64, 64, 2, 2, 4, 3):
+        with pytest.raises(pa.AttnError) as e:
+            pa.gemm(a, b)
+    assert e.value.code == pa.ATTN_EINVAL
+
+
+def test_gemm_few_rows_in_a_graph(pa):
+    # captured, the call does not use the workspace that eager calls of the
+    # stream grow (replace) between the replays
+    M, N, K = 70, 512, 4096
+    a, b = _inputs(M, N, K, True, 4800)
+    ad, bd = a.to(DEV), b.to(DEV)
+    c = torch.empty((M, N), dtype=torch.float32, device=DEV)
+    want, absc = oracle.gemm(a, b, M, N, K, b_nk=True, with_abs=True)
+    side = torch.cuda.Stream()
+    announce("attn_gemm few rows captured")
+    with torch.cuda.stream(side):
+        pa.gemm(ad, bd, c=c, b_nk=True)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=side):
+        pa.gemm(ad, bd, c=c, b_nk=True)
+    for n in (512, 2048, 8192):
+        c.fill_(float("nan"))
+        with torch.cuda.stream(side):
+            w = torch.zeros((n, K), dtype=torch.bfloat16, device=DEV)
+            pa.gemm(ad, w, b_nk=True)
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        _check(c, want, absc, K, f"replay after an eager call with {n} columns")
