@@ -67,6 +67,7 @@ hipError_t launch_fwd(const FwdPlan& p, const void* q, const void* k, const void
     a.q_sign = scale < 0.f ? 0x80008000u : 0u;
     const int n = p.kv_splits;
     a.kv_splits = n;
+    a.heavy_first = p.chunk && n == 1 && p.fold == 1;
     a.kv_chunk = n > 1 ? p.kv_chunk : Skv;
     // partial outputs first: their rows of d floats stay 16-byte aligned
     a.ws_o = n > 1 ? workspace : nullptr;
@@ -263,15 +264,16 @@ int device_state(DeviceState** out) {
 }
 
 // Optional fixed tile choice for the block-size ablation only:
-// ATTN_FORCE_PLAN="bn=64,waves=8,pipe=2" (optionally ",splits=4", and then
-// ",fold=4", the query heads folded into the rows).  Never used to select
-// tiles.
-bool forced_fwd(int* bn, int* waves, int* pipe, int* splits, int* fold) {
+// ATTN_FORCE_PLAN="bn=64,waves=8,pipe=2" (optionally ",splits=4", then
+// ",fold=4", the query heads folded into the rows, and ",singles=1", causal
+// single q-tiles).  Never used to select tiles.
+bool forced_fwd(int* bn, int* waves, int* pipe, int* splits, int* fold, int* singles) {
     const char* s = getenv("ATTN_FORCE_PLAN");
     if (!s || !*s) return false;
     *splits = *fold = 1;
-    const int n =
-        sscanf(s, "bn=%d,waves=%d,pipe=%d,splits=%d,fold=%d", bn, waves, pipe, splits, fold);
+    *singles = 0;
+    const int n = sscanf(s, "bn=%d,waves=%d,pipe=%d,splits=%d,fold=%d,singles=%d", bn, waves, pipe,
+                         splits, fold, singles);
     return n >= 3;
 }
 
@@ -551,11 +553,11 @@ int attn_fwd_ex(const void* q, const void* k, const void* v, void* o, float* lse
     const int c = causal ? 1 : 0;
     FwdPlan plan;
     const int group = Hq / Hkv;
-    int fbn, fw, fpipe, fsplits, ffold;
-    if (forced_fwd(&fbn, &fw, &fpipe, &fsplits, &ffold)) {
+    int fbn, fw, fpipe, fsplits, ffold, fsingles;
+    if (forced_fwd(&fbn, &fw, &fpipe, &fsplits, &ffold, &fsingles)) {
         if ((ffold != 1 && ffold != group) ||
             !plan_fwd_fixed(st->desc, B, Hq, Sq, Skv, d, c, fbn, fw, fpipe, &plan,
-                            fwd_resources_forced, fsplits, ffold))
+                            fwd_resources_forced, fsplits, ffold, fsingles != 0))
             return fail(ATTN_EINVAL, "ATTN_FORCE_PLAN names an infeasible or unknown tile");
     } else {
         rc = prefill_plan(st, B, Hq, Sq, Skv, d, c, group, &plan);

@@ -26,7 +26,7 @@ struct FwdPlan {
     int kv_splits = 1;  // key splits per head (not with q-tile pairs), with a combine kernel
     int kv_chunk = 0;   // keys per split (a multiple of block_n; Skv when unsplit)
     int fold = 1;       // query heads folded into the rows of one head (1, or the whole group)
-    int chunk = 0;      // causal chunk kernel: single q-tiles (splits, fold) instead of pairs
+    int chunk = 0;      // causal chunk kernel: single q-tiles (may have splits, fold) instead of pairs
     double modeled_us = 0.0;
     const char* bound = "";  // resource that binds the modelled time
 };
@@ -140,6 +140,7 @@ struct FwdArgs {
     // (running max, log2 units with the scale), ws_l (sum) and ws_o (d values)
     // instead of o and lse; the split combine then produces o and lse.
     int kv_splits;      // 1: direct output
+    int heavy_first;    // causal single q-tiles, unsplit: workgroups in order of falling work
     int kv_chunk;       // keys per split, a multiple of the tile width (Skv if 1 split)
     float* ws_m;
     float* ws_l;
@@ -174,10 +175,11 @@ bool plan_fwd(const attn_device_desc& desc, int B, int H, int Sq, int Skv, int d
 bool plan_prefill(const attn_device_desc& desc, int B, int H, int Sq, int Skv, int d, int causal,
                   int group, FwdPlan* out, FwdResFn res = nullptr);
 // fold: query heads folded into the rows (1, or the group).  A causal plan
-// with splits or folded heads is one of the chunk kernel.
+// with splits or folded heads is one of the chunk kernel, and so is one with
+// singles (single q-tiles, heaviest first, instead of pairs).
 bool plan_fwd_fixed(const attn_device_desc& desc, int B, int H, int Sq, int Skv, int d,
                     int causal, int bn, int waves, int pipe, FwdPlan* out,
-                    FwdResFn res = nullptr, int kv_splits = 1, int fold = 1);
+                    FwdResFn res = nullptr, int kv_splits = 1, int fold = 1, bool singles = false);
 // Key-split counts tried for prefill without a mask and for causal chunks
 // (each must leave every split non-empty with a chunk that is a multiple of
 // the tile width, and the split grid must stay within kFwdSplitRounds rounds

@@ -171,15 +171,18 @@ constexpr int fwd_waves_per_eu() {
     return (wgs * NW / 4) >= 2 ? 2 : 1;
 }
 
-// CHUNK (causal only): the kernel of a chunk of queries behind a longer cache
-// (Skv >= 2 Sq).  Its work is almost a rectangle, so instead of q-tile pairs it
-// takes single q-tiles, may split the keys (every row is allowed at least
-// the first key of each split: the diagonal lies in the last one), and may
-// fold the query heads of a key/value head into the rows (row i of the folded
-// head is query i % sq_pos of head i / sq_pos), so that a short chunk fills
-// its q-tiles and the group reads each K/V tile once.  Bound: MFMA, once the
-// splits fill the CUs.  B1 Hq32 Hkv8 Sq512 Skv16384 d128 (64 q-tiles of 256
-// rows): unsplit pairs 643 us, 4 splits 137 us with the combine.
+// CHUNK (causal only): single q-tiles instead of pairs.  Unsplit, with the
+// heaviest q-tiles of all heads first (heavy_first), it balances grids of pairs
+// that are no multiple of the CUs: B3 H16 S6394 d128, 624 pairs on 256 CUs, 534 us
+// as pairs and 474 as singles; d64 B2 H16 S5000 194 and 141.  It is also the kernel
+// of a chunk of queries behind a longer cache (Skv >= 2 Sq), whose work is almost
+// a rectangle: it may split the keys (every row is allowed at least the first
+// key of each split: the diagonal lies in the last one), and may fold the query
+// heads of a key/value head into the rows (row i of the folded head is query
+// i % sq_pos of head i / sq_pos), so that a short chunk fills its q-tiles and the
+// group reads each K/V tile once.  Bound: MFMA, once the splits fill the CUs.
+// B1 Hq32 Hkv8 Sq512 Skv16384 d128 (64 q-tiles of 256 rows): unsplit pairs 643 us,
+// 4 splits 134 us with the combine.
 template <int D, int BN, int NW, int PIPE, bool CAUSAL, bool CHUNK = false>
 __global__ __launch_bounds__(NW * 64, (fwd_waves_per_eu<D, BN, NW, PIPE>())) void fwd_kernel(
     const FwdArgs args) {
@@ -243,10 +246,22 @@ __global__ __launch_bounds__(NW * 64, (fwd_waves_per_eu<D, BN, NW, PIPE>())) voi
     // the workgroups reading one K/V chunk are neighbours on one XCD).
     const int units = PAIRS ? (n_qtiles + 1) / 2 : n_qtiles;
     const int kv_splits = (PAIRS || PIPE == 2) ? 1 : args.kv_splits;
-    const int bh = logical / (units * kv_splits);
+    int bh = logical / (units * kv_splits);
     const int within = logical - bh * units * kv_splits;
-    const int split = within / units;
-    const int unit = within - split * units;
+    int split = within / units;
+    int unit = within - split * units;
+    if (CHUNK && args.heavy_first) {
+        // unsplit single q-tiles: the heaviest (last) of all heads first, so
+        // that the light ones fill the gaps at the end; an XCD keeps whole
+        // heads where they can be dealt evenly
+        const int heads = n_wg / n_qtiles;
+        const bool even = heads % num_xcds == 0;
+        const int hx = even ? heads / num_xcds : heads, i = even ? slot_id : wg;
+        const int rank = i / hx;
+        bh = (even ? xcd * hx : 0) + i - rank * hx;
+        unit = n_qtiles - 1 - rank;
+        split = 0;
+    }
     const int n_pass = (PAIRS && n_qtiles - 1 - unit != unit) ? 2 : 1;
     // this workgroup's keys: [k0, k0 + Skv) of the head's args.Skv keys
     const int k0 = split * args.kv_chunk;

@@ -145,16 +145,26 @@ static double fwd_prim_scale(int d, int bn, int waves, int pipe, int causal) {
     return f > 0.0 ? f : 1.0;
 }
 
+// What a q-tile of its own costs beyond one of a pair (the dispatch of its
+// workgroup), cycles, and single q-tiles' time against the model: they win by
+// less than it says (a chip without idle CUs clocks lower), so they have to win by
+// more.  Pairs -> singles, d128 (64, 8, 3): B2 Hq32 Hkv4 S1257 49.5 -> 42.5 us (model
+// 17% apart), B3 H16 S6394 534 -> 474 (23%), B3 Hq32 Hkv4 S3583 327 -> 312 (13%),
+// B2 Hq32 Hkv8 S1777 65.1 -> 60.9 (12%); B1 Hq32 Hkv4 S2513 72.0 -> 74.4 (9%),
+// B4 H16 S2048, a whole round of pairs, 83.2 -> 84.3.
+static constexpr double kSingleCycles = 2000.0, kSingleFactor = 1.09;
+
 bool plan_fwd_fixed(const attn_device_desc& desc, int B, int H, int Sq, int Skv, int d,
                     int causal, int bn, int waves, int pipe, FwdPlan* out, FwdResFn res,
-                    int kv_splits, int fold) {
+                    int kv_splits, int fold, bool singles) {
     FwdPlan p;
     // The causal chunk kernel (single q-tiles: key splits, folded heads) where
     // the cache before the chunk is at least as long as the chunk, so that the
     // work is nearly a rectangle; shorter, the pairs balance the triangle and
     // skip more of it.
-    const bool chunk = causal && (kv_splits > 1 || fold > 1);
-    if (chunk && (!fwd_chunk_tile(bn, waves, pipe) || Skv - Sq < Sq)) return false;
+    if (singles && (!causal || kv_splits > 1 || fold > 1)) return false;
+    const bool chunk = causal && (kv_splits > 1 || fold > 1 || singles);
+    if (chunk && (!fwd_chunk_tile(bn, waves, pipe) || (!singles && Skv - Sq < Sq))) return false;
     // fold query heads into the rows (contiguous in Q, O and the log-sum-exp)
     const int diag = Skv - Sq;
     if (fold < 1 || H % fold != 0 || (fold > 1 && (long long)fold * Sq > 0x7fffffffLL - 512))
@@ -242,7 +252,25 @@ bool plan_fwd_fixed(const attn_device_desc& desc, int B, int H, int Sq, int Skv,
     const double slots = (double)desc.num_cus * wg;
     const int chunk_tiles = (p.kv_chunk + bn - 1) / bn;
     double cycles;
-    if (!pairs) {
+    auto tiles_of = [&](int qt) {  // causal: tiles up to the q-tile's last row
+        const int last_q = std::min(qt * p.block_m + p.block_m - 1, Sq - 1);
+        const int kv_end = std::min(Skv, last_q + (Skv - Sq) + 1);
+        return (kv_end + bn - 1) / bn;
+    };
+    if (singles) {
+        // Heaviest first on whatever slot is free: no slot idles before the
+        // light q-tiles are dealt, so the time is the mean over the slots and
+        // half a light one, or the heaviest.
+        const int g_eff = (int)std::min<double>(wg, ceil((double)p.grid / desc.num_cus));
+        const double tile_c = g_eff == wg ? tile : tile_cost(g_eff, nullptr, nullptr);
+        double sum = 0.0;
+        for (int qt = 0; qt < p.n_qtiles; ++qt)
+            sum += load_q + kSingleCycles + heg_for(tiles_of(qt), tile_c);
+        const double longest = load_q + kSingleCycles + heg_for(tiles_of(p.n_qtiles - 1), tile_c);
+        const double light = load_q + kSingleCycles + heg_for(tiles_of(0), tile_c);
+        cycles = kSingleFactor *
+                 std::max(sum * B * H / ((double)desc.num_cus * g_eff) + 0.5 * light, longest);
+    } else if (!pairs) {
         // full rounds of wg workgroups per CU, then a last, partial round in
         // which each CU holds only ceil(tail / CUs) of them (they share the
         // CU with fewer others, so each of its tiles costs less)
@@ -256,11 +284,6 @@ bool plan_fwd_fixed(const attn_device_desc& desc, int B, int H, int Sq, int Skv,
     } else {
         // workgroups take q-tile pairs (n-1-u, u), which regularises the
         // triangular work: per workgroup the sum of the pair's tile counts
-        auto tiles_of = [&](int qt) {
-            const int last_q = std::min(qt * p.block_m + p.block_m - 1, Sq - 1);
-            const int kv_end = std::min(Skv, last_q + (Skv - Sq) + 1);
-            return (kv_end + bn - 1) / bn;
-        };
         // workgroups resident per CU: no more than the grid gives each CU
         // (a grid of one workgroup per CU runs its tiles alone on the CU)
         const int g_eff = (int)std::min<double>(wg, ceil((double)p.grid / desc.num_cus));
@@ -322,6 +345,10 @@ static void fwd_for_each(const attn_device_desc& desc, int B, int H, int Sq, int
                     FwdPlan p;
                     if (plan_fwd_fixed(desc, B, H, Sq, Skv, d, causal, bn, waves, pipe, &p, res,
                                        ns, fold))
+                        f(p);
+                    if (causal && chunks && ns == 1 && fold == 1 &&
+                        plan_fwd_fixed(desc, B, H, Sq, Skv, d, causal, bn, waves, pipe, &p, res, 1,
+                                       1, true))
                         f(p);
                 }
 }
@@ -834,10 +861,10 @@ namespace attn {
 int format_fwd_plan(const FwdPlan& p, char* buf, int buflen) {
     return snprintf(buf, buf ? (size_t)buflen : 0,
                     "kind=fwd d=%d BLOCK_M=%d BLOCK_N=%d WAVES=%d PIPE=%d KV_SPLITS=%d "
-                    "KV_CHUNK=%d FOLD=%d causal=%d grid=%lld n_qtiles=%d lds_bytes=%d vgprs=%d "
+                    "KV_CHUNK=%d FOLD=%d CHUNK=%d causal=%d grid=%lld n_qtiles=%d lds_bytes=%d vgprs=%d "
                     "wg_per_cu=%d modeled_us=%.3f bound=%s",
                     p.d, p.block_m, p.block_n, p.waves, p.pipe, p.kv_splits, p.kv_chunk,
-                    p.fold, p.causal, p.grid, p.n_qtiles, p.lds_bytes, p.vgprs, p.wg_per_cu,
+                    p.fold, p.chunk, p.causal, p.grid, p.n_qtiles, p.lds_bytes, p.vgprs, p.wg_per_cu,
                     p.modeled_us, p.bound);
 }
 

@@ -379,9 +379,10 @@ def test_fwd_key_splits_rejected_for_causal(pa):
 
 # ---------------------------------------------------------------- causal chunks
 class forced_chunk_plan(forced_plan):
-    def __init__(self, bn: int, waves: int, pipe: int, splits: int, fold: int):
+    def __init__(self, bn: int, waves: int, pipe: int, splits: int, fold: int,
+                 singles: int = 0):
         super().__init__(bn, waves, pipe)
-        self.value += f",splits={splits},fold={fold}"
+        self.value += f",splits={splits},fold={fold},singles={singles}"
 
 
 # B, Hq, Hkv, Sq, Skv, splits, folded heads: one query; a group whose rows end
@@ -410,6 +411,29 @@ def test_fwd_causal_chunk(pa, tile, d):
         compare(lse, ref_lse, f"chunk {tile} d={d} {CHUNKS[i]} lse", max_abs=LSE_MAX_ABS,
                 mean_abs=LSE_MEAN_ABS)
         assert torch.equal(o16.cpu(), o.cpu().to(torch.bfloat16))
+
+
+# B, Hq, Hkv, Sq, Skv: heads that the XCDs share evenly (8, 16) or not; one
+# q-tile, its edge and one row past it; a short cache before the chunk
+SINGLES = [(1, 1, 1, 1, 1), (1, 3, 1, 256, 256), (2, 4, 2, 257, 257), (2, 8, 2, 300, 333),
+           (1, 5, 5, 700, 800), (1, 8, 8, 513, 513)]
+
+
+@pytest.mark.parametrize("tile", [(64, 8, 3), (64, 4, 1), (32, 4, 1)])
+@pytest.mark.parametrize("d", [64, 128])
+def test_fwd_causal_single_tiles(pa, tile, d):
+    for i, (B, Hq, Hkv, Sq, Skv) in enumerate(SINGLES):
+        q, k, v = _qkv(B, Hq, Hkv, Sq, Skv, d, 1900 + 7 * i + d)
+        qd, kd, vd = q.to(DEV), k.to(DEV), v.to(DEV)
+        sc = float(np.float32(1.0 / math.sqrt(d)))
+        announce(f"attn_fwd_ex causal single q-tiles {tile} d={d} {SINGLES[i]}")
+        with forced_chunk_plan(*tile, 1, 1, singles=1):
+            o, lse = pa.attn_fwd(qd, kd, vd, causal=True, return_lse=True)
+        torch.cuda.synchronize()
+        ref, ref_lse = oracle.attn_gqa(q, k, v, B, Hq, Hkv, Sq, Skv, d, sc, True)
+        compare(o, ref, f"singles {tile} d={d} {SINGLES[i]}")
+        compare(lse, ref_lse, f"singles {tile} d={d} {SINGLES[i]} lse", max_abs=LSE_MAX_ABS,
+                mean_abs=LSE_MEAN_ABS)
 
 
 @pytest.mark.parametrize("causal", [False, True])
