@@ -286,7 +286,8 @@ int stream_workspace(DeviceState* st, size_t bytes, std::unique_lock<std::mutex>
 }
 
 // Optional fixed GEMM tile for the block-size ablation only:
-// ATTN_FORCE_GEMM="bm=256,bn=256,bk=64,wm=2,wn=4,pipe=1[,splits=4[,deep=1]]".
+// ATTN_FORCE_GEMM="bm=256,bn=256,bk=64,wm=2,wn=4,pipe=1[,splits=4[,deep=1]]"
+// (deep: wave groups of the deep-pipeline kernel).
 // Never used to select tiles.
 bool forced_gemm(int* bm, int* bn, int* bk, int* wm, int* wn, int* pipe, int* splits, int* deep) {
     const char* s = getenv("ATTN_FORCE_GEMM");
@@ -799,8 +800,8 @@ int attn_gemm(const void* a, const void* b, void* c, int M, int N, int K, int fl
     GemmPlan plan;
     int bm, bn, bk, wm, wn, pipe, splits, deep;
     if (forced_gemm(&bm, &bn, &bk, &wm, &wn, &pipe, &splits, &deep)) {
-        if (!(deep ? plan_gemm_deep_fixed(st->desc, M, N, K, b_nk, bm, bn, bk, wm, wn, pipe + 1,
-                                          splits, &plan, gemm_resources_forced)
+        if (!(deep ? plan_gemm_deep_fixed(st->desc, M, N, K, b_nk, bm, bn, bk, wm, wn, deep,
+                                          pipe + 1, splits, &plan, gemm_resources_forced)
                    : plan_gemm_fixed(st->desc, M, N, K, b_nk, bm, bn, bk, wm, wn, pipe, &plan,
                                      gemm_resources_forced, splits)))
             return fail(ATTN_EINVAL, "ATTN_FORCE_GEMM names an infeasible or unknown tile");

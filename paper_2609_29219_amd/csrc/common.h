@@ -52,7 +52,7 @@ struct GemmPlan {
     int block_m = 0, block_n = 0, block_k = 0;  // workgroup tile of C and k-step
     int waves_m = 0, waves_n = 0;               // wave grid inside the tile
     int pipe = 0;        // LDS slots - 1: k-tiles in flight while one is multiplied
-    int deep = 0;        // the deep-pipeline kernel (any tile may split K)
+    int deep = 0;        // wave groups of the deep-pipeline kernel (any tile may split K); 0: another
     int b_nk = 0;        // B stored [N][K] (else [K][N])
     int lds_bytes = 0;
     int vgprs = 0;
@@ -220,8 +220,8 @@ int plan_gemm_all(const attn_device_desc& desc, int M, int N, int K, int b_nk, G
 bool plan_gemm_call(const attn_device_desc& desc, int M, int N, int K, int b_nk, bool may_split,
                     GemmPlan* out, GemmResFn res = nullptr);
 bool plan_gemm_deep_fixed(const attn_device_desc& desc, int M, int N, int K, int b_nk, int bm,
-                          int bn, int bk, int wm, int wn, int slots, int k_splits, GemmPlan* out,
-                          GemmResFn res = nullptr);
+                          int bn, int bk, int wm, int wn, int kg, int slots, int k_splits,
+                          GemmPlan* out, GemmResFn res = nullptr);
 bool gemm_resources(const GemmPlan& p, KernelRes* out);
 // The 256 x 256 tile on 2 x 2 waves is the hand-scheduled GEMM kernel: it
 // runs two to four LDS slots (pipe 1..3) and needs K to be a whole number of
@@ -229,10 +229,11 @@ bool gemm_resources(const GemmPlan& p, KernelRes* out);
 inline bool gemm_hand_scheduled(int bm, int bn, int wm, int wn) {
     return bm == 256 && bn == 256 && wm == 2 && wn == 2;
 }
-// Tiles of the deep-pipeline GEMM kernel: BM, BN, BK, wave grid, LDS slots.
+// Tiles of the deep-pipeline GEMM kernel: BM, BN, BK, wave grid, wave groups, LDS slots.
 #define ATTN_DEEP_TILES(X)                                                                     \
-    X(64, 64, 64, 2, 2, 4) X(128, 64, 64, 2, 2, 3) X(64, 128, 64, 2, 2, 3)                     \
-    X(128, 128, 64, 2, 4, 4)
+    X(64, 64, 64, 2, 2, 2, 5) X(128, 64, 64, 2, 2, 2, 3) X(64, 128, 64, 2, 2, 2, 3)            \
+    X(128, 128, 64, 2, 2, 2, 4) X(256, 128, 64, 2, 2, 1, 3) X(128, 256, 64, 2, 2, 1, 3)        \
+    X(128, 128, 64, 2, 2, 1, 2)
 int format_gemm_plan(const GemmPlan& p, char* buf, int buflen);
 int format_fwd_plan(const FwdPlan& p, char* buf, int buflen);
 int format_decode_plan(const DecodePlan& p, char* buf, int buflen);

@@ -211,28 +211,6 @@ struct GemmLoader {
             lds_dma16(b_rsrc, dst + L::A_TILE * 2 + (p - L::A_PIECES) * 1024, o,
                       b_tile0 + (uint32_t)t * b_tile_step);
     }
-    // all of this wave's pieces of k-tile t, of n_k, of which tile `ragged`
-    // (or none: -1) may reach past K; past the last tile they read nothing
-    __device__ __forceinline__ void guarded(int t, int s, int n_k, int ragged) const {
-        if (t < n_k && t != ragged) {
-#pragma unroll
-            for (int j = 0; j < NJ; ++j) piece<false>(t, s, j);
-        } else {
-            const bool past = t >= n_k;
-#pragma unroll
-            for (int j = 0; j < NJ; ++j) {
-                const int p = wave + j * NW;
-                if (p >= NP) break;
-                const bool is_a = p < L::A_PIECES;
-                const int o = past || ((past_k >> j) & 1u) ? OOB : off[j];
-                const uint32_t tile = past ? 0u : (uint32_t)t;
-                lds_dma16(is_a ? a_rsrc : b_rsrc,
-                          lds0 + (uint32_t)s * (SLOT * 2) +
-                              (is_a ? p * 1024 : L::A_TILE * 2 + (p - L::A_PIECES) * 1024),
-                          o, is_a ? a_tile0 + tile * (BK * 2) : b_tile0 + tile * b_tile_step);
-            }
-        }
-    }
     // all of this wave's pieces of k-tile t of n_k
     __device__ __forceinline__ void tile(int t, int s, int n_k) const {
         if (t == n_k - 1) {
@@ -508,7 +486,8 @@ typedef float g_f32x4 __attribute__((ext_vector_type(4)));
 
 // Epilogue of the 16 x 16 accumulator layout, staged in LDS in fp32 (written
 // straight from the accumulator registers) for both output types: a piece
-// is 32 rows by 64 columns (rows padded to 272 bytes); read back, each lane
+// is 32 rows by 64 columns, or 32 where a wave has no more (rows padded to 272
+// bytes); read back, each lane
 // holds 16 contiguous bytes of a row of fp32 output, or 8 values that it
 // rounds to bf16 (16 bytes).  The staging regions overlay the k-tile slots,
 // which no wave may still read (the caller has passed a barrier after its
@@ -516,8 +495,9 @@ typedef float g_f32x4 __attribute__((ext_vector_type(4)));
 template <int MB16, int NB16>
 __device__ __forceinline__ void gemm_store16(const g_f32x4 (&acc)[NB16][MB16], const GemmArgs& args,
                                              uint16_t* lds, int wave, int mbase, int nbase) {
+    constexpr int NQ = NB16 < 4 ? NB16 : 4;  // blocks across a piece
     constexpr int ROW = 272;
-    static_assert(MB16 % 2 == 0 && NB16 % 4 == 0, "pieces of 2 x 4 blocks");
+    static_assert(MB16 % 2 == 0 && NB16 % NQ == 0 && (NQ == 2 || NQ == 4), "pieces of 2 x NQ blocks");
     int elane = threadIdx.x & 63;
     asm volatile("" : "+v"(elane));
     const int M = args.M, N = args.N;
@@ -527,33 +507,35 @@ __device__ __forceinline__ void gemm_store16(const g_f32x4 (&acc)[NB16][MB16], c
 #pragma unroll
     for (int mp = 0; mp < MB16 / 2; ++mp) {
 #pragma unroll
-        for (int nq = 0; nq < NB16 / 4; ++nq) {
+        for (int nq = 0; nq < NB16 / NQ; ++nq) {
 #pragma unroll
             for (int i = 0; i < 2; ++i)
 #pragma unroll
-                for (int j = 0; j < 4; ++j)
+                for (int j = 0; j < NQ; ++j)
                     *reinterpret_cast<g_u32x4*>(stage + (16 * i + (elane & 15)) * ROW +
                                                 (16 * j + 4 * (elane >> 4)) * 4) =
-                        __builtin_bit_cast(g_u32x4, acc[nq * 4 + j][mp * 2 + i]);
+                        __builtin_bit_cast(g_u32x4, acc[nq * NQ + j][mp * 2 + i]);
             asm volatile("" ::: "memory");  // staging writes before the reads
             const int row0 = mbase + mp * 32;
             if (!bf16) {
-                // 16 lanes per row, 4 rows per read
+                // 4 NQ lanes per row
+                constexpr int LPR = 4 * NQ;
 #pragma unroll
-                for (int q = 0; q < 8; ++q) {
-                    const int r = (elane >> 4) + 4 * q;
+                for (int q = 0; q < LPR / 2; ++q) {
+                    const int r = elane / LPR + 64 / LPR * q, c4 = elane % LPR;
                     const g_u32x4 w =
-                        *reinterpret_cast<const g_u32x4*>(stage + r * ROW + (elane & 15) * 16);
-                    const int row = row0 + r, col = nbase + nq * 64 + (elane & 15) * 4;
+                        *reinterpret_cast<const g_u32x4*>(stage + r * ROW + c4 * 16);
+                    const int row = row0 + r, col = nbase + nq * NQ * 16 + c4 * 4;
                     if (row < M && col < N)
                         *reinterpret_cast<g_u32x4*>(cbase + ((long long)row * N + col) * 4) = w;
                 }
             } else {
-                // 8 lanes per row, 8 values each
+                // 2 NQ lanes per row, 8 values each
+                constexpr int LPR = 2 * NQ;
 #pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const int r = (elane >> 3) + 8 * q;
-                    const uint8_t* src = stage + r * ROW + (elane & 7) * 32;
+                for (int q = 0; q < LPR / 2; ++q) {
+                    const int r = elane / LPR + 64 / LPR * q, c8 = elane % LPR;
+                    const uint8_t* src = stage + r * ROW + c8 * 32;
                     const g_u32x4 lo = *reinterpret_cast<const g_u32x4*>(src);
                     const g_u32x4 hi = *reinterpret_cast<const g_u32x4*>(src + 16);
                     g_u32x4 packed;
@@ -568,7 +550,7 @@ __device__ __forceinline__ void gemm_store16(const g_f32x4 (&acc)[NB16][MB16], c
                                              (__bf16)__builtin_bit_cast(float, x1)};
                         packed[e] = __builtin_bit_cast(uint32_t, pr);
                     }
-                    const int row = row0 + r, col = nbase + nq * 64 + (elane & 7) * 8;
+                    const int row = row0 + r, col = nbase + nq * NQ * 16 + c8 * 8;
                     if (row < M && col < N)
                         *reinterpret_cast<g_u32x4*>(cbase + ((long long)row * N + col) * 2) = packed;
                 }
@@ -758,35 +740,143 @@ __global__ __launch_bounds__(256, 1) void gemm_sched_kernel(const GemmArgs args)
 }
 
 // The deep-pipeline kernel, for GEMMs whose output has few tiles (few rows, or
-// both dimensions small): bound by the latency of the k-tiles, not by the
-// matrix core.  Against the generic kernel it keeps NSLOT - 1 k-tiles in flight
-// instead of at most two, and any tile may split K: the grid fills the CUs and
-// each workgroup's chain of k-tiles gets shorter.  One barrier per k-tile: it
-// publishes tile t (the wave's loads of the NSLOT - 2 younger tiles stay in
-// flight) and frees the slot of tile t-1, into which tile t+NSLOT-1 is then
-// loaded.  Tiles past the end load nothing (offsets past the buffer), so that
-// the count of loads in flight is the same on every k-tile.
-// Bounds: 100 x 4096 x 4096 (weights [N][K]) streams 33.5 MB in about 9 us of
-// 4 splits, then the reduction: 27.9 -> 14.3 us; 64 x 16384 x 16384 181 -> 116
-// us (4.6 TB/s), 157 x 312 x 15504 98 -> 17 us.  Where one round of 128 x 128
-// tiles fills the CUs (16384 x 256 x 2048, 2048^3) it runs as the generic kernel
-// does, 25 us: there the tile's LDS traffic binds, not the latency.
-template <int BM, int BN, int BK, int WM, int WN, bool B_NK, int NSLOT>
-__global__ __launch_bounds__(WM * WN * 64, 2) void gemm_deep_kernel(const GemmArgs args) {
-    constexpr int NW = WM * WN;
-    constexpr int MB = BM / (32 * WM), NB = BN / (32 * WN);
-    constexpr int KS = BK / 16;
-    using Ld = GemmLoader<BM, BN, BK, NW, B_NK>;
-    constexpr int SLOT = Ld::SLOT;
-    static_assert(NSLOT >= 3 && (NSLOT - 2) * Ld::NJ < 64, "vmcnt holds 6 bits");
-    static_assert(NSLOT * SLOT * 2 >= NW * 32 * kStageRow, "the staging regions fit the slots");
+// both dimensions small, or one round of 128 x 128 tiles): bound by the latency
+// of the k-tiles and by LDS, not by the matrix core.  NSLOT LDS slots
+// of a 64-value k-tile (NSLOT - 1 of them in flight), any tile may split K.
+//
+// The slots have no padding (DeepLoader): 16-byte chunks are permuted inside
+// their rows instead, so that a slot costs only its data in LDS and in the
+// texture path.  A row of A (64 values of k, 128 bytes) keeps chunk c at place
+// c ^ ((row / 2) % 8): the 16 rows that a ds_read_b128 pass covers, two to a
+// 256-byte span, fall on 16 different places.  A row of B stored [K][N] keeps
+// its 16-column granules at place g ^ f(row), with f different for the rows of
+// equal place parity among the 8 (r .. r+3 and r+8 .. r+11) that a transposed
+// read covers.
+//
+// MFMAs and reads are those of the hand-scheduled kernel (16 x 16 x 32): in each
+// 32-k step the operands of the next step are read into the other register set
+// between the MFMAs of this one, so no MFMA waits for LDS.  With one wave group
+// (KG 1) a wave runs both steps of a k-tile; with two, eight waves share it, each
+// group taking one step over all four sub-tiles, and the groups' sums are added
+// through LDS at the end: two waves per SIMD hide each other's waits at the same
+// LDS traffic.  The barrier that publishes k-tile t+1 precedes the wave's last step
+// of tile t, whose operands are in registers, and frees the slot of tile t for tile
+// t+NSLOT, loaded in that step (and, with one group, the first step of tile t+1).
+// The last tiles' loads run in a loop of their own (chunks past K and tiles past the
+// end get an offset past the buffer), so that the count of loads in flight is the
+// same on every k-tile.
+//
+// Measured (cold operands; before: the generic kernel, and this one with padded
+// slots, 32 x 32 MFMAs and no operand prefetch): 2048^3 27.6 -> 22.3 us (770
+// TFLOP/s), 2950 x 5944 x 4224 230 -> 178, 100 x 4096 x 4096 27.8 -> 12.2 (35 MB in
+// 2.9 TB/s, with the split sum), 16384 x 256 x 2048 29.1 -> 28.9.  128 x 128 tiles
+// by one group: 28.0 us at 2048^3.  There the matrix core is busy 45% of the time
+// and waves wait for k-tiles 39% of theirs; bank conflicts are 2% of LDS cycles.
+constexpr int kDeepBK = 64;
 
-    __shared__ __attribute__((aligned(16))) uint16_t lds[NSLOT * SLOT];
+// Place of 16-column granule 0 of row k of a B tile stored [K][N].
+template <int BN>
+__device__ __forceinline__ int deep_b_place(int k) {
+    return BN == 64 ? ((k >> 1) & 1) | ((k >> 3) & 1) << 1 : (k & 3) | ((k >> 3) & 1) << 2;
+}
+
+template <int BM, int BN, int NW, bool B_NK>
+struct DeepLoader {
+    static constexpr int BK = kDeepBK;
+    static constexpr int A_BYTES = BM * BK * 2, B_BYTES = BN * BK * 2;
+    static constexpr int SLOT = A_BYTES + B_BYTES;  // bytes
+    static constexpr int NJA = A_BYTES / 1024 / NW, NJB = B_BYTES / 1024 / NW;
+    static constexpr int NJ = NJA + NJB;  // 1 KB pieces per wave: A's, then B's
+    static constexpr int OOB = 0x7fffffff;  // any offset past the buffer reads zeros
+    static_assert(A_BYTES % (NW * 1024) == 0 && B_BYTES % (NW * 1024) == 0, "whole pieces");
+    static_assert(NJ <= 32, "one bit per piece");
+
+    dma_rsrc_t a_rsrc, b_rsrc;
+    uint32_t lds0;  // of this wave's first piece
+    uint32_t a_tile0, b_tile0, b_tile_step;
+    int off[NJ];
+    uint32_t past_k;
+
+    __device__ __forceinline__ DeepLoader(const GemmArgs& args, const void* lds, int wave, int lane,
+                                          int m0, int n0, int k0) {
+        const int M = args.M, N = args.N, K = args.K;
+        a_rsrc = make_dma_rsrc(args.a, (uint32_t)((long long)M * K * 2));
+        b_rsrc = make_dma_rsrc(args.b, (uint32_t)((long long)N * K * 2));
+        lds0 = lds_address(lds) + wave * 1024;
+        a_tile0 = __builtin_amdgcn_readfirstlane(((uint32_t)m0 * (uint32_t)K + (uint32_t)k0) * 2u);
+        b_tile0 = __builtin_amdgcn_readfirstlane(
+            B_NK ? ((uint32_t)n0 * (uint32_t)K + (uint32_t)k0) * 2u
+                 : ((uint32_t)k0 * (uint32_t)N + (uint32_t)n0) * 2u);
+        b_tile_step = __builtin_amdgcn_readfirstlane(B_NK ? (uint32_t)BK * 2u
+                                                          : (uint32_t)BK * (uint32_t)N * 2u);
+        const int k_last = K - ((K + BK - 1) / BK - 1) * BK;  // k values of the last tile
+        past_k = 0;
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) {
+            const int pos = (wave + (j < NJA ? j : j - NJA) * NW) * 64 + lane;
+            int o, kc;
+            if (j < NJA || B_NK) {
+                // rows past the end re-read the last row (outputs never stored)
+                const int r = pos / 8, c = (pos % 8) ^ ((r >> 1) & 7);
+                const int row = j < NJA ? min(r, M - 1 - m0) : min(r, N - 1 - n0);
+                o = (row * K + c * 8) * 2;
+                kc = c * 8;
+            } else {
+                // columns past N re-read the last chunk of the row
+                const int r = pos / (BN / 8);
+                const int c = (pos % (BN / 8)) ^ (deep_b_place<BN>(r) << 1);
+                o = (r * N + min(c, (N - n0) / 8 - 1) * 8) * 2;
+                kc = r;
+            }
+            off[j] = o;
+            past_k |= (kc >= k_last ? 1u : 0u) << j;
+        }
+    }
+
+    // this wave's j-th piece of k-tile t into LDS slot s; RAGGED: t may reach past
+    // K (ragged) or lie past the end (past)
+    template <int j, bool RAGGED>
+    __device__ __forceinline__ void piece(int t, int s, bool ragged, bool past) const {
+        const bool zero = RAGGED && (past || (ragged && ((past_k >> j) & 1u)));
+        const uint32_t tile = RAGGED && past ? 0u : (uint32_t)t;
+        const uint32_t dst = lds0 + (uint32_t)s * SLOT;
+        if constexpr (j < NJA)
+            lds_dma16(a_rsrc, dst + j * NW * 1024, zero ? OOB : off[j], a_tile0 + tile * (BK * 2));
+        else
+            lds_dma16(b_rsrc, dst + A_BYTES + (j - NJA) * NW * 1024, zero ? OOB : off[j],
+                      b_tile0 + tile * b_tile_step);
+    }
+};
+
+// Workgroups per CU that the register allocator leaves room for.
+template <int BM, int BN, int NSLOT>
+constexpr int deep_wgs() {
+    return NSLOT * (BM + BN) * kDeepBK * 2 * 2 <= 160 * 1024 ? 2 : 1;
+}
+
+template <int BM, int BN, int WM, int WN, int KG, bool B_NK, int NSLOT>
+__global__ __launch_bounds__(256 * KG, (deep_wgs<BM, BN, NSLOT>() * KG))
+void gemm_deep_kernel(const GemmArgs args) {
+    constexpr int NW = 4 * KG, BK = kDeepBK;
+    static_assert(WM * WN == 4 && (KG == 1 || KG == 2), "four or eight waves");
+    constexpr int MB = BM / (16 * WM), NB = BN / (16 * WN);  // 16 x 16 blocks per wave
+    constexpr int NM = MB * NB, NR = MB + NB;                // MFMAs and operands per 32-k step
+    using Ld = DeepLoader<BM, BN, NW, B_NK>;
+    // pieces of tile t+NSLOT loaded in the step after tile t's slot is freed; with
+    // one group the rest follow in the first step of tile t+1
+    constexpr int NJ0 = KG == 2 ? Ld::NJ : Ld::NJ / 2;
+    static_assert(NSLOT >= 2 && NSLOT * Ld::NJ < 64, "vmcnt holds 6 bits");
+    static_assert((NB & (NB - 1)) == 0, "granules of a wave by exclusive or");
+    static_assert(NSLOT * Ld::SLOT >= 4 * 32 * 272, "the staging regions fit the slots");
+    static_assert(KG == 1 || NSLOT * Ld::SLOT >= BM * BN * 4, "and so do the partial sums");
+
+    __shared__ __attribute__((aligned(16))) uint8_t lds[NSLOT * Ld::SLOT];
 
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int sub = wave & 3, kg = wave >> 2;  // sub-tile, and which 32 of a tile's k (KG 2)
     const GemmOrigin org = gemm_origin(args, BM, BN);
-    const int wm0 = (wave % WM) * MB * 32, wn0 = (wave / WM) * NB * 32;
+    const int wm0 = (sub % WM) * MB * 16, wn0 = (sub / WM) * NB * 16;
     // this workgroup's K range: its split's chunk (all of K unsplit)
     const int k0 = org.split * args.k_chunk;
     const int K = min(args.k_chunk, args.K - k0);
@@ -794,56 +884,162 @@ __global__ __launch_bounds__(WM * WN * 64, 2) void gemm_deep_kernel(const GemmAr
     // the k-tile whose chunks may reach past K (only the last split's last one)
     const int ragged = k0 + K == args.K ? n_k - 1 : -1;
     const Ld ld(args, lds, wave, lane, org.m0, org.n0, k0);
-    const GemmFrags<BM, BN, BK, B_NK> fr(lane, wm0, wn0);
-    const bool more = wave < Ld::NP - Ld::NJ_MIN * NW;
 
-    g_f32x16 acc[NB][MB];
+    // per-lane byte offsets of the operand reads inside a slot: A (and B stored
+    // [N][K]) by step of the k-tile, B stored [K][N] by block
+    constexpr int KS = 2 / KG;  // steps of a k-tile per wave
+    const int l16 = lane & 15, g4 = lane >> 4;
+    int a_off[KS], b_off[B_NK ? KS : NB];
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) {
+        const int place = ((4 * (KG == 2 ? kg : ks) + g4) ^ (l16 >> 1)) * 16;
+        a_off[ks] = (wm0 + l16) * BK * 2 + place;
+        if constexpr (B_NK) b_off[ks] = Ld::A_BYTES + (wn0 + l16) * BK * 2 + place;
+    }
+    if constexpr (!B_NK) {
+        const int row = 8 * g4 + (l16 >> 2) + (KG == 2 ? 32 * kg : 0);
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb)
+            b_off[nb] = Ld::A_BYTES + row * BN * 2 +
+                        (((wn0 >> 4) + nb) ^ deep_b_place<BN>(row)) * 32 + (l16 & 3) * 8;
+    }
+
+    g_f32x4 acc[NB][MB];
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
-        for (int mb = 0; mb < MB; ++mb)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) acc[nb][mb][r] = 0.f;
+        for (int mb = 0; mb < MB; ++mb) acc[nb][mb] = g_f32x4{0.f, 0.f, 0.f, 0.f};
+    g_bf16x8 opa[2][MB], opb[2][NB];  // by parity of the wave's steps
 
-    auto publish = [&]() __attribute__((always_inline)) {
-        if (more)
-            publish_barrier<(NSLOT - 2) * Ld::NJ>();
-        else
-            publish_barrier<(NSLOT - 2) * Ld::NJ_MIN>();
+    // operand f (B blocks, then A blocks) of the wave's step ks of the slot at
+    // `slot` into set `par`
+    auto read = [&](const uint8_t* slot, auto ks_tag, auto par_tag, auto f_tag)
+                    __attribute__((always_inline)) {
+        constexpr int ks = decltype(ks_tag)::value, par = decltype(par_tag)::value;
+        constexpr int f = decltype(f_tag)::value;
+        if constexpr (f >= NB) {
+            opa[par][f - NB] = *reinterpret_cast<const g_bf16x8*>(slot + a_off[ks] +
+                                                                 (f - NB) * 16 * BK * 2);
+        } else if constexpr (B_NK) {
+            opb[par][f] = *reinterpret_cast<const g_bf16x8*>(slot + b_off[ks] + f * 16 * BK * 2);
+        } else {
+            // rows 4 further down keep their granules at the same places
+            const uint8_t* p = slot + b_off[f] + ks * 32 * BN * 2;
+            const g_s16x4 lo = tr_read(reinterpret_cast<const uint16_t*>(p));
+            const g_s16x4 hi = tr_read(reinterpret_cast<const uint16_t*>(p + 4 * BN * 2));
+            const g_s16x8 w = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+            opb[par][f] = __builtin_bit_cast(g_bf16x8, w);
+        }
     };
+    // pieces J0 .. J1-1 of k-tile u into slot su
+    auto load = [&](int u, int su, auto j_tag, auto tail_tag) __attribute__((always_inline)) {
+        constexpr int j = decltype(j_tag)::value;
+        ld.template piece<j, decltype(tail_tag)::value>(u, su, u == ragged, u >= n_k);
+    };
+    using I0 = std::integral_constant<int, 0>;
+    using I1 = std::integral_constant<int, 1>;
+
+    // k-tiles 0 .. NSLOT-2; publish tile 0, then what the last step of "tile -1"
+    // loads of tile NSLOT-1
 #pragma unroll
-    for (int u = 0; u < NSLOT - 1; ++u) ld.guarded(u, u, n_k, ragged);
-    int s = 0, s_load = NSLOT - 1;  // slots of k-tiles t and t + NSLOT - 1
-    for (int t = 0; t < n_k; ++t) {
-        publish();
-        ld.guarded(t + NSLOT - 1, s_load, n_k, ragged);
-        const uint16_t* const st = lds + s * SLOT;
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks) {
-            g_bf16x8 af[MB], bf[NB];
-#pragma unroll
-            for (int mb = 0; mb < MB; ++mb) af[mb] = fr.a(st, mb, ks);
-#pragma unroll
-            for (int nb = 0; nb < NB; ++nb) bf[nb] = fr.b(st, nb, ks);
+    for (int u = 0; u < NSLOT - 1; ++u)
+        static_for<0, Ld::NJ>(
+            [&](auto j) __attribute__((always_inline)) { load(u, u, j, std::true_type{}); });
+    publish_barrier<(NSLOT - 2) * Ld::NJ>();
+    static_for<0, NJ0>([&](auto j) __attribute__((always_inline)) {
+        load(NSLOT - 1, NSLOT - 1, j, std::true_type{});
+    });
+    static_for<0, NR>([&](auto fc) __attribute__((always_inline)) { read(lds, I0{}, I0{}, fc); });
+
+    int s = 0, s_prev = NSLOT - 1;  // slots of k-tiles t and t-1 (then t+NSLOT-1)
+    // One step: the MFMAs of set PAR, between them the reads of the next step's
+    // operands (step NKS of the slot at `src`) and the loads of pieces J0 .. J1-1 of
+    // tile u into slot su.
+    auto step = [&](auto par_tag, const uint8_t* src, auto nks_tag, int u, int su, auto j0_tag,
+                    auto j1_tag, auto tail_tag) __attribute__((always_inline)) {
+        constexpr int PAR = decltype(par_tag)::value;
+        constexpr int J0 = decltype(j0_tag)::value, J1 = decltype(j1_tag)::value;
+        static_for<0, NM>([&](auto ic) __attribute__((always_inline)) {
+            constexpr int i = decltype(ic)::value;
+            constexpr int nb = i / MB, mb = i % MB;
+            acc[nb][mb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(opb[PAR][nb], opa[PAR][mb],
+                                                                 acc[nb][mb], 0, 0, 0);
+            // the next step's operands in the first three quarters of the step
+            static_for<0, NR>([&](auto fc) __attribute__((always_inline)) {
+                if constexpr (decltype(fc)::value * 3 * NM / (4 * NR) == i)
+                    read(src, nks_tag, std::integral_constant<int, PAR ^ 1>{}, fc);
+            });
+            static_for<J0, J1>([&](auto jc) __attribute__((always_inline)) {
+                if constexpr ((decltype(jc)::value - J0) * NM / (J1 - J0) == i)
+                    load(u, su, jc, tail_tag);
+            });
+            __builtin_amdgcn_sched_barrier(0);
+        });
+    };
+    using J0c = std::integral_constant<int, NJ0>;
+    using JEc = std::integral_constant<int, Ld::NJ>;
+    // The wave's steps of k-tile t; TAIL: the tiles that it loads may be ragged or
+    // past the end.  (Past the last tile the operands read are stale and never used.)
+    auto tile = [&](int t, auto par_tag, auto tail_tag) __attribute__((always_inline)) {
+        const int s_next = s + 1 == NSLOT ? 0 : s + 1;
+        const uint8_t* const cur = lds + s * Ld::SLOT;
+        const uint8_t* const next = lds + s_next * Ld::SLOT;
+        if constexpr (KG == 1) {
+            step(I0{}, cur, I1{}, t + NSLOT - 1, s_prev, J0c{}, JEc{}, tail_tag);
+            publish_barrier<(NSLOT - 2) * Ld::NJ>();
+            step(I1{}, next, I0{}, t + NSLOT, s, I0{}, J0c{}, tail_tag);
+        } else {
+            publish_barrier<(NSLOT - 2) * Ld::NJ>();
+            step(par_tag, next, I0{}, t + NSLOT, s, I0{}, JEc{}, tail_tag);
+        }
+        s_prev = s;
+        s = s_next;
+    };
+    int t = 0;
+    if constexpr (KG == 1) {
+        for (; t + NSLOT + 1 < n_k; ++t) tile(t, I0{}, std::false_type{});
+        for (; t < n_k; ++t) tile(t, I0{}, std::true_type{});
+    } else {
+        // two tiles per iteration: the register sets alternate
+        for (; t + NSLOT + 2 < n_k; t += 2) {
+            tile(t, I0{}, std::false_type{});
+            tile(t + 1, I1{}, std::false_type{});
+        }
+        for (; t + 1 < n_k; t += 2) {
+            tile(t, I0{}, std::true_type{});
+            tile(t + 1, I1{}, std::true_type{});
+        }
+        if (t < n_k) tile(t, I0{}, std::true_type{});
+    }
+    // the loads past the end and every wave's reads have completed before the
+    // partial sums and the staging regions overlay the slots
+    publish_barrier<0>();
+    if constexpr (KG == 2) {
+        // the second group's sums (its 32 of every 64 k) into the first's
+        g_f32x4* const part = reinterpret_cast<g_f32x4*>(lds) + sub * NM * 64 + lane;
+        if (kg == 1) {
 #pragma unroll
             for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
-                for (int mb = 0; mb < MB; ++mb)
-                    acc[nb][mb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bf[nb], af[mb],
-                                                                          acc[nb][mb], 0, 0, 0);
+                for (int mb = 0; mb < MB; ++mb) part[(nb * MB + mb) * 64] = acc[nb][mb];
         }
-        s = s + 1 == NSLOT ? 0 : s + 1;
-        s_load = s_load + 1 == NSLOT ? 0 : s_load + 1;
+        __syncthreads();
+        if (kg == 0) {
+#pragma unroll
+            for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+                for (int mb = 0; mb < MB; ++mb) acc[nb][mb] += part[(nb * MB + mb) * 64];
+        }
+        __syncthreads();
+        if (kg == 1) return;
     }
-    // the loads past the end and every wave's reads have completed before the
-    // staging regions overlay the slots
-    publish_barrier<0>();
     GemmArgs out = args;
     if (args.k_splits > 1) {  // a split writes its fp32 partial tile to the workspace
         out.c = args.ws + (long long)org.split * args.M * args.N;
         out.out_bf16 = 0;
     }
-    gemm_store<MB, NB>(acc, out, lds, wave, org.m0 + wm0, org.n0 + wn0);
+    gemm_store16<MB, NB>(acc, out, reinterpret_cast<uint16_t*>(lds), sub, org.m0 + wm0,
+                         org.n0 + wn0);
 }
 
 // C = the sum of the K-split partials ws[s] (fp32 [M][N]) in split order,
@@ -895,12 +1091,10 @@ GemmKernel sched_kernel() {
     return {};
 }
 
-template <int BM, int BN, int BK, int WM, int WN, bool B_NK, int NSLOT>
+template <int BM, int BN, int WM, int WN, int KG, bool B_NK, int NSLOT>
 GemmKernel deep_kernel() {
-    if constexpr (gemm_lds_fits<BM, BN, BK, B_NK, NSLOT - 1>())
-        return {reinterpret_cast<const void*>(&gemm_deep_kernel<BM, BN, BK, WM, WN, B_NK, NSLOT>),
-                WM * WN * 64};
-    return {};
+    return {reinterpret_cast<const void*>(&gemm_deep_kernel<BM, BN, WM, WN, KG, B_NK, NSLOT>),
+            256 * KG};
 }
 
 template <int BM, int BN, int BK, int WM, int WN, bool B_NK>
@@ -928,11 +1122,12 @@ GemmKernel sched_kernel(int pipe) {
 // null) if that variant is not compiled or its LDS does not fit.
 GemmKernel gemm_variant(const GemmPlan& p) {
     if (p.deep) {
-#define ATTN_D(BM, BN, BK, WM, WN, NSLOT)                                                        \
+#define ATTN_D(BM, BN, BK, WM, WN, KG, NSLOT)                                                    \
+    static_assert(BK == kDeepBK, "the deep-pipeline kernel's k-tile");                           \
     if (p.block_m == BM && p.block_n == BN && p.block_k == BK && p.waves_m == WM &&              \
-        p.waves_n == WN && p.pipe == NSLOT - 1)                                                \
-        return p.b_nk ? deep_kernel<BM, BN, BK, WM, WN, true, NSLOT>()                           \
-                      : deep_kernel<BM, BN, BK, WM, WN, false, NSLOT>();
+        p.waves_n == WN && p.deep == KG && p.pipe == NSLOT - 1)                                \
+        return p.b_nk ? deep_kernel<BM, BN, WM, WN, KG, true, NSLOT>()                           \
+                      : deep_kernel<BM, BN, WM, WN, KG, false, NSLOT>();
         ATTN_DEEP_TILES(ATTN_D)
 #undef ATTN_D
         return {};

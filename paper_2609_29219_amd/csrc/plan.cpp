@@ -560,23 +560,39 @@ bool plan_gemm_fixed(const attn_device_desc& desc, int M, int N, int K, int b_nk
     return true;
 }
 
-// Deep-pipeline kernel: the latency of a k-tile that L2 does not hold, with
-// operands small enough for the memory-side cache and with a stream from HBM
-// (cycles of the nominal clock), the share of the stream bandwidth that its
-// tile loads reach, and measured / modelled k-tile rounds.  Fitted to 46 shapes
-// drawn over M 64..16384, N and K 256..16384: with them the pick was within 8%
-// of the best of all tiles and splits at 38, and never above 22%.
-static constexpr double kDeepMallCycles = 2000.0, kDeepHbmCycles = 3200.0;
+// Deep-pipeline kernel: effective latencies of a k-tile from L2, and from beyond it
+// with operands that the memory-side cache holds and with a stream from HBM
+// (cycles of the nominal clock; the loads in flight share them), the barrier, what
+// another round of workgroups costs, and measured / modelled k-tile rounds of each
+// tile.  Fitted to 207 shapes (M 64..16384, N and K 256..16384 with up to 4e11
+// flops, every tile and 10 split counts).  The generic kernel's model reads a tenth
+// low beside it, which kDeepFactor evens out (kDeepRoundsFactor over more than one
+// round of workgroups, where the deep pipeline was rarely the best: 12351 x 656 x 1032
+// 39.4 us against 35.5, 5035 x 2248 x 1136 40.3 against 37.3); the hand-scheduled
+// kernel's model reads high, so it has to be beaten by more (kDeepOverSched:
+// 5173 x 656 x 16160 157 us against 140, 3864 x 272 x 10880 56 against 49).  With them
+// the pick over all kernels was 3.9% slower than the best on average, and the calls
+// 1.24 times as fast as with the other kernels' picks, 6 of 186 slower by over 5%
+// (at most 16%, all under 13 us: 6874 x 264 x 400 8.7 -> 10.1).
+static constexpr double kDeepL2Cycles = 1027.0, kDeepMallCycles = 330.0, kDeepHbmCycles = 8508.0;
 static constexpr double kDeepMallBytes = 64e6;
-static constexpr double kDeepHbmShare = 0.75;
-static constexpr double kDeepScale = 1.1;
+static constexpr double kDeepSyncCycles = 177.0, kDeepRoundCycles = 2493.0;
+static constexpr double kDeepLaunchUs = 2.85, kDeepReduceUs = 3.08, kDeepFactor = 1.1;
+static constexpr double kDeepOverSched = 1.4, kDeepRoundsFactor = 1.25;
+static double deep_scale(int bm, int bn, int slots) {
+    if (bm + bn == 128) return 0.79;
+    if (bm + bn == 192) return bm > bn ? 0.88 : 0.84;
+    if (bm + bn == 256) return slots == 2 ? 1.2 : 0.96;
+    return bm > bn ? 1.25 : 1.27;
+}
 
 bool plan_gemm_deep_fixed(const attn_device_desc& desc, int M, int N, int K, int b_nk, int bm,
-                          int bn, int bk, int wm, int wn, int slots, int k_splits, GemmPlan* out,
-                          GemmResFn res) {
+                          int bn, int bk, int wm, int wn, int kg, int slots, int k_splits,
+                          GemmPlan* out, GemmResFn res) {
     bool known = false;
-#define ATTN_D(BM, BN, BK, WM, WN, NSLOT) \
-    known |= bm == BM && bn == BN && bk == BK && wm == WM && wn == WN && slots == NSLOT;
+#define ATTN_D(BM, BN, BK, WM, WN, KG, NSLOT)                                              \
+    known |= bm == BM && bn == BN && bk == BK && wm == WM && wn == WN && kg == KG &&         \
+             slots == NSLOT;
     ATTN_DEEP_TILES(ATTN_D)
 #undef ATTN_D
     if (!known) return false;
@@ -585,7 +601,7 @@ bool plan_gemm_deep_fixed(const attn_device_desc& desc, int M, int N, int K, int
     if (k_splits < 1 || (long long)(k_splits - 1) * chunk_tiles >= n_k_all) return false;
     if (k_splits > 1 && (long long)k_splits * M * N * 4 > kGemmMaxWorkspaceBytes) return false;
     GemmPlan p;
-    p.deep = 1;
+    p.deep = kg;
     p.k_splits = k_splits;
     p.k_chunk = k_splits > 1 ? chunk_tiles * bk : K;
     p.block_m = bm;
@@ -595,7 +611,7 @@ bool plan_gemm_deep_fixed(const attn_device_desc& desc, int M, int N, int K, int
     p.waves_n = wn;
     p.pipe = slots - 1;
     p.b_nk = b_nk ? 1 : 0;
-    p.lds_bytes = gemm_lds_bytes(bm, bn, bk, b_nk, p.pipe);
+    p.lds_bytes = slots * (bm + bn) * bk * 2;  // no padding
     if (p.lds_bytes > desc.lds_bytes_per_cu) return false;
     int g = desc.lds_bytes_per_cu / p.lds_bytes;
     if (res) {
@@ -620,7 +636,7 @@ bool plan_gemm_deep_fixed(const attn_device_desc& desc, int M, int N, int K, int
                        desc.lds_bytes_per_clk_cu;
     const double body = std::max(mfma, lds);
     const double a_bytes = (double)bm * bk * 2.0, b_bytes = (double)bn * bk * 2.0;
-    const double cu_bw = kDeepHbmShare * desc.hbm_bytes_per_s / desc.num_cus / (desc.clock_ghz * 1e9);
+    const double scale = deep_scale(bm, bn, slots);
     const double far_cycles =
         2.0 * ((double)M * K + (double)K * N) > kDeepMallBytes ? kDeepHbmCycles : kDeepMallCycles;
     // HBM bytes of one round of the whole grid: the tiles of an XCD share panels
@@ -634,9 +650,8 @@ bool plan_gemm_deep_fixed(const attn_device_desc& desc, int M, int N, int K, int
         const double hbm_per_wg =
             std::min(a_bytes + b_bytes, (dm * a_bytes + dn * b_bytes) / xcd_tiles);
         const double f_hbm = hbm_per_wg / (a_bytes + b_bytes);
-        const double load = (1.0 - f_hbm) * desc.tile_latency_cycles + f_hbm * far_cycles;
-        double t = heg_pipe(load / (slots - 1), r * body + desc.tile_sync_cycles, 0.0, 1, 0);
-        return kDeepScale * std::max(t, r * hbm_per_wg / cu_bw);
+        const double load = (1.0 - f_hbm) * kDeepL2Cycles + f_hbm * far_cycles;
+        return scale * heg_pipe(load / (slots - 1), r * body + kDeepSyncCycles, 0.0, 1, 0);
     };
     const int n_k = chunk_tiles;
     const double cu_full = desc.hbm_bytes_per_s / desc.num_cus / (desc.clock_ghz * 1e9);
@@ -649,11 +664,12 @@ bool plan_gemm_deep_fixed(const attn_device_desc& desc, int M, int N, int K, int
     const double tail = (double)p.grid - full * slots_all;
     double cycles = full * pass_of(g);
     if (tail > 0.0) cycles += pass_of((int)std::min<double>(g, ceil(tail / desc.num_cus)));
+    cycles += (full + (tail > 0.0 ? 1.0 : 0.0) - 1.0) * kDeepRoundCycles;
     double us = cycles / (desc.clock_ghz * 1e3);
     const double c_bytes = (double)M * N * 4.0 * (k_splits > 1 ? 2.0 * k_splits + 1.0 : 1.0);
     const double hbm_us =
         ((double)M * K * 2.0 + (double)K * N * 2.0 + c_bytes) / desc.hbm_bytes_per_s * 1e6;
-    p.bound = round_of(std::min(g, std::max(1, (int)(p.grid / desc.num_cus)))) > kDeepScale * body * 1.5
+    p.bound = round_of(std::min(g, std::max(1, (int)(p.grid / desc.num_cus)))) > scale * body * 1.5
                   ? "latency"
                   : (lds > mfma ? "lds" : "mfma");
     if (hbm_us > us) {
@@ -661,10 +677,11 @@ bool plan_gemm_deep_fixed(const attn_device_desc& desc, int M, int N, int K, int
         p.bound = "hbm";
     }
     const double reduce_us =
-        k_splits > 1 ? desc.launch_us + 0.5 +
+        k_splits > 1 ? kDeepReduceUs +
                            (double)M * N * 4.0 * (k_splits + 1.0) / desc.hbm_bytes_per_s * 1e6
                      : 0.0;
-    p.modeled_us = us + desc.launch_us + reduce_us;
+    p.modeled_us = (full + (tail > 0.0 ? 1.0 : 0.0) > 1.0 ? kDeepRoundsFactor : kDeepFactor) *
+                   (us + kDeepLaunchUs + reduce_us);
     *out = p;
     return true;
 }
@@ -678,30 +695,34 @@ bool plan_gemm_call(const attn_device_desc& desc, int M, int N, int K, int b_nk,
         best = p;
         found = true;
     };
-    // The generic 64 x 64 tile stands aside over a long K: its model knows no HBM latency
-    // that two k-tiles in flight cannot hide, and the same tile with three in
-    // flight was faster wherever K was over 16 k-tiles (64 x 16384 x 16384:
-    // modelled 82 us, measured 181, deep 116; 173 x 4976 x 3904: 27.7 against
-    // 19.7).  At 16 k-tiles and fewer the generic one is as fast or faster
-    // (701 x 656 x 864: 8.6 against 9.4).
+    // The generic 64 x 64 tile stands aside over more than 8 k-tiles: its model
+    // knows no latency that two k-tiles in flight cannot hide (156 x 5296 x 1360:
+    // modelled 8.7 us, measured 14.0, the same tile of the deep-pipeline kernel
+    // 9.7; 81 x 2120 x 13224: 114 against 27).  Over fewer it is as fast or faster
+    // (176 x 976 x 368: 4.7 against 4.9).
     for (const GemmTile& t : kGemmTiles)
         for (int pipe = t.pipe_min; pipe <= t.pipe_max; ++pipe)
             for (int splits : kGemmKSplits) {
                 GemmPlan p;
-                if (!(t.bm == 64 && K > 16 * t.bk) &&
+                if (!(t.bm == 64 && K > 8 * t.bk) &&
                     plan_gemm_fixed(desc, M, N, K, b_nk, t.bm, t.bn, t.bk, t.wm, t.wn, pipe, &p,
                                     res, splits))
                     consider(p);
             }
+    if (found && gemm_hand_scheduled(best.block_m, best.block_n, best.waves_m, best.waves_n))
+        best.modeled_us /= kDeepOverSched;
     for (int ks : kGemmDeepKSplits) {
         if (ks > 1 && !may_split) break;
         GemmPlan p;
-#define ATTN_D(BM, BN, BK, WM, WN, NSLOT)                                                       \
-    if (plan_gemm_deep_fixed(desc, M, N, K, b_nk, BM, BN, BK, WM, WN, NSLOT, ks, &p, res))       \
+#define ATTN_D(BM, BN, BK, WM, WN, KG, NSLOT)                                                   \
+    if (plan_gemm_deep_fixed(desc, M, N, K, b_nk, BM, BN, BK, WM, WN, KG, NSLOT, ks, &p, res))   \
         consider(p);
         ATTN_DEEP_TILES(ATTN_D)
 #undef ATTN_D
     }
+    if (found && !best.deep &&
+        gemm_hand_scheduled(best.block_m, best.block_n, best.waves_m, best.waves_n))
+        best.modeled_us *= kDeepOverSched;
     // (a device that none of these fit may still fit that tile)
     if (!found) found = plan_gemm(desc, M, N, K, b_nk, &best, res);
     if (found) *out = best;

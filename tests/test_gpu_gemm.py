@@ -303,22 +303,22 @@ def test_gemm_sweep(pa, case):
 
 # ------------------------------------------------- deep-pipeline kernel
 class forced_deep(forced_gemm):
-    def __init__(self, bm, bn, bk, wm, wn, slots, splits):
+    def __init__(self, bm, bn, bk, wm, wn, groups, slots, splits):
         self.value = (f"bm={bm},bn={bn},bk={bk},wm={wm},wn={wn},pipe={slots - 1},"
-                      f"splits={splits},deep=1")
+                      f"splits={splits},deep={groups}")
 
 
+DEEP_TILES = [(64, 64, 64, 2, 2, 2, 5), (128, 64, 64, 2, 2, 2, 3), (64, 128, 64, 2, 2, 2, 3),
+              (128, 128, 64, 2, 2, 2, 4), (256, 128, 64, 2, 2, 1, 3), (128, 256, 64, 2, 2, 1, 3)]
 # M, N, K, splits: one k-tile; fewer k-tiles than slots; a ragged last k-tile
 # (alone in the last split, too); a tile's edge and one past it; K not of whole
 # 8-value MFMA halves beyond the ragged end; many splits
 DEEP_SHAPES = [(1, 8, 8, 1), (33, 72, 40, 1), (64, 64, 128, 2), (65, 136, 200, 1),
-               (129, 128, 264, 2), (100, 264, 1032, 3), (128, 8, 2056, 17)]
+               (129, 128, 264, 2), (100, 264, 1032, 3), (128, 8, 2056, 17), (300, 392, 776, 1)]
 
 
 @pytest.mark.parametrize("b_nk", [False, True])
-@pytest.mark.parametrize("tile", [(64, 64, 64, 2, 2, 4), (128, 64, 64, 2, 2, 3),
-                                  (64, 128, 64, 2, 2, 3), (128, 128, 64, 2, 4, 4)],
-                         ids=["64x64", "128x64", "64x128", "128x128"])
+@pytest.mark.parametrize("tile", DEEP_TILES, ids=lambda t: f"{t[0]}x{t[1]}")
 def test_gemm_deep_kernel(pa, tile, b_nk):
     for M, N, K, splits in DEEP_SHAPES:
         a, b = _inputs(M, N, K, b_nk, 4700 + M)
@@ -338,7 +338,7 @@ def test_gemm_deep_refuses_an_empty_split(pa):
     a = torch.zeros((64, 128), dtype=torch.bfloat16, device=DEV)
     b = torch.zeros((128, 64), dtype=torch.bfloat16, device=DEV)
     announce("attn_gemm deep, 2 k-tiles over 3 splits refused")
-    with forced_deep(64, 64, 64, 2, 2, 4, 3):
+    with forced_deep(64, 64, 64, 2, 2, 2, 5, 3):
         with pytest.raises(pa.AttnError) as e:
             pa.gemm(a, b)
     assert e.value.code == pa.ATTN_EINVAL
