@@ -76,7 +76,9 @@ hipError_t launch_fwd(const FwdPlan& p, const void* q, const void* k, const void
     // a chunk kernel's rows must be allowed the first key of every split
     const long long last0 = (long long)(n - 1) * a.kv_chunk;
     if (p.fold < 1 || (p.fold > 1 && p.fold != group) ||
-        (p.chunk ? !p.causal || last0 > Skv - Sq : p.causal && (n > 1 || p.fold > 1)))
+        (p.tri && (!p.chunk || p.fold > 1)) ||
+        (p.chunk ? !p.causal || (!p.tri && last0 > Skv - Sq)
+                 : p.causal && (n > 1 || p.fold > 1)))
         return hipErrorInvalidValue;
     if (n > 1 && (p.pipe == 2 || !workspace || p.kv_chunk % p.block_n != 0 ||
                   (long long)(n - 1) * p.kv_chunk >= Skv))
@@ -85,7 +87,15 @@ hipError_t launch_fwd(const FwdPlan& p, const void* q, const void* k, const void
     if (p.d == 64) e = launch_fwd_d64(p, a, stream);
     if (p.d == 128) e = launch_fwd_d128(p, a, stream);
     if (e != hipSuccess || n == 1) return e;
-    return launch_split_combine(p.d, a.ws_m, a.ws_l, a.ws_o, o, out_bf16, lse, rows, n, stream);
+    CombineRows cr;
+    if (p.tri) {
+        cr.sq = Sq;
+        cr.bm = p.block_m;
+        cr.diag = Skv - Sq;
+        cr.chunk = p.kv_chunk;
+    }
+    return launch_split_combine(p.d, a.ws_m, a.ws_l, a.ws_o, o, out_bf16, lse, rows, n, stream,
+                                cr);
 }
 }  // namespace attn
 
@@ -265,15 +275,16 @@ int device_state(DeviceState** out) {
 
 // Optional fixed tile choice for the block-size ablation only:
 // ATTN_FORCE_PLAN="bn=64,waves=8,pipe=2" (optionally ",splits=4", then
-// ",fold=4", the query heads folded into the rows, and ",singles=1", causal
-// single q-tiles).  Never used to select tiles.
-bool forced_fwd(int* bn, int* waves, int* pipe, int* splits, int* fold, int* singles) {
+// ",fold=4", the query heads folded into the rows, and ",form=1", causal single
+// q-tiles, or ",form=2", causal key splits of which early q-tiles have fewer).
+// Never used to select tiles.
+bool forced_fwd(int* bn, int* waves, int* pipe, int* splits, int* fold, int* form) {
     const char* s = getenv("ATTN_FORCE_PLAN");
     if (!s || !*s) return false;
     *splits = *fold = 1;
-    *singles = 0;
-    const int n = sscanf(s, "bn=%d,waves=%d,pipe=%d,splits=%d,fold=%d,singles=%d", bn, waves, pipe,
-                         splits, fold, singles);
+    *form = 0;
+    const int n = sscanf(s, "bn=%d,waves=%d,pipe=%d,splits=%d,fold=%d,form=%d", bn, waves, pipe,
+                         splits, fold, form);
     return n >= 3;
 }
 
@@ -554,11 +565,11 @@ int attn_fwd_ex(const void* q, const void* k, const void* v, void* o, float* lse
     const int c = causal ? 1 : 0;
     FwdPlan plan;
     const int group = Hq / Hkv;
-    int fbn, fw, fpipe, fsplits, ffold, fsingles;
-    if (forced_fwd(&fbn, &fw, &fpipe, &fsplits, &ffold, &fsingles)) {
+    int fbn, fw, fpipe, fsplits, ffold, fform;
+    if (forced_fwd(&fbn, &fw, &fpipe, &fsplits, &ffold, &fform)) {
         if ((ffold != 1 && ffold != group) ||
             !plan_fwd_fixed(st->desc, B, Hq, Sq, Skv, d, c, fbn, fw, fpipe, &plan,
-                            fwd_resources_forced, fsplits, ffold, fsingles != 0))
+                            fwd_resources_forced, fsplits, ffold, fform))
             return fail(ATTN_EINVAL, "ATTN_FORCE_PLAN names an infeasible or unknown tile");
     } else {
         rc = prefill_plan(st, B, Hq, Sq, Skv, d, c, group, &plan);

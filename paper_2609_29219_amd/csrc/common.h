@@ -26,6 +26,7 @@ struct FwdPlan {
     int kv_splits = 1;  // key splits per head (not with q-tile pairs), with a combine kernel
     int kv_chunk = 0;   // keys per split (a multiple of block_n; Skv when unsplit)
     int fold = 1;       // query heads folded into the rows of one head (1, or the whole group)
+    int tri = 0;        // chunk with key splits of which early q-tiles have fewer (Skv < 2 Sq)
     int chunk = 0;      // causal chunk kernel: single q-tiles (may have splits, fold) instead of pairs
     double modeled_us = 0.0;
     const char* bound = "";  // resource that binds the modelled time
@@ -175,11 +176,12 @@ bool plan_fwd(const attn_device_desc& desc, int B, int H, int Sq, int Skv, int d
 bool plan_prefill(const attn_device_desc& desc, int B, int H, int Sq, int Skv, int d, int causal,
                   int group, FwdPlan* out, FwdResFn res = nullptr);
 // fold: query heads folded into the rows (1, or the group).  A causal plan
-// with splits or folded heads is one of the chunk kernel, and so is one with
-// singles (single q-tiles, heaviest first, instead of pairs).
+// with splits or folded heads is one of the chunk kernel, and so is one of form 1
+// (single q-tiles, heaviest first, instead of pairs) or 2 (key splits of which early
+// q-tiles have fewer).
 bool plan_fwd_fixed(const attn_device_desc& desc, int B, int H, int Sq, int Skv, int d,
                     int causal, int bn, int waves, int pipe, FwdPlan* out,
-                    FwdResFn res = nullptr, int kv_splits = 1, int fold = 1, bool singles = false);
+                    FwdResFn res = nullptr, int kv_splits = 1, int fold = 1, int form = 0);
 // Key-split counts tried for prefill without a mask and for causal chunks
 // (each must leave every split non-empty with a chunk that is a multiple of
 // the tile width, and the split grid must stay within kFwdSplitRounds rounds
@@ -246,11 +248,17 @@ hipError_t measure_device(attn_device_desc* d);
 hipError_t launch_fwd(const FwdPlan& p, const void* q, const void* k, const void* v, void* o,
                       float* lse, int group, int out_bf16, long long rows, int Sq, int Skv,
                       float scale, int num_xcds, float* workspace, hipStream_t stream);
+// Rows of a causal call whose q-tiles (of bm rows, sq to a head) have only the
+// splits that start at or before their first row's last key; sq 0: all rows have
+// all splits.
+struct CombineRows {
+    int sq = 0, bm = 1, diag = 0, chunk = 1;
+};
 // o[r] = sum_s 2^(m_rs - M) o_rs / sum_s 2^(m_rs - M) l_rs for each of rows rows
 // (M = max_s m_rs), fp32 or bf16, and optionally lse[r]; partials at r*n + s.
 hipError_t launch_split_combine(int d, const float* ws_m, const float* ws_l, const float* ws_o,
                                 void* o, int out_bf16, float* lse, long long rows, int n_splits,
-                                hipStream_t stream);
+                                hipStream_t stream, CombineRows cr = CombineRows());
 hipError_t launch_decode(const DecodePlan& p, const void* q, const void* k, const void* v,
                          float* o, float* lse, float* workspace, int B, int Hq, int Hkv, int Skv,
                          float scale, int num_xcds, hipStream_t stream);

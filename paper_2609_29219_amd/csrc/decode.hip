@@ -415,15 +415,19 @@ __global__ __launch_bounds__(256) void split_combine_kernel(const float* __restr
                                                             const float* __restrict__ ws_o,
                                                             void* __restrict__ O, int out_bf16,
                                                             float* __restrict__ lse,
-                                                            long long rows, int n_splits) {
+                                                            long long rows, int stride,
+                                                            CombineRows cr) {
     constexpr int LANES = D / 4;            // lanes per row
     constexpr int GROUPS = 256 / LANES;     // lane groups in the workgroup
     const int lane = threadIdx.x % LANES, grp = threadIdx.x / LANES;
     const long long r = PAR ? (long long)blockIdx.x : (long long)blockIdx.x * GROUPS + grp;
     if (!PAR && r >= rows) return;
-    const float* mm = ws_m + r * n_splits;
-    const float* ll = ws_l + r * n_splits;
-    const f32x4_t* oo = reinterpret_cast<const f32x4_t*>(ws_o + r * n_splits * D) + lane;
+    // this row's splits, of the stride that rows are apart
+    const int n_splits =
+        cr.sq ? min(stride, ((int)(r % cr.sq) / cr.bm * cr.bm + cr.diag) / cr.chunk + 1) : stride;
+    const float* mm = ws_m + r * stride;
+    const float* ll = ws_l + r * stride;
+    const f32x4_t* oo = reinterpret_cast<const f32x4_t*>(ws_o + r * stride * D) + lane;
     // four splits' loads in flight (past the end the last split's again, unused),
     // the first four issued before the maximum is known
     constexpr int U = 4;
@@ -488,7 +492,7 @@ __global__ __launch_bounds__(256) void split_combine_kernel(const float* __restr
 template <int D>
 static hipError_t launch_split_combine_d(const float* ws_m, const float* ws_l, const float* ws_o,
                                          void* o, int out_bf16, float* lse, long long rows,
-                                         int n_splits, hipStream_t st) {
+                                         int n_splits, hipStream_t st, CombineRows cr) {
     constexpr int GROUPS = 256 / (D / 4);
     // one workgroup per row while the rows are too few to fill the device with
     // a lane group each, or the chain of splits is long
@@ -497,22 +501,22 @@ static hipError_t launch_split_combine_d(const float* ws_m, const float* ws_l, c
     if (wgs * 256 > 0xffffffffLL) return hipErrorInvalidValue;  // threads of one grid
     if (par)
         hipLaunchKernelGGL((split_combine_kernel<D, true>), dim3((unsigned)wgs), dim3(256), 0, st,
-                           ws_m, ws_l, ws_o, o, out_bf16, lse, rows, n_splits);
+                           ws_m, ws_l, ws_o, o, out_bf16, lse, rows, n_splits, cr);
     else
         hipLaunchKernelGGL((split_combine_kernel<D, false>), dim3((unsigned)wgs), dim3(256), 0, st,
-                           ws_m, ws_l, ws_o, o, out_bf16, lse, rows, n_splits);
+                           ws_m, ws_l, ws_o, o, out_bf16, lse, rows, n_splits, cr);
     return hipGetLastError();
 }
 
 // (ws_o rows 16-byte aligned)
 hipError_t launch_split_combine(int d, const float* ws_m, const float* ws_l, const float* ws_o,
                                 void* o, int out_bf16, float* lse, long long rows, int n_splits,
-                                hipStream_t st) {
+                                hipStream_t st, CombineRows cr) {
     if (rows <= 0) return hipErrorInvalidValue;
     if (d == 64)
-        return launch_split_combine_d<64>(ws_m, ws_l, ws_o, o, out_bf16, lse, rows, n_splits, st);
+        return launch_split_combine_d<64>(ws_m, ws_l, ws_o, o, out_bf16, lse, rows, n_splits, st, cr);
     if (d == 128)
-        return launch_split_combine_d<128>(ws_m, ws_l, ws_o, o, out_bf16, lse, rows, n_splits, st);
+        return launch_split_combine_d<128>(ws_m, ws_l, ws_o, o, out_bf16, lse, rows, n_splits, st, cr);
     return hipErrorInvalidValue;
 }
 

@@ -176,8 +176,10 @@ constexpr int fwd_waves_per_eu() {
 // that are no multiple of the CUs: B3 H16 S6394 d128, 624 pairs on 256 CUs, 534 us
 // as pairs and 474 as singles; d64 B2 H16 S5000 194 and 141.  It is also the kernel
 // of a chunk of queries behind a longer cache (Skv >= 2 Sq), whose work is almost
-// a rectangle: it may split the keys (every row is allowed at least the first
-// key of each split: the diagonal lies in the last one), and may fold the query
+// a rectangle, and of causal calls with few heads: it may split the keys (every
+// row of a q-tile is allowed at least the first key of each of the tile's splits:
+// the diagonal lies in the last one; rows of a short cache have fewer splits than
+// kv_splits, and the workgroups past them end at once), and may fold the query
 // heads of a key/value head into the rows (row i of the folded head is query
 // i % sq_pos of head i / sq_pos), so that a short chunk fills its q-tiles and the
 // group reads each K/V tile once.  Bound: MFMA, once the splits fill the CUs.
@@ -263,13 +265,8 @@ __global__ __launch_bounds__(NW * 64, (fwd_waves_per_eu<D, BN, NW, PIPE>())) voi
         split = 0;
     }
     const int n_pass = (PAIRS && n_qtiles - 1 - unit != unit) ? 2 : 1;
-    // this workgroup's keys: [k0, k0 + Skv) of the head's args.Skv keys
-    const int k0 = split * args.kv_chunk;
-    const int Skv = PAIRS ? args.Skv : min(args.kv_chunk, args.Skv - k0);
-    // causal: key j of this workgroup's allowed iff j <= position + diag (a
-    // row's position is its index, or modulo sq_pos where heads are folded)
+    // a row's position is its index, or modulo sq_pos where heads are folded
     const int sq_pos = CHUNK ? args.sq_pos : Sq;
-    const int diag = CHUNK ? args.Skv - sq_pos - k0 : Skv - Sq;
     // least and greatest position of the rows [first, last]
     auto pos_range = [&](int first, int last, int& lo, int& hi) __attribute__((always_inline)) {
         lo = first;
@@ -284,6 +281,22 @@ __global__ __launch_bounds__(NW * 64, (fwd_waves_per_eu<D, BN, NW, PIPE>())) voi
             }
         }
     };
+    // this workgroup's keys: [k0, k0 + Skv) of the head's args.Skv keys
+    const int k0 = split * args.kv_chunk;
+    bool last_split = false;
+    if (CHUNK && kv_splits > 1) {
+        // A q-tile has only the splits whose first key all of its rows are
+        // allowed, and the last of them reaches its diagonal.
+        int lo, hi;
+        pos_range(unit * BM, min(unit * BM + BM - 1, Sq - 1), lo, hi);
+        const int n_mine = min(kv_splits, (lo + args.Skv - sq_pos) / args.kv_chunk + 1);
+        if (split >= n_mine) return;
+        last_split = split == n_mine - 1;
+    }
+    const int Skv =
+        PAIRS || last_split ? args.Skv - k0 : min(args.kv_chunk, args.Skv - k0);
+    // causal: key j of this workgroup's allowed iff j <= position + diag
+    const int diag = CHUNK ? args.Skv - sq_pos - k0 : Skv - Sq;
     // grouped-query heads: query head bh reads key/value head bh / group
     const long long kv_base = ((long long)(bh / args.group) * args.Skv + k0) * D;
     const uint16_t* Kb = K + kv_base;
@@ -318,9 +331,13 @@ __global__ __launch_bounds__(NW * 64, (fwd_waves_per_eu<D, BN, NW, PIPE>())) voi
     const int qt = qt_of(pass);
     const int q_wave0 = qt * BM + wave * 32;  // first query row of this wave
     const int qrow = q_wave0 + l32;
-    const int qpos = CHUNK ? qrow % sq_pos : qrow;
+    // (a chunk's rows past the end take the last row's position: with their own, or
+    // wrapped, they might be allowed no key of this split, and a row without any
+    // upsets the running maximum of its wave)
+    const int row_max = CHUNK ? Sq - 1 : 0x7fffffff;
+    const int qpos = CHUNK ? min(qrow, row_max) % sq_pos : qrow;
     int wave_lo, wave_hi;  // positions of this wave's rows
-    pos_range(q_wave0, q_wave0 + 31, wave_lo, wave_hi);
+    pos_range(min(q_wave0, row_max), min(q_wave0 + 31, row_max), wave_lo, wave_hi);
 
     // ---- key range of this workgroup ------------------------------------
     int kv_end = Skv;

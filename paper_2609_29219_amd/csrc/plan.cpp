@@ -152,19 +152,21 @@ static double fwd_prim_scale(int d, int bn, int waves, int pipe, int causal) {
 // 17% apart), B3 H16 S6394 534 -> 474 (23%), B3 Hq32 Hkv4 S3583 327 -> 312 (13%),
 // B2 Hq32 Hkv8 S1777 65.1 -> 60.9 (12%); B1 Hq32 Hkv4 S2513 72.0 -> 74.4 (9%),
 // B4 H16 S2048, a whole round of pairs, 83.2 -> 84.3.
-static constexpr double kSingleCycles = 2000.0, kSingleFactor = 1.09;
+static constexpr double kSingleCycles = 2000.0, kSingleFactor = 1.1;
 
 bool plan_fwd_fixed(const attn_device_desc& desc, int B, int H, int Sq, int Skv, int d,
                     int causal, int bn, int waves, int pipe, FwdPlan* out, FwdResFn res,
-                    int kv_splits, int fold, bool singles) {
+                    int kv_splits, int fold, int form) {
+    const bool singles = form == 1, tri = form == 2;
     FwdPlan p;
     // The causal chunk kernel (single q-tiles: key splits, folded heads) where
     // the cache before the chunk is at least as long as the chunk, so that the
     // work is nearly a rectangle; shorter, the pairs balance the triangle and
     // skip more of it.
     if (singles && (!causal || kv_splits > 1 || fold > 1)) return false;
+    if (form < 0 || form > 2 || (tri && (!causal || kv_splits < 2 || fold > 1))) return false;
     const bool chunk = causal && (kv_splits > 1 || fold > 1 || singles);
-    if (chunk && (!fwd_chunk_tile(bn, waves, pipe) || (!singles && Skv - Sq < Sq))) return false;
+    if (chunk && (!fwd_chunk_tile(bn, waves, pipe) || (!form && Skv - Sq < Sq))) return false;
     // fold query heads into the rows (contiguous in Q, O and the log-sum-exp)
     const int diag = Skv - Sq;
     if (fold < 1 || H % fold != 0 || (fold > 1 && (long long)fold * Sq > 0x7fffffffLL - 512))
@@ -173,6 +175,7 @@ bool plan_fwd_fixed(const attn_device_desc& desc, int B, int H, int Sq, int Skv,
     Sq *= fold;
     p.fold = fold;
     p.chunk = chunk ? 1 : 0;
+    p.tri = tri ? 1 : 0;
     p.d = d;
     p.block_n = bn;
     p.waves = waves;
@@ -213,7 +216,9 @@ bool plan_fwd_fixed(const attn_device_desc& desc, int B, int H, int Sq, int Skv,
         if ((Skv + p.kv_chunk - 1) / p.kv_chunk != kv_splits) return false;
         // causal: the diagonal within the last split, so that every row is
         // allowed the first key of each split
-        if (causal && (long long)(kv_splits - 1) * p.kv_chunk > diag) return false;
+        // (in some q-tile's last split, where early ones have fewer)
+        const int lo = tri ? (p.n_qtiles - 1) * p.block_m : 0;
+        if (causal && (long long)(kv_splits - 1) * p.kv_chunk > diag + lo) return false;
         if (rows * d > 0xffffffffLL) return false;  // one combine workgroup per row
     }
     // causal workgroups take q-tile pairs (n-1-u, u), except in chunks
@@ -221,7 +226,7 @@ bool plan_fwd_fixed(const attn_device_desc& desc, int B, int H, int Sq, int Skv,
     p.grid = (long long)B * H * (pairs ? (p.n_qtiles + 1) / 2 : (long long)p.n_qtiles * kv_splits);
     if (p.grid > 0x7fffffffLL) return false;
     // splits fill the device; beyond a few rounds of it they only add partials
-    if (kv_splits > 1 && p.grid > (long long)kFwdSplitRounds * desc.num_cus) return false;
+    if (kv_splits > 1 && p.grid > (long long)(tri ? 2 : 1) * kFwdSplitRounds * desc.num_cus) return false;
 
     const double mfma_cyc = 32768.0 / (desc.mfma_bf16_flops_per_clk_cu / simds);
     const double scores_per_lane = 32.0 * bn / desc.wave_size;
@@ -257,19 +262,40 @@ bool plan_fwd_fixed(const attn_device_desc& desc, int B, int H, int Sq, int Skv,
         const int kv_end = std::min(Skv, last_q + (Skv - Sq) + 1);
         return (kv_end + bn - 1) / bn;
     };
-    if (singles) {
+    double split_share = 1.0;  // of the rows' splits that exist
+    if (tri) {
+        // each q-tile's own splits, dealt to whatever slot is free
+        double sum = 0.0, longest = 0.0, count = 0.0;
+        const double pass0 = load_q + kSingleCycles;
+        for (int qt = 0; qt < p.n_qtiles; ++qt) {
+            const int nv = std::min(kv_splits, (qt * p.block_m + diag) / p.kv_chunk + 1);
+            count += nv;
+        }
+        const int g_eff = (int)std::min<double>(wg, ceil(count * B * H / desc.num_cus));
+        const double tile_c = g_eff == wg ? tile : tile_cost(g_eff, nullptr, nullptr);
+        for (int qt = 0; qt < p.n_qtiles; ++qt) {
+            const int nv = std::min(kv_splits, (qt * p.block_m + diag) / p.kv_chunk + 1);
+            const double full = pass0 + heg_for(chunk_tiles, tile_c);
+            const double last = pass0 + heg_for(tiles_of(qt) - (nv - 1) * chunk_tiles, tile_c);
+            sum += (nv - 1) * full + last;
+            longest = std::max(longest, nv > 1 ? std::max(full, last) : last);
+        }
+        const double mean = sum / count;
+        cycles = kSingleFactor *
+                 std::max(sum * B * H / ((double)desc.num_cus * g_eff) + 0.5 * mean, longest);
+        split_share = count / ((double)p.n_qtiles * kv_splits);
+    } else if (singles) {
         // Heaviest first on whatever slot is free: no slot idles before the
-        // light q-tiles are dealt, so the time is the mean over the slots and
-        // half a light one, or the heaviest.
+        // light q-tiles are dealt, so the time is the mean over the slots, or
+        // the heaviest.
         const int g_eff = (int)std::min<double>(wg, ceil((double)p.grid / desc.num_cus));
         const double tile_c = g_eff == wg ? tile : tile_cost(g_eff, nullptr, nullptr);
         double sum = 0.0;
         for (int qt = 0; qt < p.n_qtiles; ++qt)
             sum += load_q + kSingleCycles + heg_for(tiles_of(qt), tile_c);
         const double longest = load_q + kSingleCycles + heg_for(tiles_of(p.n_qtiles - 1), tile_c);
-        const double light = load_q + kSingleCycles + heg_for(tiles_of(0), tile_c);
         cycles = kSingleFactor *
-                 std::max(sum * B * H / ((double)desc.num_cus * g_eff) + 0.5 * light, longest);
+                 std::max(sum * B * H / ((double)desc.num_cus * g_eff), longest);
     } else if (!pairs) {
         // full rounds of wg workgroups per CU, then a last, partial round in
         // which each CU holds only ceil(tail / CUs) of them (they share the
@@ -302,7 +328,8 @@ bool plan_fwd_fixed(const attn_device_desc& desc, int B, int H, int Sq, int Skv,
     }
     double us = cycles / (desc.clock_ghz * 1e3);
     // Q read once per split, K/V once, O (or the partials) written once
-    const double part_bytes = kv_splits > 1 ? (double)rows * kv_splits * (d + 2) * 4.0 : 0.0;
+    const double part_bytes =
+        kv_splits > 1 ? split_share * rows * kv_splits * (d + 2) * 4.0 : 0.0;
     const double bytes = (double)B * H * ((double)Sq * d * 2.0 * kv_splits + (double)Skv * d * 4.0) +
                          (kv_splits > 1 ? part_bytes : (double)rows * d * 4.0);
     const double hbm_us = bytes / desc.hbm_bytes_per_s * 1e6;
@@ -348,7 +375,11 @@ static void fwd_for_each(const attn_device_desc& desc, int B, int H, int Sq, int
                         f(p);
                     if (causal && chunks && ns == 1 && fold == 1 &&
                         plan_fwd_fixed(desc, B, H, Sq, Skv, d, causal, bn, waves, pipe, &p, res, 1,
-                                       1, true))
+                                       1, 1))
+                        f(p);
+                    if (causal && chunks && ns > 1 && fold == 1 &&
+                        plan_fwd_fixed(desc, B, H, Sq, Skv, d, causal, bn, waves, pipe, &p, res,
+                                       ns, 1, 2))
                         f(p);
                 }
 }
@@ -885,7 +916,7 @@ int format_fwd_plan(const FwdPlan& p, char* buf, int buflen) {
                     "KV_CHUNK=%d FOLD=%d CHUNK=%d causal=%d grid=%lld n_qtiles=%d lds_bytes=%d vgprs=%d "
                     "wg_per_cu=%d modeled_us=%.3f bound=%s",
                     p.d, p.block_m, p.block_n, p.waves, p.pipe, p.kv_splits, p.kv_chunk,
-                    p.fold, p.chunk, p.causal, p.grid, p.n_qtiles, p.lds_bytes, p.vgprs, p.wg_per_cu,
+                    p.fold, p.chunk + p.tri, p.causal, p.grid, p.n_qtiles, p.lds_bytes, p.vgprs, p.wg_per_cu,
                     p.modeled_us, p.bound);
 }
 

@@ -380,9 +380,9 @@ def test_fwd_key_splits_rejected_for_causal(pa):
 # ---------------------------------------------------------------- causal chunks
 class forced_chunk_plan(forced_plan):
     def __init__(self, bn: int, waves: int, pipe: int, splits: int, fold: int,
-                 singles: int = 0):
+                 form: int = 0):
         super().__init__(bn, waves, pipe)
-        self.value += f",splits={splits},fold={fold},singles={singles}"
+        self.value += f",splits={splits},fold={fold},form={form}"
 
 
 # B, Hq, Hkv, Sq, Skv, splits, folded heads: one query; a group whose rows end
@@ -427,13 +427,47 @@ def test_fwd_causal_single_tiles(pa, tile, d):
         qd, kd, vd = q.to(DEV), k.to(DEV), v.to(DEV)
         sc = float(np.float32(1.0 / math.sqrt(d)))
         announce(f"attn_fwd_ex causal single q-tiles {tile} d={d} {SINGLES[i]}")
-        with forced_chunk_plan(*tile, 1, 1, singles=1):
+        with forced_chunk_plan(*tile, 1, 1, form=1):
             o, lse = pa.attn_fwd(qd, kd, vd, causal=True, return_lse=True)
         torch.cuda.synchronize()
         ref, ref_lse = oracle.attn_gqa(q, k, v, B, Hq, Hkv, Sq, Skv, d, sc, True)
         compare(o, ref, f"singles {tile} d={d} {SINGLES[i]}")
         compare(lse, ref_lse, f"singles {tile} d={d} {SINGLES[i]} lse", max_abs=LSE_MAX_ABS,
                 mean_abs=LSE_MEAN_ABS)
+
+
+# B, Hq, Hkv, Sq, Skv, splits: a split per q-tile and one more row; splits that end
+# inside, at and one key past a q-tile's first row; a cache shorter than the chunk;
+# early q-tiles of one split and late ones of all; grouped heads
+TRIANGLES = [(1, 1, 1, 513, 513, 2), (2, 4, 2, 600, 600, 4), (1, 3, 1, 1100, 1100, 8),
+             (1, 2, 2, 700, 801, 3), (1, 1, 1, 1024, 1024, 16), (1, 2, 1, 640, 1000, 6)]
+
+
+@pytest.mark.parametrize("tile", [(64, 8, 3), (64, 4, 1), (32, 4, 1)])
+@pytest.mark.parametrize("d", [64, 128])
+def test_fwd_causal_split_triangle(pa, tile, d):
+    for i, (B, Hq, Hkv, Sq, Skv, splits) in enumerate(TRIANGLES):
+        per = -(-Skv // splits)
+        chunk = -(-per // tile[0]) * tile[0]
+        if -(-Skv // chunk) != splits or \
+                (splits - 1) * chunk > Skv - Sq + (Sq - 1) // (32 * tile[1]) * 32 * tile[1]:
+            continue  # an empty split, or one that no q-tile has
+        q, k, v = _qkv(B, Hq, Hkv, Sq, Skv, d, 2100 + 7 * i + d)
+        qd, kd, vd = q.to(DEV), k.to(DEV), v.to(DEV)
+        sc = float(np.float32(1.0 / math.sqrt(d)))
+        announce(f"attn_fwd_ex causal split triangle {tile} d={d} {TRIANGLES[i]}")
+        # NaN in the workspace where no split of a row writes
+        with forced_split_plan(*tile, 2):
+            pa.attn_fwd(torch.full_like(qd, float("nan")), kd, vd)
+        with forced_chunk_plan(*tile, splits, 1, form=2):
+            o, lse = pa.attn_fwd(qd, kd, vd, causal=True, return_lse=True)
+            o16 = pa.attn_fwd(qd, kd, vd, causal=True, out_dtype=torch.bfloat16)
+        torch.cuda.synchronize()
+        ref, ref_lse = oracle.attn_gqa(q, k, v, B, Hq, Hkv, Sq, Skv, d, sc, True)
+        compare(o, ref, f"triangle {tile} d={d} {TRIANGLES[i]}")
+        compare(lse, ref_lse, f"triangle {tile} d={d} {TRIANGLES[i]} lse", max_abs=LSE_MAX_ABS,
+                mean_abs=LSE_MEAN_ABS)
+        assert torch.equal(o16.cpu(), o.cpu().to(torch.bfloat16))
 
 
 @pytest.mark.parametrize("causal", [False, True])
