@@ -135,13 +135,26 @@ def _check(rc: int):
         raise AttnError(rc, last_error())
 
 
+# The host path is most of the time of the smallest calls (kernels of a few
+# microseconds): the stream is read as a raw handle, without a Python stream
+# object around it, and _require passes a good tensor in one expression.
+try:
+    from torch._C import _cuda_getCurrentRawStream as _raw_stream
+except ImportError:
+    def _raw_stream(index: int) -> int:
+        import torch
+        return torch.cuda.current_stream(index).cuda_stream
+
+
 def _set_stream(t) -> None:
-    import torch
-    lib.attn_set_stream(ctypes.c_void_p(torch.cuda.current_stream(t.device).cuda_stream))
+    lib.attn_set_stream(_raw_stream(t.get_device()))
 
 
 def _require(t, dtype, shape, name):
     import torch
+    if isinstance(t, torch.Tensor) and t.dtype is dtype and t.is_cuda and t.shape == shape and \
+            t.is_contiguous():
+        return
     if not isinstance(t, torch.Tensor) or t.dtype != dtype or not t.is_cuda:
         raise TypeError(f"{name} must be a {dtype} tensor on a HIP device")
     if tuple(t.shape) != tuple(shape):
@@ -167,7 +180,8 @@ def attn_fwd(q, k, v, o=None, scale: float | None = None, causal: bool = False,
         raise ValueError("out_dtype must be torch.float32 or torch.bfloat16")
     if o is None:
         o = torch.empty((B, Hq, Sq, d), dtype=out_dtype, device=q.device)
-    _require(o, out_dtype, (B, Hq, Sq, d), "o")
+    else:
+        _require(o, out_dtype, (B, Hq, Sq, d), "o")
     lse = None
     if return_lse:
         lse = torch.empty((B, Hq, Sq), dtype=torch.float32, device=q.device)
@@ -194,7 +208,8 @@ def attn_decode(q, k, v, o=None, n_splits: int = 0, workspace=None, return_lse: 
     _require(v, torch.bfloat16, (B, Hkv, Skv, d), "v")
     if o is None:
         o = torch.empty((B, Hq, d), dtype=torch.float32, device=q.device)
-    _require(o, torch.float32, (B, Hq, d), "o")
+    else:
+        _require(o, torch.float32, (B, Hq, d), "o")
     lse = None
     if return_lse:
         lse = torch.empty((B, Hq), dtype=torch.float32, device=q.device)
@@ -254,7 +269,8 @@ def gemm(a, b, c=None, b_nk: bool = False, out_dtype=None):
         raise ValueError("out_dtype must be torch.float32 or torch.bfloat16")
     if c is None:
         c = torch.empty((M, N), dtype=out_dtype, device=a.device)
-    _require(c, out_dtype, (M, N), "c")
+    else:
+        _require(c, out_dtype, (M, N), "c")
     flags = (ATTN_OUT_BF16 if out_dtype == torch.bfloat16 else 0) | \
         (ATTN_GEMM_B_NK if b_nk else 0)
     _set_stream(a)
