@@ -599,7 +599,9 @@ bool plan_gemm_fixed(const attn_device_desc& desc, int M, int N, int K, int b_nk
 // flops, every tile and 10 split counts).  The generic kernel's model reads a tenth
 // low beside it, which kDeepFactor evens out (kDeepRoundsFactor over more than one
 // round of workgroups, where the deep pipeline was rarely the best: 12351 x 656 x 1032
-// 39.4 us against 35.5, 5035 x 2248 x 1136 40.3 against 37.3); the hand-scheduled
+// 39.4 us against 35.5, 5035 x 2248 x 1136 40.3 against 37.3; the 256-wide tiles' factor
+// is above the fitted 1.26 for 4336 x 1664 x 3000, 62.3 us against 56.8, and
+// 1886 x 3848 x 4776, 93.5 against 86.1); the hand-scheduled
 // kernel's model reads high, so it has to be beaten by more (kDeepOverSched:
 // 5173 x 656 x 16160 157 us against 140, 3864 x 272 x 10880 56 against 49).  With them
 // the pick over all kernels was 3.9% slower than the best on average, and the calls
@@ -609,12 +611,12 @@ static constexpr double kDeepL2Cycles = 1027.0, kDeepMallCycles = 330.0, kDeepHb
 static constexpr double kDeepMallBytes = 64e6;
 static constexpr double kDeepSyncCycles = 177.0, kDeepRoundCycles = 2493.0;
 static constexpr double kDeepLaunchUs = 2.85, kDeepReduceUs = 3.08, kDeepFactor = 1.1;
-static constexpr double kDeepOverSched = 1.4, kDeepRoundsFactor = 1.25;
+static constexpr double kDeepOverSched = 1.4, kDeepRoundsFactor = 1.5;
 static double deep_scale(int bm, int bn, int slots) {
     if (bm + bn == 128) return 0.79;
     if (bm + bn == 192) return bm > bn ? 0.88 : 0.84;
     if (bm + bn == 256) return slots == 2 ? 1.2 : 0.96;
-    return bm > bn ? 1.25 : 1.27;
+    return 1.5;
 }
 
 bool plan_gemm_deep_fixed(const attn_device_desc& desc, int M, int N, int K, int b_nk, int bm,

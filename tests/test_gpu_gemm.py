@@ -309,7 +309,8 @@ class forced_deep(forced_gemm):
 
 
 DEEP_TILES = [(64, 64, 64, 2, 2, 2, 5), (128, 64, 64, 2, 2, 2, 3), (64, 128, 64, 2, 2, 2, 3),
-              (128, 128, 64, 2, 2, 2, 4), (256, 128, 64, 2, 2, 1, 3), (128, 256, 64, 2, 2, 1, 3)]
+              (128, 128, 64, 2, 2, 2, 4), (256, 128, 64, 2, 2, 1, 3), (128, 256, 64, 2, 2, 1, 3),
+              (128, 128, 64, 2, 2, 1, 2)]
 # M, N, K, splits: one k-tile; fewer k-tiles than slots; a ragged last k-tile
 # (alone in the last split, too); a tile's edge and one past it; K not of whole
 # 8-value MFMA halves beyond the ragged end; many splits
@@ -318,7 +319,7 @@ DEEP_SHAPES = [(1, 8, 8, 1), (33, 72, 40, 1), (64, 64, 128, 2), (65, 136, 200, 1
 
 
 @pytest.mark.parametrize("b_nk", [False, True])
-@pytest.mark.parametrize("tile", DEEP_TILES, ids=lambda t: f"{t[0]}x{t[1]}")
+@pytest.mark.parametrize("tile", DEEP_TILES, ids=lambda t: f"{t[0]}x{t[1]}_{t[6]}")
 def test_gemm_deep_kernel(pa, tile, b_nk):
     for M, N, K, splits in DEEP_SHAPES:
         a, b = _inputs(M, N, K, b_nk, 4700 + M)
