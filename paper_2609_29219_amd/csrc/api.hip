@@ -778,10 +778,10 @@ int attn__gemm_candidates(const attn_device_desc* desc, int M, int N, int K, int
     return len;
 }
 
-// Plan of one GEMM call (cached per shape); may_split: the deep-pipeline kernel
-// may split K, which needs the workspace.
-static int gemm_call_plan(DeviceState* st, int M, int N, int K, int b_nk, bool may_split,
-                          GemmPlan* plan) {
+// Plan of one GEMM shape (cached); may_split false: without K splits, which need the
+// workspace.
+static int gemm_plan_for(DeviceState* st, int M, int N, int K, int b_nk, bool may_split,
+                         GemmPlan* plan) {
     const auto key = std::make_tuple(M, N, K, b_nk + (may_split ? 0 : 2), st->desc.num_cus);
     {
         std::lock_guard<std::mutex> lk(g_mu);
@@ -796,6 +796,30 @@ static int gemm_call_plan(DeviceState* st, int M, int N, int K, int b_nk, bool m
     std::lock_guard<std::mutex> lk(g_mu);
     g_gemm_cache[key] = *plan;
     return ATTN_OK;
+}
+
+// Plan of a GEMM call enqueued now on the thread's stream.  A graph keeps its
+// kernels' pointers, and a later call may replace the workspace: captured, no
+// kernel splits K.
+static int gemm_call_plan(DeviceState* st, int M, int N, int K, int b_nk, GemmPlan* plan) {
+    int rc = gemm_plan_for(st, M, N, K, b_nk, true, plan);
+    if (!rc && plan->k_splits > 1 && capturing(t_stream))
+        rc = gemm_plan_for(st, M, N, K, b_nk, false, plan);
+    return rc;
+}
+
+// Not part of the ABI: the plan line that attn_gemm with these arguments would
+// run now on the thread's stream (eagerly, or into the graph being captured).
+int attn__gemm_call_plan(int M, int N, int K, int flags, char* buf, int buflen) {
+    if (buflen < 0 || (buflen > 0 && !buf)) return fail(ATTN_EINVAL, "bad output buffer");
+    int rc = validate_gemm_dims(M, N, K, flags);
+    if (rc) return rc;
+    DeviceState* st = nullptr;
+    rc = device_state(&st);
+    if (rc) return rc;
+    GemmPlan plan;
+    rc = gemm_call_plan(st, M, N, K, (flags & ATTN_GEMM_B_NK) ? 1 : 0, &plan);
+    return rc ? rc : format_gemm_plan(plan, buf, buflen);
 }
 
 int attn_gemm(const void* a, const void* b, void* c, int M, int N, int K, int flags) {
@@ -817,23 +841,15 @@ int attn_gemm(const void* a, const void* b, void* c, int M, int N, int K, int fl
                                      gemm_resources_forced, splits)))
             return fail(ATTN_EINVAL, "ATTN_FORCE_GEMM names an infeasible or unknown tile");
     } else {
-        rc = gemm_call_plan(st, M, N, K, b_nk, true, &plan);
-        // the deep-pipeline kernel's K splits need the workspace, which a later
-        // call may replace under a graph: captured, it runs unsplit
-        if (!rc && plan.deep && plan.k_splits > 1 && capturing(t_stream))
-            rc = gemm_call_plan(st, M, N, K, b_nk, false, &plan);
+        rc = gemm_call_plan(st, M, N, K, b_nk, &plan);
         if (rc) return rc;
     }
     void* ws = nullptr;
     std::unique_lock<std::mutex> ws_lock;  // held until the kernels are enqueued
     if (plan.k_splits > 1) {
         rc = stream_workspace(st, (size_t)gemm_workspace_bytes(plan, M, N), &ws_lock, &ws);
-        // without memory for them the deep-pipeline kernel's splits are given up
-        if (rc && plan.deep) {
-            rc = gemm_call_plan(st, M, N, K, b_nk, false, &plan);
-            if (!rc && plan.k_splits > 1)
-                rc = stream_workspace(st, (size_t)gemm_workspace_bytes(plan, M, N), &ws_lock, &ws);
-        }
+        // without memory for the partials the call runs unsplit
+        if (rc) rc = gemm_plan_for(st, M, N, K, b_nk, false, &plan);
         if (rc) return rc;
     }
     const hipError_t e = launch_gemm(plan, a, b, c, M, N, K, (flags & ATTN_OUT_BF16) ? 1 : 0,

@@ -218,7 +218,9 @@ bool plan_gemm(const attn_device_desc& desc, int M, int N, int K, int b_nk, Gemm
                GemmResFn res = nullptr);
 int plan_gemm_all(const attn_device_desc& desc, int M, int N, int K, int b_nk, GemmPlan* out,
                   int cap, GemmResFn res = nullptr);
-// The plan of a call: the faster of plan_gemm's and the deep-pipeline kernel's.
+// The plan of a call: the fastest of all kernels'.  may_split false: no kernel splits
+// K, so that the call needs no workspace (such a plan exists whenever one with splits
+// does).
 bool plan_gemm_call(const attn_device_desc& desc, int M, int N, int K, int b_nk, bool may_split,
                     GemmPlan* out, GemmResFn res = nullptr);
 bool plan_gemm_deep_fixed(const attn_device_desc& desc, int M, int N, int K, int b_nk, int bm,

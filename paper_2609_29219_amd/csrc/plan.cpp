@@ -728,20 +728,24 @@ bool plan_gemm_call(const attn_device_desc& desc, int M, int N, int K, int b_nk,
         best = p;
         found = true;
     };
-    // The generic 64 x 64 tile stands aside over more than 8 k-tiles: its model
-    // knows no latency that two k-tiles in flight cannot hide (156 x 5296 x 1360:
-    // modelled 8.7 us, measured 14.0, the same tile of the deep-pipeline kernel
-    // 9.7; 81 x 2120 x 13224: 114 against 27).  Over fewer it is as fast or faster
-    // (176 x 976 x 368: 4.7 against 4.9).
-    for (const GemmTile& t : kGemmTiles)
-        for (int pipe = t.pipe_min; pipe <= t.pipe_max; ++pipe)
-            for (int splits : kGemmKSplits) {
-                GemmPlan p;
-                if (!(t.bm == 64 && K > 8 * t.bk) &&
-                    plan_gemm_fixed(desc, M, N, K, b_nk, t.bm, t.bn, t.bk, t.wm, t.wn, pipe, &p,
-                                    res, splits))
-                    consider(p);
-            }
+    // The generic and the hand-scheduled kernel.  The generic 64 x 64 tile stands
+    // aside over more than 8 k-tiles: its model knows no latency that two k-tiles in
+    // flight cannot hide (156 x 5296 x 1360: modelled 8.7 us, measured 14.0, the same
+    // tile of the deep-pipeline kernel 9.7; 81 x 2120 x 13224: 114 against 27).  Over
+    // fewer it is as fast or faster (176 x 976 x 368: 4.7 against 4.9).
+    auto others = [&](bool long_k_64) {
+        for (const GemmTile& t : kGemmTiles)
+            for (int pipe = t.pipe_min; pipe <= t.pipe_max; ++pipe)
+                for (int splits : kGemmKSplits) {
+                    if (splits > 1 && !may_split) break;
+                    GemmPlan p;
+                    if ((long_k_64 || !(t.bm == 64 && K > 8 * t.bk)) &&
+                        plan_gemm_fixed(desc, M, N, K, b_nk, t.bm, t.bn, t.bk, t.wm, t.wn, pipe,
+                                        &p, res, splits))
+                        consider(p);
+                }
+    };
+    others(false);
     if (found && gemm_hand_scheduled(best.block_m, best.block_n, best.waves_m, best.waves_n))
         best.modeled_us /= kDeepOverSched;
     for (int ks : kGemmDeepKSplits) {
@@ -757,7 +761,7 @@ bool plan_gemm_call(const attn_device_desc& desc, int M, int N, int K, int b_nk,
         gemm_hand_scheduled(best.block_m, best.block_n, best.waves_m, best.waves_n))
         best.modeled_us *= kDeepOverSched;
     // (a device that none of these fit may still fit that tile)
-    if (!found) found = plan_gemm(desc, M, N, K, b_nk, &best, res);
+    if (!found) others(true);
     if (found) *out = best;
     return found;
 }

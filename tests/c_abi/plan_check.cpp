@@ -2,7 +2,8 @@
 // AddressSanitizer and UndefinedBehaviorSanitizer (g++, no device code).
 //
 // Sweeps seeded pseudo-random problem shapes through plan_fwd, plan_fwd_all,
-// plan_decode and plan_gemm with the built-in gfx950 description (register
+// plan_decode, plan_gemm and plan_gemm_call (as a call plans, and as a call that
+// may use no workspace does) with the built-in gfx950 description (register
 // footprints estimated, no device), and checks that every plan satisfies the
 // legality rules the kernels rely on -- tile symbols from the compiled
 // domains, LDS within capacity, the grid the launch will use, key splits that
@@ -111,14 +112,25 @@ bool check_gemm(const attn_device_desc& desc, const GemmPlan& p, int M, int N, i
     CHECK(p.block_m % (32 * p.waves_m) == 0 && p.block_n % (32 * p.waves_n) == 0,
           "tile %dx%d over %dx%d waves", p.block_m, p.block_n, p.waves_m, p.waves_n);
     CHECK(p.block_k == 32 || p.block_k == 64, "BK %d", p.block_k);
-    // the 256 x 256 tile on 2 x 2 waves (hand-scheduled) runs pipes 1..3, the others 0..2
-    const bool scheduled = p.block_m == 256 && p.block_n == 256 && p.waves_m == 2 && p.waves_n == 2;
-    CHECK(scheduled ? p.pipe >= 1 && p.pipe <= 3 : p.pipe >= 0 && p.pipe <= 2, "pipe %d", p.pipe);
+    // the 256 x 256 tile on 2 x 2 waves (hand-scheduled) runs pipes 1..3, the generic
+    // kernel 0..2, the deep-pipeline kernel its own list of tiles
+    const bool scheduled = !p.deep && gemm_hand_scheduled(p.block_m, p.block_n, p.waves_m, p.waves_n);
+    if (p.deep) {
+        bool known = false;
+#define ATTN_D(BM, BN, BK, WM, WN, KG, NSLOT)                                                  \
+    known |= p.block_m == BM && p.block_n == BN && p.block_k == BK && p.waves_m == WM &&       \
+             p.waves_n == WN && p.deep == KG && p.pipe == NSLOT - 1;
+        ATTN_DEEP_TILES(ATTN_D)
+#undef ATTN_D
+        CHECK(known, "deep tile %dx%dx%d", p.block_m, p.block_n, p.block_k);
+    } else {
+        CHECK(scheduled ? p.pipe >= 1 && p.pipe <= 3 : p.pipe >= 0 && p.pipe <= 2, "pipe %d", p.pipe);
+    }
     CHECK(p.lds_bytes > 0 && p.lds_bytes <= desc.lds_bytes_per_cu, "lds %d", p.lds_bytes);
     CHECK(p.tiles_m == (M + p.block_m - 1) / p.block_m &&
               p.tiles_n == (N + p.block_n - 1) / p.block_n,
           "tiles %dx%d", p.tiles_m, p.tiles_n);
-    CHECK(p.k_splits >= 1 && (p.k_splits == 1 || scheduled), "k_splits %d", p.k_splits);
+    CHECK(p.k_splits >= 1 && (p.k_splits == 1 || scheduled || p.deep), "k_splits %d", p.k_splits);
     CHECK(p.grid == (long long)p.tiles_m * p.tiles_n * p.k_splits, "grid %lld", p.grid);
     if (p.k_splits > 1) {
         CHECK(p.k_chunk % p.block_k == 0, "k_chunk %d not whole k-tiles", p.k_chunk);
@@ -131,6 +143,23 @@ bool check_gemm(const attn_device_desc& desc, const GemmPlan& p, int M, int N, i
     }
     CHECK(std::isfinite(p.modeled_us) && p.modeled_us > 0.0, "modeled %g", p.modeled_us);
     CHECK(!scheduled || K % p.block_k == 0, "hand-scheduled tile with K %d not whole k-tiles", K);
+    return true;
+}
+
+// The plan of a call, and that of a call that may use no workspace (captured, or
+// without memory): it exists and no kernel splits K.
+bool check_gemm_call(const attn_device_desc& desc, int M, int N, int K, int b_nk) {
+    GemmPlan p;
+    for (const bool may_split : {true, false}) {
+        CHECK(plan_gemm_call(desc, M, N, K, b_nk, may_split, &p), "no plan for %dx%dx%d split %d",
+              M, N, K, (int)may_split);
+        CHECK(p.b_nk == b_nk, "b_nk %d", p.b_nk);
+        if (!check_gemm(desc, p, M, N, K)) return false;
+        CHECK(may_split || p.k_splits == 1, "%dx%dx%d without a workspace has %d K splits", M, N, K,
+              p.k_splits);
+        CHECK(may_split || gemm_workspace_bytes(p, M, N) == 0, "workspace %lld",
+              gemm_workspace_bytes(p, M, N));
+    }
     return true;
 }
 
@@ -216,6 +245,16 @@ int main(int argc, char** argv) {
         check_gemm(desc, g, M, N, K);
         check_format(g, format_gemm_plan);
         ++plans;
+        if (!check_gemm_call(desc, M, N, K, (int)(next() & 1))) break;
+        plans += 2;
+    }
+    // shapes whose unsplit plan once fell back to a kernel that splits K itself
+    const int split_shapes[][4] = {{195, 4072, 9216, 0}, {1053, 4288, 3232, 1},
+                                   {928, 4152, 7520, 0}, {105, 296, 11232, 0},
+                                   {123, 264, 15424, 0}};
+    for (const auto& s : split_shapes) {
+        if (!check_gemm_call(desc, s[0], s[1], s[2], s[3])) break;
+        plans += 2;
     }
     if (failures) return 1;
     std::printf("plan_check ok: %d plans\n", plans);

@@ -12,6 +12,7 @@ sum_k |a_mk b_kn| next to C.
 """
 from __future__ import annotations
 
+import ctypes
 import itertools
 
 import numpy as np
@@ -370,3 +371,49 @@ def test_gemm_few_rows_in_a_graph(pa):
         graph.replay()
         torch.cuda.synchronize()
         _check(c, want, absc, K, f"replay after an eager call with {n} columns")
+
+
+def call_plan(pa, M, N, K, b_nk=False):
+    """The plan that a call on the current stream would run now."""
+    buf = ctypes.create_string_buffer(512)
+    pa.lib.attn_set_stream(torch.cuda.current_stream().cuda_stream)
+    rc = pa.lib.attn__gemm_call_plan(M, N, K, pa.ATTN_GEMM_B_NK if b_nk else 0, buf, 512)
+    assert rc > 0, pa.last_error()
+    return pa.parse_plan(buf.value.decode())
+
+
+# shapes that split K in an eager call: with the deep-pipeline kernel, and with the
+# hand-scheduled one (of which the first once was captured with its splits)
+GRAPH_SHAPES = [(195, 4072, 9216, False), (70, 512, 4096, True), (256, 256, 16384, False),
+                (1053, 4288, 3232, True), (928, 4152, 7520, False)]
+
+
+@pytest.mark.parametrize("shape", GRAPH_SHAPES, ids=lambda s: f"{s[0]}x{s[1]}x{s[2]}")
+def test_gemm_in_a_graph_uses_no_workspace(pa, shape):
+    # the invariant is checked on the plan: a replay that used a released workspace
+    # could still give the right sums
+    M, N, K, b_nk = shape
+    a, b = _inputs(M, N, K, b_nk, 4900 + M)
+    ad, bd = a.to(DEV), b.to(DEV)
+    c = torch.empty((M, N), dtype=torch.float32, device=DEV)
+    rows = np.unique(np.linspace(0, M - 1, 12).astype(int))
+    want, absc = oracle.gemm(a, b, M, N, K, b_nk=b_nk, rows=rows, with_abs=True)
+    side = torch.cuda.Stream()
+    announce(f"attn_gemm {shape} captured")
+    with torch.cuda.stream(side):
+        assert call_plan(pa, *shape)["K_SPLITS"] > 1
+        pa.gemm(ad, bd, c=c, b_nk=b_nk)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=side):
+        assert call_plan(pa, *shape)["K_SPLITS"] == 1
+        pa.gemm(ad, bd, c=c, b_nk=b_nk)
+    for n in (512, 8192):
+        c.fill_(float("nan"))
+        with torch.cuda.stream(side):  # grows the stream's workspace
+            x = torch.zeros((64, 8192), dtype=torch.bfloat16, device=DEV)
+            pa.gemm(x, torch.zeros((8192, n), dtype=torch.bfloat16, device=DEV))
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        _check(c.cpu()[torch.from_numpy(rows)], want, absc, K, f"replay {shape} after {n} columns")
