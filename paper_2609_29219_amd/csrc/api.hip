@@ -392,7 +392,7 @@ int attn_get_plan_for(const attn_device_desc* desc, int kind, int B, int H, int 
     if (kind == ATTN_KIND_FWD) {
         if (causal && Sq > Skv) return fail(ATTN_EUNSUPPORTED, "causal needs Sq <= Skv");
         FwdPlan p;
-        if (!plan_prefill(*desc, B, H, Sq, Skv, d, causal ? 1 : 0, 1, &p, res))
+        if (!plan_prefill(*desc, B, H, Sq, Skv, d, causal ? 1 : 0, 1, true, &p, res))
             return fail(ATTN_EUNSUPPORTED, "no feasible prefill plan");
         return format_fwd_plan(p, buf, buflen);
     }
@@ -510,13 +510,14 @@ int attn_get_plan(int kind, int B, int H, int Sq, int Skv, int d, int causal, in
     return attn_get_plan_for(nullptr, kind, B, H, Sq, Skv, d, causal, n_splits, buf, buflen);
 }
 
-// Plan of one prefill call (cached per shape): looked up under the lock,
-// planned (which queries the runtime for the compiled kernels' footprint)
-// outside it.  group: query heads per key/value head; 0: the plain form only
-// (no chunk kernel, no folded heads).
+// Plan of one prefill shape (cached): looked up under the lock, planned (which
+// queries the runtime for the compiled kernels' footprint) outside it.  group:
+// query heads per key/value head; may_split false: without key splits, which need
+// the workspace.
 static int prefill_plan(DeviceState* st, int B, int Hq, int Sq, int Skv, int d, int causal,
-                        int group, FwdPlan* plan) {
-    const auto key = std::make_tuple(B, Hq, Sq, Skv, d, causal, st->desc.num_cus, group);
+                        int group, bool may_split, FwdPlan* plan) {
+    const auto key = std::make_tuple(B, Hq, Sq, Skv, d, causal + (may_split ? 0 : 2),
+                                     st->desc.num_cus, group);
     {
         std::lock_guard<std::mutex> lk(g_mu);
         auto it = g_fwd_cache.find(key);
@@ -525,8 +526,7 @@ static int prefill_plan(DeviceState* st, int B, int Hq, int Sq, int Skv, int d, 
             return ATTN_OK;
         }
     }
-    if (!(group ? plan_prefill(st->desc, B, Hq, Sq, Skv, d, causal, group, plan, fwd_resources)
-                : plan_fwd(st->desc, B, Hq, Sq, Skv, d, causal, plan, fwd_resources)))
+    if (!plan_prefill(st->desc, B, Hq, Sq, Skv, d, causal, group, may_split, plan, fwd_resources))
         return fail(ATTN_EUNSUPPORTED, "no feasible prefill plan for this shape");
     std::lock_guard<std::mutex> lk(g_mu);
     g_fwd_cache[key] = *plan;
@@ -541,6 +541,33 @@ static bool capturing(hipStream_t stream) {
         return false;
     }
     return status != hipStreamCaptureStatusNone;
+}
+
+// Plan of a prefill call enqueued now on the thread's stream.  A graph keeps its
+// kernels' pointers, and a later call may replace the workspace: captured, no form
+// splits the keys.
+static int prefill_call_plan(DeviceState* st, int B, int Hq, int Sq, int Skv, int d, int causal,
+                             int group, FwdPlan* plan) {
+    int rc = prefill_plan(st, B, Hq, Sq, Skv, d, causal, group, true, plan);
+    if (!rc && plan->kv_splits > 1 && capturing(t_stream))
+        rc = prefill_plan(st, B, Hq, Sq, Skv, d, causal, group, false, plan);
+    return rc;
+}
+
+// Not part of the ABI: the plan line that attn_fwd_ex with these arguments would
+// run now on the thread's stream (eagerly, or into the graph being captured).
+int attn__fwd_call_plan(int B, int Hq, int Hkv, int Sq, int Skv, int d, int causal, char* buf,
+                        int buflen) {
+    if (buflen < 0 || (buflen > 0 && !buf)) return fail(ATTN_EINVAL, "bad output buffer");
+    if (B <= 0 || Hq <= 0 || Hkv <= 0 || Hq % Hkv != 0 || Sq <= 0 || Skv <= 0)
+        return fail(ATTN_EINVAL, "bad dimensions");
+    if (causal && Sq > Skv) return fail(ATTN_EUNSUPPORTED, "causal needs Sq <= Skv");
+    DeviceState* st = nullptr;
+    int rc = device_state(&st);
+    if (rc) return rc;
+    FwdPlan plan;
+    rc = prefill_call_plan(st, B, Hq, Sq, Skv, d, causal ? 1 : 0, Hq / Hkv, &plan);
+    return rc ? rc : format_fwd_plan(plan, buf, buflen);
 }
 
 int attn_fwd_ex(const void* q, const void* k, const void* v, void* o, float* lse, int B, int Hq,
@@ -572,12 +599,7 @@ int attn_fwd_ex(const void* q, const void* k, const void* v, void* o, float* lse
                             fwd_resources_forced, fsplits, ffold, fform))
             return fail(ATTN_EINVAL, "ATTN_FORCE_PLAN names an infeasible or unknown tile");
     } else {
-        rc = prefill_plan(st, B, Hq, Sq, Skv, d, c, group, &plan);
-        // A causal chunk's or folded call's key splits need the workspace, which
-        // a later call may replace: a graph keeps its kernels' pointers, so a
-        // captured call takes the plain form, whose causal plans need none.
-        if (!rc && plan.kv_splits > 1 && (plan.chunk || plan.fold > 1) && capturing(t_stream))
-            rc = prefill_plan(st, B, Hq, Sq, Skv, d, c, 0, &plan);
+        rc = prefill_call_plan(st, B, Hq, Sq, Skv, d, c, group, &plan);
         if (rc) return rc;
     }
     const long long rows = (long long)B * Hq * Sq;
@@ -585,12 +607,8 @@ int attn_fwd_ex(const void* q, const void* k, const void* v, void* o, float* lse
     std::unique_lock<std::mutex> ws_lock;  // held until the kernels are enqueued
     if (plan.kv_splits > 1) {
         rc = stream_workspace(st, (size_t)fwd_workspace_bytes(plan, rows), &ws_lock, &ws);
-        // without memory for them a chunk's or folded call's splits are given up
-        if (rc && (plan.chunk || plan.fold > 1)) {
-            rc = prefill_plan(st, B, Hq, Sq, Skv, d, c, 0, &plan);
-            if (!rc && plan.kv_splits > 1)
-                rc = stream_workspace(st, (size_t)fwd_workspace_bytes(plan, rows), &ws_lock, &ws);
-        }
+        // without memory for the partials the call runs unsplit
+        if (rc) rc = prefill_plan(st, B, Hq, Sq, Skv, d, c, group, false, &plan);
         if (rc) return rc;
     }
     hipError_t e = launch_fwd(plan, q, k, v, o, lse, group, (flags & ATTN_OUT_BF16) ? 1 : 0,

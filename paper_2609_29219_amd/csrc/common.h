@@ -172,9 +172,11 @@ void default_desc(attn_device_desc* out);
 bool plan_fwd(const attn_device_desc& desc, int B, int H, int Sq, int Skv, int d, int causal,
               FwdPlan* out, FwdResFn res = nullptr);
 // The plan of a call: the fastest of plan_fwd's candidates, causal chunks, and
-// (H query heads, group of them to a key/value head) folded heads.
+// (H query heads, group of them to a key/value head) folded heads.  may_split
+// false: no form splits the keys, so that the call needs no workspace (such a plan
+// exists whenever one with splits does).
 bool plan_prefill(const attn_device_desc& desc, int B, int H, int Sq, int Skv, int d, int causal,
-                  int group, FwdPlan* out, FwdResFn res = nullptr);
+                  int group, bool may_split, FwdPlan* out, FwdResFn res = nullptr);
 // fold: query heads folded into the rows (1, or the group).  A causal plan
 // with splits or folded heads is one of the chunk kernel, and so is one of form 1
 // (single q-tiles, heaviest first, instead of pairs) or 2 (key splits of which early

@@ -360,15 +360,16 @@ bool plan_fwd_fixed(const attn_device_desc& desc, int B, int H, int Sq, int Skv,
 }
 
 // Every feasible candidate of one form, in search order: fold 1 is the plain
-// form (no key splits under a causal mask unless chunks are asked for).
+// form (no key splits under a causal mask unless chunks are asked for, and none
+// at all without may_split).
 template <typename F>
 static void fwd_for_each(const attn_device_desc& desc, int B, int H, int Sq, int Skv, int d,
-                         int causal, FwdResFn res, bool chunks, int fold, F&& f) {
+                         int causal, FwdResFn res, bool chunks, int fold, bool may_split, F&& f) {
     for (int bn : kFwdBlockN)
         for (int waves : kFwdWaves)
             for (int pipe : kFwdPipe)
                 for (int ns : kFwdKvSplits) {
-                    if (causal && !chunks && ns > 1) break;
+                    if (ns > 1 && (!may_split || (causal && !chunks))) break;
                     FwdPlan p;
                     if (plan_fwd_fixed(desc, B, H, Sq, Skv, d, causal, bn, waves, pipe, &p, res,
                                        ns, fold))
@@ -398,16 +399,16 @@ struct FwdBest {
 bool plan_fwd(const attn_device_desc& desc, int B, int H, int Sq, int Skv, int d, int causal,
               FwdPlan* out, FwdResFn res) {
     FwdBest b;
-    fwd_for_each(desc, B, H, Sq, Skv, d, causal, res, false, 1, b);
+    fwd_for_each(desc, B, H, Sq, Skv, d, causal, res, false, 1, true, b);
     if (b.found) *out = b.best;
     return b.found;
 }
 
 bool plan_prefill(const attn_device_desc& desc, int B, int H, int Sq, int Skv, int d, int causal,
-                  int group, FwdPlan* out, FwdResFn res) {
+                  int group, bool may_split, FwdPlan* out, FwdResFn res) {
     FwdBest b;
-    fwd_for_each(desc, B, H, Sq, Skv, d, causal, res, true, 1, b);
-    if (group > 1) fwd_for_each(desc, B, H, Sq, Skv, d, causal, res, true, group, b);
+    fwd_for_each(desc, B, H, Sq, Skv, d, causal, res, true, 1, may_split, b);
+    if (group > 1) fwd_for_each(desc, B, H, Sq, Skv, d, causal, res, true, group, may_split, b);
     if (b.found) *out = b.best;
     return b.found;
 }
@@ -415,7 +416,7 @@ bool plan_prefill(const attn_device_desc& desc, int B, int H, int Sq, int Skv, i
 int plan_fwd_all(const attn_device_desc& desc, int B, int H, int Sq, int Skv, int d, int causal,
                  FwdPlan* out, int cap, FwdResFn res) {
     int n = 0;
-    fwd_for_each(desc, B, H, Sq, Skv, d, causal, res, false, 1, [&](const FwdPlan& p) {
+    fwd_for_each(desc, B, H, Sq, Skv, d, causal, res, false, 1, true, [&](const FwdPlan& p) {
         if (n < cap) out[n] = p;
         ++n;
     });

@@ -2,8 +2,8 @@
 // AddressSanitizer and UndefinedBehaviorSanitizer (g++, no device code).
 //
 // Sweeps seeded pseudo-random problem shapes through plan_fwd, plan_fwd_all,
-// plan_decode, plan_gemm and plan_gemm_call (as a call plans, and as a call that
-// may use no workspace does) with the built-in gfx950 description (register
+// plan_decode, plan_gemm, plan_prefill and plan_gemm_call (the last two as a call
+// plans, and as a call that may use no workspace does) with the built-in gfx950 description (register
 // footprints estimated, no device), and checks that every plan satisfies the
 // legality rules the kernels rely on -- tile symbols from the compiled
 // domains, LDS within capacity, the grid the launch will use, key splits that
@@ -57,8 +57,11 @@ bool in(int v, const int* set, int n) {
     return false;
 }
 
+// H, Sq: the heads and rows of the launch (the group folded into the rows where
+// the plan folds it); sq_pos: the queries of an unfolded head.
 bool check_fwd(const attn_device_desc& desc, const FwdPlan& p, int B, int H, int Sq, int Skv,
-               int d, int causal) {
+               int d, int causal, int sq_pos = 0) {
+    if (!sq_pos) sq_pos = Sq;
     CHECK(p.d == d, "d %d", p.d);
     CHECK(in(p.block_n, kFwdBlockN, 3) && in(p.waves, kFwdWaves, 2) && in(p.pipe, kFwdPipe, 4),
           "tile (%d, %d, %d)", p.block_n, p.waves, p.pipe);
@@ -70,16 +73,33 @@ bool check_fwd(const attn_device_desc& desc, const FwdPlan& p, int B, int H, int
     CHECK(p.n_qtiles == (Sq + p.block_m - 1) / p.block_m, "n_qtiles %d", p.n_qtiles);
     CHECK(p.kv_splits >= 1, "splits %d", p.kv_splits);
     const long long grid = (long long)B * H *
-                           (causal ? (p.n_qtiles + 1) / 2 : (long long)p.n_qtiles * p.kv_splits);
+                           (causal && !p.chunk ? (p.n_qtiles + 1) / 2
+                                               : (long long)p.n_qtiles * p.kv_splits);
     CHECK(p.grid == grid && p.grid > 0 && p.grid <= 0x7fffffffLL, "grid %lld (want %lld)",
           p.grid, grid);
     if (p.kv_splits > 1) {
-        CHECK(!causal && p.pipe != 2, "splits with causal or ping-pong");
+        CHECK((!causal || p.chunk) && p.pipe != 2, "splits with q-tile pairs or ping-pong");
         CHECK(p.kv_chunk % p.block_n == 0, "chunk %d not whole tiles", p.kv_chunk);
         CHECK((long long)(p.kv_splits - 1) * p.kv_chunk < Skv, "empty last split");
         CHECK((long long)p.kv_splits * p.kv_chunk >= Skv, "keys not covered");
     } else {
         CHECK(p.kv_chunk == Skv, "unsplit chunk %d != Skv %d", p.kv_chunk, Skv);
+    }
+    if (p.chunk) {
+        CHECK(causal && fwd_chunk_tile(p.block_n, p.waves, p.pipe), "chunk tile (%d, %d, %d)",
+              p.block_n, p.waves, p.pipe);
+        // the last split's first key is one that a row of some q-tile (the
+        // triangle: its last) is allowed, and without the triangle every row is
+        const long long last0 = (long long)(p.kv_splits - 1) * p.kv_chunk;
+        const int first_row = p.tri ? (p.n_qtiles - 1) * p.block_m : 0;
+        CHECK(last0 <= Skv - sq_pos + first_row, "no row reaches split %d", p.kv_splits - 1);
+        CHECK(!p.tri || (p.fold == 1 && p.kv_splits > 1), "triangle with fold %d, %d splits", p.fold,
+              p.kv_splits);
+        // workspace: the split grid is bounded by rounds of the compute units
+        CHECK(p.kv_splits == 1 || p.grid <= (p.tri ? 2LL : 1LL) * kFwdSplitRounds * desc.num_cus,
+              "split grid %lld", p.grid);
+    } else {
+        CHECK(!p.tri && (!causal || p.fold == 1), "tri %d, causal fold %d", p.tri, p.fold);
     }
     CHECK(std::isfinite(p.modeled_us) && p.modeled_us > 0.0, "modeled %g", p.modeled_us);
     CHECK(p.bound && *p.bound, "no bound");
@@ -146,23 +166,6 @@ bool check_gemm(const attn_device_desc& desc, const GemmPlan& p, int M, int N, i
     return true;
 }
 
-// The plan of a call, and that of a call that may use no workspace (captured, or
-// without memory): it exists and no kernel splits K.
-bool check_gemm_call(const attn_device_desc& desc, int M, int N, int K, int b_nk) {
-    GemmPlan p;
-    for (const bool may_split : {true, false}) {
-        CHECK(plan_gemm_call(desc, M, N, K, b_nk, may_split, &p), "no plan for %dx%dx%d split %d",
-              M, N, K, (int)may_split);
-        CHECK(p.b_nk == b_nk, "b_nk %d", p.b_nk);
-        if (!check_gemm(desc, p, M, N, K)) return false;
-        CHECK(may_split || p.k_splits == 1, "%dx%dx%d without a workspace has %d K splits", M, N, K,
-              p.k_splits);
-        CHECK(may_split || gemm_workspace_bytes(p, M, N) == 0, "workspace %lld",
-              gemm_workspace_bytes(p, M, N));
-    }
-    return true;
-}
-
 // A formatter writes at most buflen bytes, NUL-terminated, and returns the
 // full length whatever buflen is.
 template <typename P, typename F>
@@ -180,6 +183,42 @@ bool check_format(const P& p, F fmt) {
                   "buflen %d prefix", len);
         }
         for (int i = len; i < len + 8; ++i) CHECK(buf[(size_t)i] == '#', "wrote past %d", len);
+    }
+    return true;
+}
+
+// The plan of a prefill call with H query heads, group of them to a key/value
+// head, and that of a call that may use no workspace (captured, or without memory):
+// it exists, folds all of a group or nothing, and the second one splits no keys.
+bool check_prefill_call(const attn_device_desc& desc, int B, int H, int group, int Sq, int Skv,
+                        int d, int causal) {
+    FwdPlan p;
+    for (const bool may_split : {true, false}) {
+        CHECK(plan_prefill(desc, B, H, Sq, Skv, d, causal, group, may_split, &p),
+              "no plan for B%d H%d group %d Sq%d Skv%d", B, H, group, Sq, Skv);
+        CHECK(p.fold == 1 || p.fold == group, "fold %d of group %d", p.fold, group);
+        if (!check_fwd(desc, p, B, H / p.fold, Sq * p.fold, Skv, d, causal, Sq)) return false;
+        CHECK(may_split || p.kv_splits == 1, "B%d H%d group %d Sq%d Skv%d without a workspace: %d "
+              "splits", B, H, group, Sq, Skv, p.kv_splits);
+        CHECK(may_split || fwd_workspace_bytes(p, (long long)B * H * Sq) == 0, "workspace");
+        if (!check_format(p, format_fwd_plan)) return false;
+    }
+    return true;
+}
+
+// The plan of a GEMM call, and that of a call that may use no workspace (captured,
+// or without memory): it exists and no kernel splits K.
+bool check_gemm_call(const attn_device_desc& desc, int M, int N, int K, int b_nk) {
+    GemmPlan p;
+    for (const bool may_split : {true, false}) {
+        CHECK(plan_gemm_call(desc, M, N, K, b_nk, may_split, &p), "no plan for %dx%dx%d split %d",
+              M, N, K, (int)may_split);
+        CHECK(p.b_nk == b_nk, "b_nk %d", p.b_nk);
+        if (!check_gemm(desc, p, M, N, K)) return false;
+        CHECK(may_split || p.k_splits == 1, "%dx%dx%d without a workspace has %d K splits", M, N, K,
+              p.k_splits);
+        CHECK(may_split || gemm_workspace_bytes(p, M, N) == 0, "workspace %lld",
+              gemm_workspace_bytes(p, M, N));
     }
     return true;
 }
@@ -246,7 +285,8 @@ int main(int argc, char** argv) {
         check_format(g, format_gemm_plan);
         ++plans;
         if (!check_gemm_call(desc, M, N, K, (int)(next() & 1))) break;
-        plans += 2;
+        if (!check_prefill_call(desc, B, Hkv * group, group, Sq, Skv, d, causal)) break;
+        plans += 4;
     }
     // shapes whose unsplit plan once fell back to a kernel that splits K itself
     const int split_shapes[][4] = {{195, 4072, 9216, 0}, {1053, 4288, 3232, 1},

@@ -9,6 +9,7 @@ within 2^-8 = 3.9e-3 of exact, plus fp32 accumulation of the scores).
 """
 from __future__ import annotations
 
+import ctypes
 import math
 
 import numpy as np
@@ -513,3 +514,51 @@ def test_fwd_causal_chunk_in_a_graph(pa):
         graph.replay()
         torch.cuda.synchronize()
         compare(o, ref, f"replay after an eager call of {rows} rows")
+
+
+def call_plan(pa, B, Hq, Hkv, Sq, Skv, d, causal):
+    """The plan that a call on the current stream would run now."""
+    buf = ctypes.create_string_buffer(512)
+    pa.lib.attn_set_stream(torch.cuda.current_stream().cuda_stream)
+    rc = pa.lib.attn__fwd_call_plan(B, Hq, Hkv, Sq, Skv, d, int(causal), buf, 512)
+    assert rc > 0, pa.last_error()
+    return pa.parse_plan(buf.value.decode())
+
+
+# B, Hq, Hkv, Sq, Skv, causal: each splits its keys in an eager call -- few heads,
+# folded heads of a short chunk, a longer chunk, the causal triangle
+GRAPH_SHAPES = [(1, 2, 2, 700, 4096, False), (1, 8, 1, 16, 8000, False),
+                (1, 4, 1, 64, 4096, True), (1, 2, 2, 2048, 2048, True)]
+
+
+@pytest.mark.parametrize("shape", GRAPH_SHAPES, ids=lambda s: "x".join(map(str, s[:5])))
+def test_fwd_in_a_graph_uses_no_workspace(pa, shape):
+    # the invariant is checked on the plan: a replay that used a released workspace
+    # could still give the right result
+    B, Hq, Hkv, Sq, Skv, causal = shape
+    d = 128
+    q, k, v = _qkv(B, Hq, Hkv, Sq, Skv, d, 2300 + Sq)
+    qd, kd, vd = q.to(DEV), k.to(DEV), v.to(DEV)
+    o = torch.empty((B, Hq, Sq, d), dtype=torch.float32, device=DEV)
+    ref = oracle.attn_gqa(q, k, v, B, Hq, Hkv, Sq, Skv, d, float(np.float32(1 / math.sqrt(d))),
+                          causal)[0]
+    args = (B, Hq, Hkv, Sq, Skv, d, causal)
+    announce(f"attn_fwd {args} captured")
+    side = torch.cuda.Stream()
+    with torch.cuda.stream(side):
+        assert call_plan(pa, *args)["KV_SPLITS"] > 1
+        pa.attn_fwd(qd, kd, vd, o=o, causal=causal)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=side):
+        assert call_plan(pa, *args)["KV_SPLITS"] == 1
+        pa.attn_fwd(qd, kd, vd, o=o, causal=causal)
+    for heads in (2, 4):
+        o.fill_(float("nan"))
+        with torch.cuda.stream(side):  # grows the stream's workspace
+            big = torch.zeros((1, heads, 4096, d), dtype=torch.bfloat16, device=DEV)
+            pa.attn_fwd(big, big, big)
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        compare(o, ref, f"replay {args} after an eager call of {heads} heads")
