@@ -122,6 +122,11 @@ int attn_fwd_ex(const void* q, const void* k, const void* v, void* o, float* lse
  * the moment a call takes the workspace until its kernels are enqueued, so
  * a growth on one thread cannot release a buffer another thread's call is
  * about to use.  No call synchronises.
+ * Under stream capture the call takes the workspace of the capturing stream;
+ * a buffer that a graph was given is never released (growth leaves it to the
+ * graph), and growth under capture allocates outside the graph.  Replays have
+ * to be ordered with the other calls that use that stream's workspace;
+ * attn_decode_ex with a caller's workspace has no such tie.
  */
 int attn_decode(const void* q, const void* k, const void* v, float* o, int B, int H, int Skv,
                 int d, int n_splits);

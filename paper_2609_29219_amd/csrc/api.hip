@@ -133,19 +133,26 @@ bool aligned16(const void* p) { return ((uintptr_t)p & 15u) == 0; }
 // kernels), so growth never waits for the device.  (hipFree synchronises
 // the whole device, so it is never called on this path.)  The map's own
 // lock guards only the map and is never held across an allocation.
+//
+// A graph keeps the pointers of its kernels.  A buffer that a captured call was
+// given is therefore never released: growth leaves it to the graph and takes
+// a fresh one (each is at least twice the one before, so what is left is less than
+// the buffer in use).  Growth while a call is captured allocates outside the graph,
+// whose own allocations live only while it runs, and releases nothing into it.
 class WorkspaceMap {
 public:
     // Stream-ordered allocation and release: HIP's, or a host-only double
     // in the self-test.  Both return 0 or an ATTN_E* code.
     struct Ops {
-        int (*alloc)(void* ctx, void* stream, size_t bytes, void** out);
+        int (*alloc)(void* ctx, void* stream, size_t bytes, bool captured, void** out);
         int (*release)(void* ctx, void* stream, void* ptr);
         void* ctx;
     };
     // On success *lk holds the stream's entry (keep it until the kernels
     // that use *out are enqueued) and *out is its buffer of at least bytes.
-    int acquire(void* stream, size_t bytes, const Ops& ops, std::unique_lock<std::mutex>* lk,
-                void** out) {
+    // captured: those kernels go into a graph.
+    int acquire(void* stream, size_t bytes, bool captured, const Ops& ops,
+                std::unique_lock<std::mutex>* lk, void** out) {
         Entry* e = nullptr;
         {
             std::lock_guard<std::mutex> g(mu_);
@@ -158,18 +165,21 @@ public:
             size_t want = 4096;
             while (want < bytes) want *= 2;
             void* fresh = nullptr;
-            const int rc = ops.alloc(ops.ctx, stream, want, &fresh);
+            const int rc = ops.alloc(ops.ctx, stream, want, captured, &fresh);
             if (rc) return rc;
             void* old = e->ptr;
+            const bool keep_old = e->in_graph || captured;
             e->ptr = fresh;
             e->bytes = want;
+            e->in_graph = false;
             // work already enqueued on the stream still reads the old buffer:
             // released behind it, in stream order
-            if (old) {
+            if (old && !keep_old) {
                 const int rr = ops.release(ops.ctx, stream, old);
                 if (rr) return rr;
             }
         }
+        if (captured) e->in_graph = true;
         *out = e->ptr;
         *lk = std::move(l);
         return ATTN_OK;
@@ -180,13 +190,24 @@ private:
         std::mutex mu;
         void* ptr = nullptr;
         size_t bytes = 0;
+        bool in_graph = false;  // a captured call was given ptr
     };
     std::mutex mu_;
     std::map<void*, std::unique_ptr<Entry>> entries_;
 };
 
-int hip_ws_alloc(void*, void* stream, size_t bytes, void** out) {
-    const hipError_t e = hipMallocAsync(out, bytes, static_cast<hipStream_t>(stream));
+int hip_ws_alloc(void*, void* stream, size_t bytes, bool captured, void** out) {
+    hipError_t e;
+    if (captured) {  // not through the stream: that would be an allocation of the graph
+        hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+        e = hipThreadExchangeStreamCaptureMode(&mode);
+        if (e == hipSuccess) {
+            e = hipMalloc(out, bytes);
+            (void)hipThreadExchangeStreamCaptureMode(&mode);
+        }
+    } else {
+        e = hipMallocAsync(out, bytes, static_cast<hipStream_t>(stream));
+    }
     if (e != hipSuccess || !*out) {
         (void)hipGetLastError();
         return fail(ATTN_ENOMEM, "workspace of %zu bytes: %s", bytes, hipGetErrorString(e));
@@ -288,12 +309,22 @@ bool forced_fwd(int* bn, int* waves, int* pipe, int* splits, int* fold, int* for
     return n >= 3;
 }
 
+// Whether work enqueued on the stream now goes into a graph.
+bool capturing(hipStream_t stream) {
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(stream, &status) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    return status != hipStreamCaptureStatusNone;
+}
+
 // The per-stream workspace (decode partials, split-key prefill partials) of
 // at least bytes bytes; *lk holds the stream's entry until the caller has
 // enqueued the kernels that use it.
 int stream_workspace(DeviceState* st, size_t bytes, std::unique_lock<std::mutex>* lk,
                      void** out) {
-    return st->ws.acquire(t_stream, bytes, kHipWorkspaceOps, lk, out);
+    return st->ws.acquire(t_stream, bytes, capturing(t_stream), kHipWorkspaceOps, lk, out);
 }
 
 // Optional fixed GEMM tile for the block-size ablation only:
@@ -463,7 +494,7 @@ int attn__workspace_selftest(int threads, int rounds, int hold_lock) {
         std::vector<std::pair<int, uintptr_t>> log;  // (0 job | 1 release, buffer)
         std::atomic<uintptr_t> next{4096};
     } sim;
-    auto alloc = [](void* ctx, void*, size_t bytes, void** out) -> int {
+    auto alloc = [](void* ctx, void*, size_t bytes, bool, void** out) -> int {
         Sim* s = static_cast<Sim*>(ctx);
         *out = reinterpret_cast<void*>(s->next.fetch_add((bytes + 4095) / 4096 * 4096));
         return ATTN_OK;
@@ -484,7 +515,7 @@ int attn__workspace_selftest(int threads, int rounds, int hold_lock) {
                 for (int i = 0; i < 12; ++i) {
                     std::unique_lock<std::mutex> lk;
                     void* buf = nullptr;
-                    if (map.acquire(stream, ((size_t)2048 << i) + (size_t)t, ops, &lk, &buf))
+                    if (map.acquire(stream, ((size_t)2048 << i) + (size_t)t, false, ops, &lk, &buf))
                         continue;
                     if (!hold_lock) {
                         lk.unlock();
@@ -503,6 +534,55 @@ int attn__workspace_selftest(int threads, int rounds, int hold_lock) {
         else if (released.count(rec.second)) ++bad;
     }
     return bad;
+}
+
+// Not part of the ABI: a host-only check of the workspace under capture, with no
+// device.  steps calls of growing and repeated sizes on one simulated stream, call i
+// captured where bit i % 32 of captured_mask is set.  Returns how often a buffer that a
+// captured call was given is released, anything is released by a captured call, a
+// captured call's allocation goes through the stream, or a buffer that an eager call
+// replaces and no graph holds is not released; or -1 if a captured call ever gets
+// less than it asked for.
+int attn__workspace_graph_selftest(unsigned captured_mask, int steps) {
+    struct Sim {
+        uintptr_t next = 4096;
+        bool captured = false;  // the call in progress
+        std::map<uintptr_t, size_t> size;
+        std::set<uintptr_t> in_graph, released;
+        int bad = 0;
+    } sim;
+    auto alloc = [](void* ctx, void*, size_t bytes, bool captured, void** out) -> int {
+        Sim* s = static_cast<Sim*>(ctx);
+        if (captured != s->captured) ++s->bad;
+        *out = reinterpret_cast<void*>(s->next);
+        s->size[s->next] = bytes;
+        s->next += (bytes + 4095) / 4096 * 4096;
+        return ATTN_OK;
+    };
+    auto release = [](void* ctx, void*, void* ptr) -> int {
+        Sim* s = static_cast<Sim*>(ctx);
+        if (s->captured || s->in_graph.count(reinterpret_cast<uintptr_t>(ptr))) ++s->bad;
+        s->released.insert(reinterpret_cast<uintptr_t>(ptr));
+        return ATTN_OK;
+    };
+    const WorkspaceMap::Ops ops = {alloc, release, &sim};
+    WorkspaceMap map;
+    uintptr_t last = 0;
+    for (int i = 0; i < steps; ++i) {
+        std::unique_lock<std::mutex> lk;
+        void* buf = nullptr;
+        const size_t bytes = (size_t)4000 << (i / 2 % 40);  // every second call grows
+        sim.captured = (captured_mask >> (i % 32)) & 1u;
+        if (map.acquire(&sim, bytes, sim.captured, ops, &lk, &buf)) return -1;
+        const uintptr_t p = reinterpret_cast<uintptr_t>(buf);
+        if (sim.size[p] < bytes || sim.released.count(p)) return -1;
+        if (last && last != p && !sim.captured && !sim.in_graph.count(last) &&
+            !sim.released.count(last))
+            ++sim.bad;
+        if (sim.captured) sim.in_graph.insert(p);
+        last = p;
+    }
+    return sim.bad;
 }
 
 int attn_get_plan(int kind, int B, int H, int Sq, int Skv, int d, int causal, int n_splits,
@@ -531,16 +611,6 @@ static int prefill_plan(DeviceState* st, int B, int Hq, int Sq, int Skv, int d, 
     std::lock_guard<std::mutex> lk(g_mu);
     g_fwd_cache[key] = *plan;
     return ATTN_OK;
-}
-
-// Whether work enqueued on the stream now goes into a graph.
-static bool capturing(hipStream_t stream) {
-    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(stream, &status) != hipSuccess) {
-        (void)hipGetLastError();
-        return false;
-    }
-    return status != hipStreamCaptureStatusNone;
 }
 
 // Plan of a prefill call enqueued now on the thread's stream.  A graph keeps its

@@ -196,3 +196,15 @@ def test_workspace_growth_cannot_release_a_buffer_before_its_users_are_enqueued(
     for _ in range(5):
         assert f(8, 200, 1) == 0
     assert any(f(8, 200, 0) > 0 for _ in range(20))
+
+
+def test_workspace_of_a_captured_call_is_never_released():
+    # Host-only: a graph keeps the address that a captured call was given, so
+    # growth must leave that buffer alone, and growth under capture must neither
+    # allocate from nor release into the graph.  Without captures every replaced
+    # buffer is released.
+    f = pa.lib.attn__workspace_graph_selftest
+    f.argtypes = [ctypes.c_uint, ctypes.c_int]
+    f.restype = ctypes.c_int
+    for mask in (0, 1, 2, 4, 0b1001, 0x55555555, 0xAAAAAAAA, 0xFFFFFFFF, 0x0F0F3C21):
+        assert f(mask, 32) == 0, hex(mask)

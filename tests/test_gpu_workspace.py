@@ -76,3 +76,43 @@ def test_workspace_growth_does_not_wait_for_queued_work(pa):
         stream.synchronize()
     for n, o in zip(splits, outs):
         compare(o, ref, f"decode n_splits={n} around workspace growth")
+
+
+def test_captured_decode_keeps_its_workspace(pa):
+    # captured on a stream that has no workspace yet (allocated under capture), then
+    # replayed between eager calls that grow the workspace, decode and causal
+    # prefill among them; every replay is checked on an output of NaN
+    B, H, Skv, d = 2, 8, 3000, 128
+    q = random_bf16((B, H, d), 1600)
+    k, v = random_bf16((B, H, Skv, d), 1601), random_bf16((B, H, Skv, d), 1602)
+    ref = _decode_ref(q, k, v)
+    qd, kd, vd = q.to(DEV), k.to(DEV), v.to(DEV)
+    o = torch.empty((B, H, d), dtype=torch.float32, device=DEV)
+    pa.decode_workspace_bytes(B, H, H, Skv, d, 16)  # plans
+    stream = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    announce("attn_decode captured on a stream without a workspace")
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=stream):
+        pa.attn_decode(qd, kd, vd, o=o, n_splits=16)
+
+    def check(what):
+        o.fill_(float("nan"))
+        torch.cuda.synchronize()
+        announce(f"replay {what}")
+        graph.replay()
+        torch.cuda.synchronize()
+        compare(o, ref, f"captured decode, replay {what}")
+
+    check("first")
+    for n in (32, 96):
+        with torch.cuda.stream(stream):
+            eager = pa.attn_decode(qd, kd, vd, n_splits=n)
+        torch.cuda.synchronize()
+        compare(eager, ref, f"eager decode n_splits={n}")
+        check(f"after an eager decode of {n} splits")
+    with torch.cuda.stream(stream):
+        x = torch.zeros((1, 2, 4096, d), dtype=torch.bfloat16, device=DEV)
+        pa.attn_fwd(x, x, x, causal=True)
+    torch.cuda.synchronize()
+    check("after an eager causal prefill")
