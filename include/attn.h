@@ -241,8 +241,9 @@ int attn_measure_device(attn_device_desc* out);
 
 /*
  * Plan query: writes a one-line, human-readable plan -- the named tile
- * symbols (BLOCK_M, BLOCK_N, WAVES, PIPE, KV_SPLITS, KV_CHUNK for
- * ATTN_KIND_FWD; N_SPLITS, CHUNK, ... for ATTN_KIND_DECODE), the grid size,
+ * symbols (BLOCK_M, BLOCK_N, WAVES, PIPE, KV_SPLITS, KV_CHUNK, FOLD, CHUNK for
+ * ATTN_KIND_FWD, where CHUNK is 0 for the plain form, 1 for a causal chunk or single
+ * q-tiles and 2 for a causal triangle with key splits; N_SPLITS, CHUNK, ... for ATTN_KIND_DECODE), the grid size,
  * the modelled time in us and the binding resource -- for the given problem
  * into buf (NUL-terminated, truncated to buflen).  This is the paper's
  * reporting of solved schedule symbols under the names the program gave
@@ -250,12 +251,20 @@ int attn_measure_device(attn_device_desc* out);
  * chosen values can be reported back by name), with the latency the model
  * predicts (Eq. heg-optimization).  Returns the full length of the line (excluding the
  * NUL) or a negative ATTN_E* code.  Sq is ignored for decode.  desc may be
- * NULL (use attn_query_device()).  Host-only; launches nothing.
+ * NULL (use attn_query_device()).  Host-only; launches nothing.  The plan is that of
+ * an eager call; a call under stream capture, or without memory for its workspace,
+ * runs without key splits.
  */
 int attn_get_plan(int kind, int B, int H, int Sq, int Skv, int d, int causal, int n_splits,
                   char* buf, int buflen);
 int attn_get_plan_for(const attn_device_desc* desc, int kind, int B, int H, int Sq, int Skv,
                       int d, int causal, int n_splits, char* buf, int buflen);
+/* The same for Hq query heads over Hkv key/value heads (which divide them; EINVAL
+ * otherwise): the plan of attn_fwd_ex or attn_decode_ex.  A prefill may fold the
+ * query heads of a key/value head into its rows (FOLD > 1), which the two queries
+ * above, for equal head counts, never report. */
+int attn_get_plan_ex(const attn_device_desc* desc, int kind, int B, int Hq, int Hkv, int Sq,
+                     int Skv, int d, int causal, int n_splits, char* buf, int buflen);
 
 /*
  * Matrix multiplication C = A B, the paper's GEMM workload (Evaluation,
@@ -281,8 +290,9 @@ int attn_get_plan_for(const attn_device_desc* desc, int kind, int B, int H, int 
  */
 int attn_gemm(const void* a, const void* b, void* c, int M, int N, int K, int flags);
 
-/* GEMM plan query (host only): the named tile symbols BLOCK_M, BLOCK_N,
- * BLOCK_K, WAVES_M, WAVES_N, PIPE, K_SPLITS (with the k values per split),
+/* GEMM plan query (host only), the plan that an eager attn_gemm runs: the named tile
+ * symbols BLOCK_M, BLOCK_N, BLOCK_K, WAVES_M, WAVES_N, PIPE, DEEP (wave groups of the
+ * deep-pipeline kernel, 0 for the others), K_SPLITS (with the k values per split),
  * the grid, the modelled time in us and the
  * binding resource, as one NUL-terminated line in buf (truncated to buflen).
  * desc NULL: this device's description and its compiled kernels' real

@@ -33,7 +33,7 @@ ATTN_GEMM_B_NK = 2
 EXPORTED = ("attn_fwd", "attn_decode", "attn_fwd_ex", "attn_decode_ex",
             "attn_decode_workspace_bytes", "attn_set_stream", "attn_get_stream",
             "attn_last_error", "attn_query_device", "attn_measure_device", "attn_get_plan",
-            "attn_get_plan_for", "attn_gemm", "attn_gemm_plan", "attn_decode_noalloc")
+            "attn_get_plan_for", "attn_get_plan_ex", "attn_gemm", "attn_gemm_plan", "attn_decode_noalloc")
 NOALLOC_SCRATCH_BYTES = 16 << 20  # ATTN_NOALLOC_SCRATCH_BYTES
 
 
@@ -106,8 +106,10 @@ def _load() -> ctypes.CDLL:
     lib.attn_get_plan.argtypes = [ci, ci, ci, ci, ci, ci, ci, ci, ctypes.c_char_p, ci]
     lib.attn_get_plan_for.argtypes = [ctypes.POINTER(DeviceDesc), ci, ci, ci, ci, ci, ci, ci,
                                       ci, ctypes.c_char_p, ci]
+    lib.attn_get_plan_ex.argtypes = [ctypes.POINTER(DeviceDesc), ci, ci, ci, ci, ci, ci, ci, ci,
+                                     ci, ctypes.c_char_p, ci]
     lib.attn__fwd_candidates.argtypes = [ctypes.POINTER(DeviceDesc), ci, ci, ci, ci, ci, ci, ci,
-                                         ctypes.c_char_p, ci]
+                                         ci, ctypes.c_char_p, ci]
     lib.attn_gemm.argtypes = [vp, vp, vp, ci, ci, ci, ci]
     lib.attn_gemm_plan.argtypes = [ctypes.POINTER(DeviceDesc), ci, ci, ci, ci, ctypes.c_char_p,
                                    ci]
@@ -117,6 +119,7 @@ def _load() -> ctypes.CDLL:
                lib.attn_decode_noalloc,
                lib.attn_set_stream, lib.attn_query_device,
                lib.attn_measure_device, lib.attn_get_plan, lib.attn_get_plan_for,
+               lib.attn_get_plan_ex,
                lib.attn__fwd_candidates, lib.attn_gemm, lib.attn_gemm_plan,
                lib.attn__gemm_candidates):
         fn.restype = ci
@@ -288,15 +291,17 @@ def gemm_plan(M: int, N: int, K: int, b_nk: bool = False, desc: DeviceDesc | Non
 
 
 def gemm_candidates(M: int, N: int, K: int, b_nk: bool = False, desc: DeviceDesc | None = None,
-                    device_footprint: bool = False, analytic_only: bool = False) -> list[dict]:
+                    device_footprint: bool = False, analytic_only: bool = False,
+                    deep: bool = False) -> list[dict]:
     """Every feasible GEMM candidate with its modelled time (not ABI; for the
-    block-size ablation).  analytic_only: without the measured per-variant
-    costs."""
-    buf = ctypes.create_string_buffer(1 << 16)
+    block-size ablation) of the generic and the hand-scheduled kernel, and with
+    deep of the deep-pipeline kernel.  analytic_only: without the measured
+    per-variant costs."""
+    buf = ctypes.create_string_buffer(1 << 17)
     ptr = ctypes.byref(desc) if desc is not None else None
-    flags = int(bool(device_footprint)) | (2 if analytic_only else 0)
+    flags = int(bool(device_footprint)) | (2 if analytic_only else 0) | (4 if deep else 0)
     rc = lib.attn__gemm_candidates(ptr, M, N, K, ATTN_GEMM_B_NK if b_nk else 0, flags, buf,
-                                   1 << 16)
+                                   1 << 17)
     if rc < 0:
         raise AttnError(rc, last_error())
     return [parse_plan(l) for l in buf.value.decode().splitlines() if l.strip()]
@@ -316,13 +321,13 @@ def measure_device() -> dict:
 
 
 def get_plan(kind: int, B: int, H: int, Sq: int, Skv: int, d: int, causal: bool = False,
-             n_splits: int = 0, desc: DeviceDesc | None = None) -> str:
+             n_splits: int = 0, desc: DeviceDesc | None = None, Hkv: int | None = None) -> str:
+    """The plan line of a call with H query heads and Hkv (default H) key/value
+    heads."""
     buf = ctypes.create_string_buffer(512)
-    if desc is None:
-        rc = lib.attn_get_plan(kind, B, H, Sq, Skv, d, int(bool(causal)), n_splits, buf, 512)
-    else:
-        rc = lib.attn_get_plan_for(ctypes.byref(desc), kind, B, H, Sq, Skv, d, int(bool(causal)),
-                                   n_splits, buf, 512)
+    ptr = ctypes.byref(desc) if desc is not None else None
+    rc = lib.attn_get_plan_ex(ptr, kind, B, H, H if Hkv is None else Hkv, Sq, Skv, d,
+                              int(bool(causal)), n_splits, buf, 512)
     if rc < 0:
         raise AttnError(rc, last_error())
     return buf.value.decode()
@@ -330,16 +335,18 @@ def get_plan(kind: int, B: int, H: int, Sq: int, Skv: int, d: int, causal: bool 
 
 def fwd_candidates(B: int, H: int, Sq: int, Skv: int, d: int, causal: bool = False,
                    desc: DeviceDesc | None = None, device_footprint: bool = False,
-                   analytic_only: bool = False) -> list[dict]:
+                   analytic_only: bool = False, group: int = 0) -> list[dict]:
     """Every feasible prefill candidate with its modelled time (not ABI; for
     the block-size ablation).  desc None: this device's description and the
     compiled kernels' real register/occupancy footprint; with a desc, the
     footprint is estimated unless device_footprint is set.  analytic_only:
-    without the measured per-variant tile costs."""
-    buf = ctypes.create_string_buffer(1 << 18)
+    without the measured per-variant tile costs.  group 0: the plain form only;
+    else every form of a call with that many query heads to a key/value head."""
+    buf = ctypes.create_string_buffer(1 << 20)
     ptr = ctypes.byref(desc) if desc is not None else None
     flags = int(bool(device_footprint)) | (2 if analytic_only else 0)
-    rc = lib.attn__fwd_candidates(ptr, B, H, Sq, Skv, d, int(bool(causal)), flags, buf, 1 << 18)
+    rc = lib.attn__fwd_candidates(ptr, B, H, Sq, Skv, d, int(bool(causal)), group, flags, buf,
+                                  1 << 20)
     if rc < 0:
         raise AttnError(rc, last_error())
     return [parse_plan(l) for l in buf.value.decode().splitlines() if l.strip()]

@@ -396,8 +396,8 @@ int attn_measure_device(attn_device_desc* out) {
     return ATTN_OK;
 }
 
-int attn_get_plan_for(const attn_device_desc* desc, int kind, int B, int H, int Sq, int Skv,
-                      int d, int causal, int n_splits, char* buf, int buflen) {
+int attn_get_plan_ex(const attn_device_desc* desc, int kind, int B, int Hq, int Hkv, int Sq,
+                     int Skv, int d, int causal, int n_splits, char* buf, int buflen) {
     attn_device_desc local;
     FwdResFn res = nullptr;
     if (!desc) {
@@ -408,8 +408,10 @@ int attn_get_plan_for(const attn_device_desc* desc, int kind, int B, int H, int 
         desc = &local;
     }
     if (buflen < 0 || (buflen > 0 && !buf)) return fail(ATTN_EINVAL, "bad output buffer");
-    if (B <= 0 || H <= 0 || Skv <= 0 || d <= 0 || (kind == ATTN_KIND_FWD && Sq <= 0))
+    if (B <= 0 || Hq <= 0 || Skv <= 0 || d <= 0 || (kind == ATTN_KIND_FWD && Sq <= 0))
         return fail(ATTN_EINVAL, "dimensions must be positive");
+    if (Hkv <= 0 || Hq % Hkv != 0)
+        return fail(ATTN_EINVAL, "Hkv (%d) must be positive and divide Hq (%d)", Hkv, Hq);
     if (d != 64 && d != 128) return fail(ATTN_EUNSUPPORTED, "head dim %d not in {64, 128}", d);
     if (desc->num_cus <= 0 || desc->num_xcds <= 0 || desc->clock_ghz <= 0.0 ||
         desc->lds_bytes_per_cu <= 0 || desc->hbm_bytes_per_s <= 0.0 ||
@@ -423,27 +425,34 @@ int attn_get_plan_for(const attn_device_desc* desc, int kind, int B, int H, int 
     if (kind == ATTN_KIND_FWD) {
         if (causal && Sq > Skv) return fail(ATTN_EUNSUPPORTED, "causal needs Sq <= Skv");
         FwdPlan p;
-        if (!plan_prefill(*desc, B, H, Sq, Skv, d, causal ? 1 : 0, 1, true, &p, res))
+        if (!plan_prefill(*desc, B, Hq, Sq, Skv, d, causal ? 1 : 0, Hq / Hkv, true, &p, res))
             return fail(ATTN_EUNSUPPORTED, "no feasible prefill plan");
         return format_fwd_plan(p, buf, buflen);
     }
     if (kind == ATTN_KIND_DECODE) {
         DecodePlan p;
-        if (!plan_decode(*desc, B, H, H, Skv, d, n_splits, &p))
+        if (!plan_decode(*desc, B, Hq, Hkv, Skv, d, n_splits, &p))
             return fail(ATTN_EUNSUPPORTED, "no feasible decode plan");
         return format_decode_plan(p, buf, buflen);
     }
     return fail(ATTN_EINVAL, "unknown plan kind %d", kind);
 }
 
+int attn_get_plan_for(const attn_device_desc* desc, int kind, int B, int H, int Sq, int Skv,
+                      int d, int causal, int n_splits, char* buf, int buflen) {
+    return attn_get_plan_ex(desc, kind, B, H, H, Sq, Skv, d, causal, n_splits, buf, buflen);
+}
+
 // Not part of the ABI: every feasible prefill candidate with its modelled
 // time, one plan line each (newline-separated), for the block-size ablation
 // that validates the model (plan_ablation.py).  Returns the full length.
+// group 0: the plain form (q-tile pairs under a mask, key splits without one); else
+// every form that a call with group query heads to a key/value head may take.
 // device_footprint != 0: with a gfx950 device present, use the compiled
 // kernels' real register and occupancy footprint (always so for desc NULL);
 // otherwise the estimate, as attn_get_plan_for does for an explicit desc.
 int attn__fwd_candidates(const attn_device_desc* desc, int B, int H, int Sq, int Skv, int d,
-                         int causal, int device_footprint, char* buf, int buflen) {
+                         int causal, int group, int device_footprint, char* buf, int buflen) {
     attn_device_desc local;
     FwdResFn res = nullptr;
     const bool have = attn_query_device(&local) == ATTN_OK && strcmp(local.arch, "gfx950") == 0;
@@ -456,12 +465,13 @@ int attn__fwd_candidates(const attn_device_desc* desc, int B, int H, int Sq, int
     } scales(!(device_footprint & 2));
     if (!desc) desc = &local;
     if (buflen < 0 || (buflen > 0 && !buf)) return fail(ATTN_EINVAL, "bad output buffer");
-    if (B <= 0 || H <= 0 || Sq <= 0 || Skv <= 0) return fail(ATTN_EINVAL, "bad dimensions");
+    if (B <= 0 || H <= 0 || Sq <= 0 || Skv <= 0 || group < 0 || (group > 0 && H % group != 0))
+        return fail(ATTN_EINVAL, "bad dimensions");
     if (d != 64 && d != 128) return fail(ATTN_EUNSUPPORTED, "head dim %d not in {64, 128}", d);
-    constexpr int kCap = 512;
+    constexpr int kCap = 2048;
     std::vector<FwdPlan> plans(kCap);
     const int n = std::min(kCap, plan_fwd_all(*desc, B, H, Sq, Skv, d, causal ? 1 : 0,
-                                              plans.data(), kCap, res));
+                                              plans.data(), kCap, res, group));
     int len = 0;
     for (int i = 0; i < n; ++i) {
         char line[512];
@@ -825,13 +835,15 @@ int attn_gemm_plan(const attn_device_desc* desc, int M, int N, int K, int flags,
     int rc = validate_gemm_dims(M, N, K, flags);
     if (rc) return rc;
     GemmPlan p;
-    if (!plan_gemm(*desc, M, N, K, (flags & ATTN_GEMM_B_NK) ? 1 : 0, &p, res))
+    if (!plan_gemm_call(*desc, M, N, K, (flags & ATTN_GEMM_B_NK) ? 1 : 0, true, &p, res))
         return fail(ATTN_EUNSUPPORTED, "no feasible GEMM plan");
     return format_gemm_plan(p, buf, buflen);
 }
 
 // Not part of the ABI: every feasible GEMM candidate with its modelled time,
 // one plan line each (for the block-size ablation).  Returns the full length.
+// device_footprint as for the prefill candidates; bit 2: the deep-pipeline
+// kernel's candidates too.
 int attn__gemm_candidates(const attn_device_desc* desc, int M, int N, int K, int flags,
                           int device_footprint, char* buf, int buflen) {
     attn_device_desc local;
@@ -848,9 +860,11 @@ int attn__gemm_candidates(const attn_device_desc* desc, int M, int N, int K, int
     if (buflen < 0 || (buflen > 0 && !buf)) return fail(ATTN_EINVAL, "bad output buffer");
     int rc = validate_gemm_dims(M, N, K, flags);
     if (rc) return rc;
-    GemmPlan plans[64];
-    const int n = std::min(64, plan_gemm_all(*desc, M, N, K, (flags & ATTN_GEMM_B_NK) ? 1 : 0,
-                                             plans, 64, res));
+    constexpr int kCap = 256;
+    std::vector<GemmPlan> plans(kCap);
+    const int n = std::min(kCap, plan_gemm_all(*desc, M, N, K, (flags & ATTN_GEMM_B_NK) ? 1 : 0,
+                                               plans.data(), kCap, res,
+                                               (device_footprint & 4) != 0));
     int len = 0;
     for (int i = 0; i < n; ++i) {
         char line[512];

@@ -200,9 +200,10 @@ inline long long fwd_workspace_bytes(const FwdPlan& p, long long rows) {
     return p.kv_splits > 1 ? rows * p.kv_splits * (p.d + 2) * 4LL : 0;
 }
 // Every feasible candidate (in the planner's search order), up to cap of them
-// into out; returns how many there are.
+// into out; returns how many there are.  group 0: plan_fwd's candidates; else
+// plan_prefill's.
 int plan_fwd_all(const attn_device_desc& desc, int B, int H, int Sq, int Skv, int d, int causal,
-                 FwdPlan* out, int cap, FwdResFn res = nullptr);
+                 FwdPlan* out, int cap, FwdResFn res = nullptr, int group = 0);
 bool fwd_resources(int d, int bn, int waves, int pipe, int causal, KernelRes* out);
 // Per-thread switch of the measured per-variant tile costs, prefill and GEMM
 // (on by default).
@@ -218,8 +219,10 @@ bool plan_gemm_fixed(const attn_device_desc& desc, int M, int N, int K, int b_nk
                      int k_splits = 1);
 bool plan_gemm(const attn_device_desc& desc, int M, int N, int K, int b_nk, GemmPlan* out,
                GemmResFn res = nullptr);
+// Candidates of plan_gemm (the generic and the hand-scheduled kernel), and with
+// deep the deep-pipeline kernel's.
 int plan_gemm_all(const attn_device_desc& desc, int M, int N, int K, int b_nk, GemmPlan* out,
-                  int cap, GemmResFn res = nullptr);
+                  int cap, GemmResFn res = nullptr, bool deep = false);
 // The plan of a call: the fastest of all kernels'.  may_split false: no kernel splits
 // K, so that the call needs no workspace (such a plan exists whenever one with splits
 // does).

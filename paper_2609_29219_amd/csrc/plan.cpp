@@ -414,12 +414,14 @@ bool plan_prefill(const attn_device_desc& desc, int B, int H, int Sq, int Skv, i
 }
 
 int plan_fwd_all(const attn_device_desc& desc, int B, int H, int Sq, int Skv, int d, int causal,
-                 FwdPlan* out, int cap, FwdResFn res) {
+                 FwdPlan* out, int cap, FwdResFn res, int group) {
     int n = 0;
-    fwd_for_each(desc, B, H, Sq, Skv, d, causal, res, false, 1, true, [&](const FwdPlan& p) {
+    auto add = [&](const FwdPlan& p) {
         if (n < cap) out[n] = p;
         ++n;
-    });
+    };
+    fwd_for_each(desc, B, H, Sq, Skv, d, causal, res, group > 0, 1, true, add);
+    if (group > 1) fwd_for_each(desc, B, H, Sq, Skv, d, causal, res, true, group, true, add);
     return n;
 }
 
@@ -768,18 +770,27 @@ bool plan_gemm_call(const attn_device_desc& desc, int M, int N, int K, int b_nk,
 }
 
 int plan_gemm_all(const attn_device_desc& desc, int M, int N, int K, int b_nk, GemmPlan* out,
-                  int cap, GemmResFn res) {
+                  int cap, GemmResFn res, bool deep) {
     int n = 0;
+    auto add = [&](const GemmPlan& p) {
+        if (n < cap) out[n] = p;
+        ++n;
+    };
+    GemmPlan p;
     for (const GemmTile& t : kGemmTiles)
         for (int pipe = t.pipe_min; pipe <= t.pipe_max; ++pipe)
-            for (int splits : kGemmKSplits) {
-                GemmPlan p;
-                if (!plan_gemm_fixed(desc, M, N, K, b_nk, t.bm, t.bn, t.bk, t.wm, t.wn, pipe, &p,
-                                     res, splits))
-                    continue;
-                if (n < cap) out[n] = p;
-                ++n;
-            }
+            for (int splits : kGemmKSplits)
+                if (plan_gemm_fixed(desc, M, N, K, b_nk, t.bm, t.bn, t.bk, t.wm, t.wn, pipe, &p,
+                                    res, splits))
+                    add(p);
+    if (!deep) return n;
+    for (int ks : kGemmDeepKSplits) {
+#define ATTN_D(BM, BN, BK, WM, WN, KG, NSLOT)                                                   \
+    if (plan_gemm_deep_fixed(desc, M, N, K, b_nk, BM, BN, BK, WM, WN, KG, NSLOT, ks, &p, res))   \
+        add(p);
+        ATTN_DEEP_TILES(ATTN_D)
+#undef ATTN_D
+    }
     return n;
 }
 

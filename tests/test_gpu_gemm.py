@@ -417,3 +417,9 @@ def test_gemm_in_a_graph_uses_no_workspace(pa, shape):
         graph.replay()
         torch.cuda.synchronize()
         _check(c.cpu()[torch.from_numpy(rows)], want, absc, K, f"replay {shape} after {n} columns")
+
+
+@pytest.mark.parametrize("shape", GRAPH_SHAPES + [(8192, 8192, 8192, False), (300, 520, 1000, True)],
+                         ids=lambda s: f"{s[0]}x{s[1]}x{s[2]}")
+def test_gemm_plan_reports_the_plan_that_runs(pa, shape):
+    assert call_plan(pa, *shape) == pa.parse_plan(pa.gemm_plan(*shape))

@@ -476,6 +476,7 @@ def test_fwd_folded_heads_by_plan(pa, causal):
     # the planner's own choice where folding the group fills the q-tile
     B, Hq, Hkv, Sq, Skv, d = 2, 16, 2, 9, 3000, 128
     q, k, v = _qkv(B, Hq, Hkv, Sq, Skv, d, 1700)
+    assert call_plan(pa, B, Hq, Hkv, Sq, Skv, d, causal)["FOLD"] == Hq // Hkv
     announce(f"attn_fwd_ex folded heads causal={causal}")
     o, lse = pa.attn_fwd(q.to(DEV), k.to(DEV), v.to(DEV), scale=-0.1, causal=causal,
                          return_lse=True)
@@ -562,3 +563,11 @@ def test_fwd_in_a_graph_uses_no_workspace(pa, shape):
         graph.replay()
         torch.cuda.synchronize()
         compare(o, ref, f"replay {args} after an eager call of {heads} heads")
+
+
+@pytest.mark.parametrize("shape", GRAPH_SHAPES + [(2, 16, 2, 9, 3000, True), (4, 16, 16, 512, 512, True)],
+                         ids=lambda s: "x".join(map(str, s[:5])))
+def test_plan_query_reports_the_plan_that_runs(pa, shape):
+    B, Hq, Hkv, Sq, Skv, causal = shape
+    assert call_plan(pa, B, Hq, Hkv, Sq, Skv, 128, causal) == pa.parse_plan(
+        pa.get_plan(pa.KIND_FWD, B, Hq, Sq, Skv, 128, causal, Hkv=Hkv))

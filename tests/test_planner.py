@@ -254,6 +254,63 @@ def test_key_split_model_charges_the_combine():
             assert times[2] > times[1] - 1e-9, tile
 
 
+# ------------------------------------------------- forms of a prefill call
+def form(p):
+    if p["FOLD"] > 1:
+        return "folded"
+    return ("plain", "triangle" if p["KV_SPLITS"] > 1 and p["CHUNK"] == 2 else
+            "chunk" if p["KV_SPLITS"] > 1 else "singles")[p["CHUNK"] > 0]
+
+
+# B, Hq, Hkv, Sq, Skv, d, causal and the form that the planner takes
+FORMS = [((4, 16, 16, 2048, 2048, 128, True), "plain"),
+         ((1, 32, 32, 8192, 8192, 128, False), "plain"),
+         ((2, 16, 2, 9, 3000, 128, True), "folded"),
+         ((2, 16, 2, 9, 3000, 128, False), "folded"),
+         ((1, 16, 16, 512, 16384, 128, True), "chunk"),
+         ((3, 16, 16, 6394, 6394, 128, True), "singles"),
+         ((1, 8, 8, 2048, 2048, 128, True), "triangle")]
+
+
+@pytest.mark.parametrize("shape,want", FORMS, ids=[f"{f[1]}-{f[0][3]}x{f[0][4]}" for f in FORMS])
+def test_prefill_plan_of_a_call(shape, want):
+    """The plan query with both head counts gives the fastest modelled candidate
+    over every form of the call."""
+    B, Hq, Hkv, Sq, Skv, d, causal = shape
+    desc = spec()
+    p = pa.parse_plan(pa.get_plan(pa.KIND_FWD, B, Hq, Sq, Skv, d, causal, desc=desc, Hkv=Hkv))
+    assert form(p) == want
+    cands = pa.fwd_candidates(B, Hq, Sq, Skv, d, causal, desc=desc, group=Hq // Hkv)
+    assert p["modeled_us"] == pytest.approx(min(c["modeled_us"] for c in cands))
+    keys = [(c["BLOCK_N"], c["WAVES"], c["PIPE"], c["KV_SPLITS"], c["FOLD"], c["CHUNK"])
+            for c in cands]
+    assert len(keys) == len(set(keys))
+    for c in cands:
+        n, chunk, fold = c["KV_SPLITS"], c["KV_CHUNK"], c["FOLD"]
+        assert fold in (1, Hq // Hkv) and c["n_qtiles"] == -(-Sq * fold // c["BLOCK_M"])
+        if n > 1:
+            # no split empty, and under a mask the last one's first key is allowed to
+            # every row, or in the triangle to a row of the last q-tile
+            assert chunk % c["BLOCK_N"] == 0 and (n - 1) * chunk < Skv <= n * chunk
+            if causal:
+                first = (c["n_qtiles"] - 1) * c["BLOCK_M"] if c["CHUNK"] == 2 else 0
+                assert c["CHUNK"] and (n - 1) * chunk <= Skv - Sq + first
+            # the partials: four rounds of the compute units, the triangle's eight
+            rounds = 8 if c["CHUNK"] == 2 else 4
+            assert B * Hq * Sq * n * (d + 2) * 4 <= rounds * desc.num_cus * 256 * (d + 2) * 4
+
+
+def test_plan_query_checks_the_head_counts():
+    for hkv in (0, -1, 3):
+        with pytest.raises(pa.AttnError) as e:
+            pa.get_plan(pa.KIND_FWD, 1, 8, 64, 64, 64, desc=spec(), Hkv=hkv)
+        assert e.value.code == pa.ATTN_EINVAL
+    same = pa.get_plan(pa.KIND_DECODE, 2, 8, 1, 5000, 128, desc=spec())
+    assert same == pa.get_plan(pa.KIND_DECODE, 2, 8, 1, 5000, 128, desc=spec(), Hkv=8)
+    assert pa.parse_plan(pa.get_plan(pa.KIND_DECODE, 2, 32, 1, 5000, 128, desc=spec(),
+                                     Hkv=2)) != pa.parse_plan(same)
+
+
 # --------------------------------------------------------------------- GEMM
 GEMM_SHAPES = [(256, 256, 256), (1024, 1024, 1024), (4096, 4096, 4096), (16384, 256, 2048),
                (256, 256, 16384), (8192, 8192, 8192), (300, 520, 1000)]
@@ -264,19 +321,31 @@ GEMM_SHAPES = [(256, 256, 256), (1024, 1024, 1024), (4096, 4096, 4096), (16384, 
 def test_gemm_plan_is_the_argmin_of_its_candidates(shape, b_nk):
     desc = spec()
     M, N, K = shape
-    cands = pa.gemm_candidates(M, N, K, b_nk, desc=desc)
+    cands = pa.gemm_candidates(M, N, K, b_nk, desc=desc, deep=True)
     assert cands
-    best = min(c["modeled_us"] for c in cands)
+    # The fastest of the generic and the hand-scheduled kernel (the generic 64 x 64
+    # tile only over at most 8 k-tiles), or the deep-pipeline kernel's fastest where
+    # that is modelled faster -- against the hand-scheduled kernel by a factor.
+    best = min(c["modeled_us"] for c in cands
+               if not c["DEEP"] and not (c["BLOCK_M"] == 64 and K > 8 * c["BLOCK_K"]))
+    deep = min(c["modeled_us"] for c in cands if c["DEEP"])
     p = pa.parse_plan(pa.gemm_plan(M, N, K, b_nk, desc=desc))
-    assert abs(p["modeled_us"] - best) <= 1e-3 * best
+    assert abs(p["modeled_us"] - (deep if p["DEEP"] else best)) <= 1e-3 * best
+    if p["DEEP"]:
+        assert deep < best
+    else:
+        scheduled = (p["BLOCK_M"], p["BLOCK_N"], p["WAVES_M"], p["WAVES_N"]) == (256, 256, 2, 2)
+        assert best <= deep * (1.401 if scheduled else 1.001)
     for c in cands:
         assert c["lds_bytes"] <= desc.lds_bytes_per_cu
         splits = c["K_SPLITS"]
         assert c["grid"] == -(-M // c["BLOCK_M"]) * -(-N // c["BLOCK_N"]) * splits
         assert c["b_nk"] == int(b_nk)
         if splits > 1:
-            # hand-scheduled tiles only, whole k-tiles per split, none empty
-            assert (c["BLOCK_M"], c["BLOCK_N"], c["WAVES_M"], c["WAVES_N"]) == (256, 256, 2, 2)
+            # hand-scheduled and deep-pipeline tiles only, whole k-tiles per split,
+            # none empty
+            assert c["DEEP"] or \
+                (c["BLOCK_M"], c["BLOCK_N"], c["WAVES_M"], c["WAVES_N"]) == (256, 256, 2, 2)
             assert c["k_chunk"] % c["BLOCK_K"] == 0
             assert (splits - 1) * c["k_chunk"] < K <= splits * c["k_chunk"]
         else:
