@@ -159,10 +159,10 @@ bool plan_fwd_fixed(const attn_device_desc& desc, int B, int H, int Sq, int Skv,
                     int kv_splits, int fold, int form) {
     const bool singles = form == 1, tri = form == 2;
     FwdPlan p;
-    // The causal chunk kernel (single q-tiles: key splits, folded heads) where
-    // the cache before the chunk is at least as long as the chunk, so that the
-    // work is nearly a rectangle; shorter, the pairs balance the triangle and
-    // skip more of it.
+    // The causal chunk kernel: single q-tiles (form 1) and the triangle of key splits
+    // (form 2) at any length of the cache before the chunk; uniform key splits and
+    // folded heads (form 0) where it is at least as long as the chunk, so that the work
+    // is nearly a rectangle -- shorter, the pairs balance the triangle and skip more.
     if (singles && (!causal || kv_splits > 1 || fold > 1)) return false;
     if (form < 0 || form > 2 || (tri && (!causal || kv_splits < 2 || fold > 1))) return false;
     const bool chunk = causal && (kv_splits > 1 || fold > 1 || singles);
@@ -195,15 +195,6 @@ bool plan_fwd_fixed(const attn_device_desc& desc, int B, int H, int Sq, int Skv,
     int wg = desc.lds_bytes_per_cu / p.lds_bytes;
     wg = std::min(wg, (wpe_regs * simds) / waves);
     wg = std::min(wg, (desc.max_waves_per_simd * simds) / waves);
-    if (res) {  // the compiled kernel's real footprint overrides the estimate
-        KernelRes kr;
-        if (!res(d, bn, waves, pipe, chunk ? 2 : causal, &kr)) return false;
-        if (kr.scratch_bytes > 0) return false;  // spills: not a valid primitive
-        wg = kr.wg_per_cu;
-        if (kr.vgprs > 0) p.vgprs = kr.vgprs;
-    }
-    if (wg < 1) return false;
-    p.wg_per_cu = wg;
     p.n_qtiles = (Sq + p.block_m - 1) / p.block_m;
     // key splits: every split non-empty, chunks of whole tiles
     if (kv_splits < 1 || (kv_splits > 1 && pipe == 2)) return false;
@@ -219,14 +210,26 @@ bool plan_fwd_fixed(const attn_device_desc& desc, int B, int H, int Sq, int Skv,
         // (in some q-tile's last split, where early ones have fewer)
         const int lo = tri ? (p.n_qtiles - 1) * p.block_m : 0;
         if (causal && (long long)(kv_splits - 1) * p.kv_chunk > diag + lo) return false;
-        if (rows * d > 0xffffffffLL) return false;  // one combine workgroup per row
     }
     // causal workgroups take q-tile pairs (n-1-u, u), except in chunks
     const bool pairs = causal && !chunk;
     p.grid = (long long)B * H * (pairs ? (p.n_qtiles + 1) / 2 : (long long)p.n_qtiles * kv_splits);
     if (p.grid > 0x7fffffffLL) return false;
     // splits fill the device; beyond a few rounds of it they only add partials
-    if (kv_splits > 1 && p.grid > (long long)(tri ? 2 : 1) * kFwdSplitRounds * desc.num_cus) return false;
+    // (this bounds the rows of a split plan far below what the combine's grid holds)
+    if (kv_splits > 1 && p.grid > (long long)(tri ? 2 : 1) * kFwdSplitRounds * desc.num_cus)
+        return false;
+    // asked last: the query of the runtime costs more than all of the above, and most
+    // split counts end there
+    if (res) {  // the compiled kernel's real footprint overrides the estimate
+        KernelRes kr;
+        if (!res(d, bn, waves, pipe, chunk ? 2 : causal, &kr)) return false;
+        if (kr.scratch_bytes > 0) return false;  // spills: not a valid primitive
+        wg = kr.wg_per_cu;
+        if (kr.vgprs > 0) p.vgprs = kr.vgprs;
+    }
+    if (wg < 1) return false;
+    p.wg_per_cu = wg;
 
     const double mfma_cyc = 32768.0 / (desc.mfma_bf16_flops_per_clk_cu / simds);
     const double scores_per_lane = 32.0 * bn / desc.wave_size;
@@ -622,9 +625,9 @@ static double deep_scale(int bm, int bn, int slots) {
     return 1.5;
 }
 
-bool plan_gemm_deep_fixed(const attn_device_desc& desc, int M, int N, int K, int b_nk, int bm,
-                          int bn, int bk, int wm, int wn, int kg, int slots, int k_splits,
-                          GemmPlan* out, GemmResFn res) {
+// The tile and grid of one deep-pipeline candidate; false if it is none.
+static bool deep_tile(const attn_device_desc& desc, int M, int N, int K, int b_nk, int bm, int bn,
+                      int bk, int wm, int wn, int kg, int slots, int k_splits, GemmPlan* out) {
     bool known = false;
 #define ATTN_D(BM, BN, BK, WM, WN, KG, NSLOT)                                              \
     known |= bm == BM && bn == BN && bk == BK && wm == WM && wn == WN && kg == KG &&         \
@@ -649,19 +652,27 @@ bool plan_gemm_deep_fixed(const attn_device_desc& desc, int M, int N, int K, int
     p.b_nk = b_nk ? 1 : 0;
     p.lds_bytes = slots * (bm + bn) * bk * 2;  // no padding
     if (p.lds_bytes > desc.lds_bytes_per_cu) return false;
-    int g = desc.lds_bytes_per_cu / p.lds_bytes;
-    if (res) {
-        KernelRes kr;
-        if (!res(p, &kr) || kr.scratch_bytes > 0) return false;
-        g = kr.wg_per_cu;
-        p.vgprs = kr.vgprs;
-    }
-    if (g < 1) return false;
-    p.wg_per_cu = g;
+    p.wg_per_cu = desc.lds_bytes_per_cu / p.lds_bytes;
     p.tiles_m = (M + bm - 1) / bm;
     p.tiles_n = (N + bn - 1) / bn;
     p.grid = (long long)p.tiles_m * p.tiles_n * k_splits;
     if (p.grid > 0x7fffffffLL) return false;
+    *out = p;
+    return true;
+}
+
+// Its modelled time; kr: the compiled kernel's footprint, or null (estimated).
+static bool deep_model(const attn_device_desc& desc, int M, int N, int K, const KernelRes* kr,
+                       GemmPlan* plan) {
+    GemmPlan& p = *plan;
+    if (kr) {
+        if (kr->scratch_bytes > 0) return false;
+        p.wg_per_cu = kr->wg_per_cu;
+        p.vgprs = kr->vgprs;
+    }
+    const int g = p.wg_per_cu, bm = p.block_m, bn = p.block_n, bk = p.block_k;
+    const int wm = p.waves_m, wn = p.waves_n, slots = p.pipe + 1, k_splits = p.k_splits;
+    if (g < 1) return false;
 
     // One k-tile round of g workgroups on a CU, as in plan_gemm_fixed, with the
     // LDS bound counting the tile's writes, and the latency of an HBM-served
@@ -689,7 +700,7 @@ bool plan_gemm_deep_fixed(const attn_device_desc& desc, int M, int N, int K, int
         const double load = (1.0 - f_hbm) * kDeepL2Cycles + f_hbm * far_cycles;
         return scale * heg_pipe(load / (slots - 1), r * body + kDeepSyncCycles, 0.0, 1, 0);
     };
-    const int n_k = chunk_tiles;
+    const int n_k = (p.k_chunk + bk - 1) / bk;
     const double cu_full = desc.hbm_bytes_per_s / desc.num_cus / (desc.clock_ghz * 1e9);
     auto pass_of = [&](int r) {
         return far_cycles + heg_for(n_k, round_of(r)) + r * (double)bm * bn * 4.0 / cu_full;
@@ -718,8 +729,41 @@ bool plan_gemm_deep_fixed(const attn_device_desc& desc, int M, int N, int K, int
                      : 0.0;
     p.modeled_us = (full + (tail > 0.0 ? 1.0 : 0.0) > 1.0 ? kDeepRoundsFactor : kDeepFactor) *
                    (us + kDeepLaunchUs + reduce_us);
+    return true;
+}
+
+bool plan_gemm_deep_fixed(const attn_device_desc& desc, int M, int N, int K, int b_nk, int bm,
+                          int bn, int bk, int wm, int wn, int kg, int slots, int k_splits,
+                          GemmPlan* out, GemmResFn res) {
+    GemmPlan p;
+    KernelRes kr;
+    if (!deep_tile(desc, M, N, K, b_nk, bm, bn, bk, wm, wn, kg, slots, k_splits, &p) ||
+        (res && !res(p, &kr)) || !deep_model(desc, M, N, K, res ? &kr : nullptr, &p))
+        return false;
     *out = p;
     return true;
+}
+
+// Every deep-pipeline candidate.  The runtime is asked once for each tile's kernel,
+// which all of its split counts run: the query costs more than the model.
+template <typename F>
+static void deep_for_each(const attn_device_desc& desc, int M, int N, int K, int b_nk,
+                          bool may_split, GemmResFn res, F&& f) {
+    auto tile = [&](int bm, int bn, int bk, int wm, int wn, int kg, int slots) {
+        KernelRes kr;
+        bool asked = false;
+        for (int ks : kGemmDeepKSplits) {
+            if (ks > 1 && !may_split) break;
+            GemmPlan p;
+            if (!deep_tile(desc, M, N, K, b_nk, bm, bn, bk, wm, wn, kg, slots, ks, &p)) continue;
+            if (res && !asked && !res(p, &kr)) return;
+            asked = true;
+            if (deep_model(desc, M, N, K, res ? &kr : nullptr, &p)) f(p);
+        }
+    };
+#define ATTN_D(BM, BN, BK, WM, WN, KG, NSLOT) tile(BM, BN, BK, WM, WN, KG, NSLOT);
+    ATTN_DEEP_TILES(ATTN_D)
+#undef ATTN_D
 }
 
 bool plan_gemm_call(const attn_device_desc& desc, int M, int N, int K, int b_nk, bool may_split,
@@ -751,15 +795,7 @@ bool plan_gemm_call(const attn_device_desc& desc, int M, int N, int K, int b_nk,
     others(false);
     if (found && gemm_hand_scheduled(best.block_m, best.block_n, best.waves_m, best.waves_n))
         best.modeled_us /= kDeepOverSched;
-    for (int ks : kGemmDeepKSplits) {
-        if (ks > 1 && !may_split) break;
-        GemmPlan p;
-#define ATTN_D(BM, BN, BK, WM, WN, KG, NSLOT)                                                   \
-    if (plan_gemm_deep_fixed(desc, M, N, K, b_nk, BM, BN, BK, WM, WN, KG, NSLOT, ks, &p, res))   \
-        consider(p);
-        ATTN_DEEP_TILES(ATTN_D)
-#undef ATTN_D
-    }
+    deep_for_each(desc, M, N, K, b_nk, may_split, res, consider);
     if (found && !best.deep &&
         gemm_hand_scheduled(best.block_m, best.block_n, best.waves_m, best.waves_n))
         best.modeled_us *= kDeepOverSched;
@@ -783,14 +819,7 @@ int plan_gemm_all(const attn_device_desc& desc, int M, int N, int K, int b_nk, G
                 if (plan_gemm_fixed(desc, M, N, K, b_nk, t.bm, t.bn, t.bk, t.wm, t.wn, pipe, &p,
                                     res, splits))
                     add(p);
-    if (!deep) return n;
-    for (int ks : kGemmDeepKSplits) {
-#define ATTN_D(BM, BN, BK, WM, WN, KG, NSLOT)                                                   \
-    if (plan_gemm_deep_fixed(desc, M, N, K, b_nk, BM, BN, BK, WM, WN, KG, NSLOT, ks, &p, res))   \
-        add(p);
-        ATTN_DEEP_TILES(ATTN_D)
-#undef ATTN_D
-    }
+    if (deep) deep_for_each(desc, M, N, K, b_nk, true, res, add);
     return n;
 }
 

@@ -223,6 +223,40 @@ bool check_gemm_call(const attn_device_desc& desc, int M, int N, int K, int b_nk
     return true;
 }
 
+// Planning a new shape asks the runtime for a kernel's footprint only where it can
+// matter: once for each deep-pipeline tile, and in prefill for no more than the
+// feasible candidates.
+int fwd_queries = 0, deep_queries = 0;
+bool count_fwd(int, int, int, int, int, KernelRes* r) {
+    ++fwd_queries;
+    r->wg_per_cu = 1;
+    return true;
+}
+bool count_gemm(const GemmPlan& p, KernelRes* r) {
+    deep_queries += p.deep > 0;
+    r->wg_per_cu = 1;
+    return true;
+}
+bool check_queries(const attn_device_desc& desc) {
+    std::vector<FwdPlan> all(2048);
+    FwdPlan p;
+    for (const int Sq : {101, 3000, 8192})
+        for (const int causal : {0, 1}) {
+            fwd_queries = 0;
+            CHECK(plan_prefill(desc, 1, 32, Sq, Sq + 3000, 128, causal, 4, true, &p, count_fwd),
+                  "no plan for Sq %d", Sq);
+            const int asked = fwd_queries;
+            const int n = plan_fwd_all(desc, 1, 32, Sq, Sq + 3000, 128, causal, all.data(),
+                                       (int)all.size(), count_fwd, 4);
+            CHECK(asked <= n, "Sq %d: %d queries for %d candidates", Sq, asked, n);
+        }
+    GemmPlan g;
+    deep_queries = 0;
+    CHECK(plan_gemm_call(desc, 101, 1024, 4096, 0, true, &g, count_gemm), "no GEMM plan");
+    CHECK(deep_queries <= 7, "%d queries for seven deep-pipeline tiles", deep_queries);
+    return true;
+}
+
 }  // namespace
 
 int main(int argc, char** argv) {
@@ -237,6 +271,7 @@ int main(int argc, char** argv) {
         std::printf(failures ? "planted violation caught\n" : "planted violation missed\n");
         return failures ? 0 : 1;
     }
+    check_queries(desc);
     int plans = 0;
     std::vector<FwdPlan> all(512);
     for (int it = 0; it < 2000 && failures == 0; ++it) {
