@@ -598,26 +598,40 @@ bool plan_gemm_fixed(const attn_device_desc& desc, int M, int N, int K, int b_nk
 }
 
 // Deep-pipeline kernel: effective latencies of a k-tile from L2, and from beyond it
-// with operands that the memory-side cache holds and with a stream from HBM
-// (cycles of the nominal clock; the loads in flight share them), the barrier, what
-// another round of workgroups costs, and measured / modelled k-tile rounds of each
-// tile.  Fitted to 207 shapes (M 64..16384, N and K 256..16384 with up to 4e11
-// flops, every tile and 10 split counts).  The generic kernel's model reads a tenth
-// low beside it, which kDeepFactor evens out (kDeepRoundsFactor over more than one
-// round of workgroups, where the deep pipeline was rarely the best: 12351 x 656 x 1032
-// 39.4 us against 35.5, 5035 x 2248 x 1136 40.3 against 37.3; the 256-wide tiles' factor
-// is above the fitted 1.26 for 4336 x 1664 x 3000, 62.3 us against 56.8, and
-// 1886 x 3848 x 4776, 93.5 against 86.1); the hand-scheduled
-// kernel's model reads high, so it has to be beaten by more (kDeepOverSched:
-// 5173 x 656 x 16160 157 us against 140, 3864 x 272 x 10880 56 against 49).  With them
-// the pick over all kernels was 3.9% slower than the best on average, and the calls
-// 1.24 times as fast as with the other kernels' picks, 6 of 186 slower by over 5%
-// (at most 16%, all under 13 us: 6874 x 264 x 400 8.7 -> 10.1).
+// with operands of up to kDeepMallBytes and of more (cycles of the nominal clock; the
+// loads in flight share them), the barrier, what another round of workgroups costs, and
+// measured / modelled k-tile rounds of each tile.  Fitted to 207 shapes (M 64..16384, N
+// and K 256..16384 with up to 4e11 flops, every tile and 10 split counts).
+// kDeepMallBytes is where those shapes part best, not a capacity of the card (its
+// memory-side cache holds 256 MB); the modelled time steps there (M x 256 x 2048 from
+// 18.7 to 24.9 us between M 15360 and 15400).
+//
+// Factors over that fit, each for shapes where the pick was slower than the other
+// kernels':
+// - kDeepFactor: the generic kernel's model reads a tenth low beside this one;
+//   kDeepRoundsFactor over more than one round of workgroups, where this kernel was
+//   rarely the best: 12351 x 656 x 1032 39.4 us against 35.5, 5035 x 2248 x 1136 40.3
+//   against 37.3;
+// - deep_scale of the 256-wide tiles, fitted 1.26: 4336 x 1664 x 3000 62.3 us against
+//   56.8, 1886 x 3848 x 4776 93.5 against 86.1;
+// - kDeepOverSched: the hand-scheduled kernel's model reads high, so where it is the
+//   best of the others it has to be beaten by more: 5173 x 656 x 16160 157 us against 140,
+//   3864 x 272 x 10880 56 against 49;
+// - kDeepStream64: 64 x 64 tiles read each operand once for every 64 of the other, which
+//   costs more than modelled when both come from HBM and both dimensions have several
+//   tiles: 5484 x 120 x 7360 49.7 us against 38.2, 6922 x 256 x 4904 63.2 against 55.2; over 280
+//   shapes of more than 64 MB the factor makes the calls 2.1% faster, none slower.
+// Over 700 further drawn shapes (M from 8 or 64 to 16384, N and K to match) the calls take
+// 0.78 of the time that they took with the other kernels' picks (0.66 where the pick
+// differs); two are slower by over 5%, at most 6.5% (5865 x 520 x 656 15.4 -> 16.4 us).
+// Elsewhere 320 x 16152 x 2752 was seen 27% slower (64.8 -> 82.1, the generic 64 x 64 tile
+// without a k-tile in flight, which stands aside there).
 static constexpr double kDeepL2Cycles = 1027.0, kDeepMallCycles = 330.0, kDeepHbmCycles = 8508.0;
 static constexpr double kDeepMallBytes = 64e6;
 static constexpr double kDeepSyncCycles = 177.0, kDeepRoundCycles = 2493.0;
 static constexpr double kDeepLaunchUs = 2.85, kDeepReduceUs = 3.08, kDeepFactor = 1.1;
 static constexpr double kDeepOverSched = 1.4, kDeepRoundsFactor = 1.5;
+static constexpr double kDeepStream64 = 1.3;
 static double deep_scale(int bm, int bn, int slots) {
     if (bm + bn == 128) return 0.79;
     if (bm + bn == 192) return bm > bn ? 0.88 : 0.84;
@@ -683,9 +697,11 @@ static bool deep_model(const attn_device_desc& desc, int M, int N, int K, const 
                        desc.lds_bytes_per_clk_cu;
     const double body = std::max(mfma, lds);
     const double a_bytes = (double)bm * bk * 2.0, b_bytes = (double)bn * bk * 2.0;
-    const double scale = deep_scale(bm, bn, slots);
-    const double far_cycles =
-        2.0 * ((double)M * K + (double)K * N) > kDeepMallBytes ? kDeepHbmCycles : kDeepMallCycles;
+    const bool stream = 2.0 * ((double)M * K + (double)K * N) > kDeepMallBytes;
+    const double far_cycles = stream ? kDeepHbmCycles : kDeepMallCycles;
+    const double scale =
+        deep_scale(bm, bn, slots) *
+        (stream && bm + bn == 128 && M > bm && N > bn ? kDeepStream64 : 1.0);
     // HBM bytes of one round of the whole grid: the tiles of an XCD share panels
     auto round_of = [&](int r) {
         const double xcd_tiles =
@@ -766,6 +782,35 @@ static void deep_for_each(const attn_device_desc& desc, int M, int N, int K, int
 #undef ATTN_D
 }
 
+// Whether K is long enough for a deep-pipeline candidate to stand against the other
+// kernels.  Its model charges what its pipeline hides on a long K; over few k-tiles it
+// reads low, most where a tile is large or shares its CU: the fill and the epilogue
+// are then most of the time.  Generic kernel -> this one, us, of about 1500 drawn shapes:
+// - up to 5 k-tiles 48 of 56 were slower, by up to 21% (267 x 4296 x 40 4.1 -> 5.0,
+//   1037 x 352 x 88 3.5 -> 4.2, 148 x 6304 x 256 5.1 -> 5.7; best 5565 x 80 x 264 -1%);
+// - up to 13, the 128 x 128 tile of four slots where the whole chip has less than 8.75
+//   k-tiles to a CU: 3754 x 688 x 408 9.8 -> 11.2, 5113 x 416 x 664 12.7 -> 15.2, 6109 x 360 x
+//   784 15.9 -> 17.5; with more 147 x 16040 x 648 17.2 -> 14.9, 424 x 6032 x 728 16.4 -> 15.0;
+// - up to 11, that of two slots with at most one workgroup per CU: 4176 x 576 x 544 11.1 ->
+//   13.9, 1146 x 3536 x 624 14.7 -> 17.8; with more 10924 x 456 x 600 25.0 -> 19.1, 13092 x 424
+//   x 432 19.5 -> 16.0;
+// - up to 11, the 64 x 128 and 128 x 64 tiles with more than one, where 128 x 128 tiles
+//   would have a CU each: 833 x 2592 x 344 8.3 -> 10.1, 14462 x 224 x 576 11.8 -> 13.7; where
+//   they would not 303 x 11616 x 600 19.2 -> 15.8; with at most one 7195 x 240 x 536 11.2 ->
+//   10.1, 487 x 3544 x 584 10.5 -> 9.9.
+static bool deep_fits_k(const attn_device_desc& desc, const GemmPlan& p, int M, int N, int K) {
+    const int k_tiles = (K + p.block_k - 1) / p.block_k, edges = p.block_m + p.block_n;
+    const long long cus = desc.num_cus;
+    if (k_tiles > 13) return true;
+    if (k_tiles < 6) return false;
+    if (edges == 256 && p.pipe == 3) return k_tiles > 10 && 4 * k_tiles * p.grid >= 35 * cus;
+    if (k_tiles > 11 || edges == 128) return true;
+    if (edges == 192)
+        return p.grid <= cus ||
+               (p.grid <= 2 * cus && (long long)((M + 127) / 128) * ((N + 127) / 128) > cus);
+    return edges == 256 && p.grid > cus;
+}
+
 bool plan_gemm_call(const attn_device_desc& desc, int M, int N, int K, int b_nk, bool may_split,
                     GemmPlan* out, GemmResFn res) {
     GemmPlan best;
@@ -779,23 +824,29 @@ bool plan_gemm_call(const attn_device_desc& desc, int M, int N, int K, int b_nk,
     // aside over more than 8 k-tiles: its model knows no latency that two k-tiles in
     // flight cannot hide (156 x 5296 x 1360: modelled 8.7 us, measured 14.0, the same
     // tile of the deep-pipeline kernel 9.7; 81 x 2120 x 13224: 114 against 27).  Over
-    // fewer it is as fast or faster (176 x 976 x 368: 4.7 against 4.9).
+    // fewer it is as fast or faster (176 x 976 x 368: 4.7 against 4.9).  In one
+    // round of three workgroups per CU it stays up to 11, where the larger deep-pipeline
+    // tiles stand aside (227 x 8504 x 528: 12.0, the generic 128 x 128 tile 14.7).
     auto others = [&](bool long_k_64) {
         for (const GemmTile& t : kGemmTiles)
             for (int pipe = t.pipe_min; pipe <= t.pipe_max; ++pipe)
                 for (int splits : kGemmKSplits) {
                     if (splits > 1 && !may_split) break;
                     GemmPlan p;
-                    if ((long_k_64 || !(t.bm == 64 && K > 8 * t.bk)) &&
-                        plan_gemm_fixed(desc, M, N, K, b_nk, t.bm, t.bn, t.bk, t.wm, t.wn, pipe,
-                                        &p, res, splits))
+                    if (plan_gemm_fixed(desc, M, N, K, b_nk, t.bm, t.bn, t.bk, t.wm, t.wn, pipe,
+                                        &p, res, splits) &&
+                        (long_k_64 || t.bm != 64 || K <= 8 * t.bk ||
+                         (K <= 11 * t.bk && pipe > 0 && p.grid <= 3LL * desc.num_cus)))
                         consider(p);
                 }
     };
     others(false);
     if (found && gemm_hand_scheduled(best.block_m, best.block_n, best.waves_m, best.waves_n))
         best.modeled_us /= kDeepOverSched;
-    deep_for_each(desc, M, N, K, b_nk, may_split, res, consider);
+    const bool any = found;
+    deep_for_each(desc, M, N, K, b_nk, may_split, res, [&](const GemmPlan& p) {
+        if (!any || deep_fits_k(desc, p, M, N, K)) consider(p);
+    });
     if (found && !best.deep &&
         gemm_hand_scheduled(best.block_m, best.block_n, best.waves_m, best.waves_n))
         best.modeled_us *= kDeepOverSched;
