@@ -494,9 +494,16 @@ static hipError_t launch_split_combine_d(const float* ws_m, const float* ws_l, c
                                          void* o, int out_bf16, float* lse, long long rows,
                                          int n_splits, hipStream_t st, CombineRows cr) {
     constexpr int GROUPS = 256 / (D / 4);
-    // one workgroup per row while the rows are too few to fill the device with
-    // a lane group each, or the chain of splits is long
-    const bool par = n_splits >= 8 && rows <= 65536;
+    // One workgroup per row where few rows leave the device idle or the chain of
+    // splits is long.  us, a lane group / a workgroup per row, back to back: d128, 16
+    // splits of 1024, 4096, 16384 rows 3.9/3.6, 5.1/6.3, 25.4/21.1, 64 splits of 512 and
+    // 4096 7.4/3.8, 27.7/20.5; d64, 32 splits of the same three 4.9/3.7, 6.7/7.0, 22.5/22.4.
+    // Over many rows a short chain leaves most of a workgroup idle: 8 splits of 4096 and
+    // 16384 rows 3.6/5.7 and 12.3/16.4 (d128), 3.6/5.6 and 5.3/15.8 (d64).  Right behind the
+    // kernel that wrote the partials each step of a chain waits longer, and up to 2048
+    // rows the whole call is 0.5 to 1.7 us faster with a workgroup per row: 328 rows of 24
+    // splits 11.1/9.3, 1056 of 16 16.2/15.5 (d64), 296 of 12 12.8/11.8 (d128).
+    const bool par = rows <= 2048 ? n_splits >= 8 : (long long)n_splits * D >= 2048 && rows <= 65536;
     const long long wgs = par ? rows : (rows + GROUPS - 1) / GROUPS;
     if (wgs * 256 > 0xffffffffLL) return hipErrorInvalidValue;  // threads of one grid
     if (par)

@@ -571,3 +571,24 @@ def test_plan_query_reports_the_plan_that_runs(pa, shape):
     B, Hq, Hkv, Sq, Skv, causal = shape
     assert call_plan(pa, B, Hq, Hkv, Sq, Skv, 128, causal) == pa.parse_plan(
         pa.get_plan(pa.KIND_FWD, B, Hq, Sq, Skv, 128, causal, Hkv=Hkv))
+
+
+# key splits and rows on both sides of where the combine gives each row a workgroup: 8
+# splits up to 2048 rows, past them chains of 2048 / d splits
+@pytest.mark.parametrize("d,rows,splits", [(128, 2047, 6), (128, 2048, 8), (128, 2049, 8),
+                                           (128, 2049, 12), (128, 2049, 16), (64, 2048, 8),
+                                           (64, 2049, 24), (64, 2049, 32)])
+def test_fwd_split_combine_forms(pa, d, rows, splits):
+    B, H, Skv = 1, 1, 32 * splits - 5
+    q, k, v = _qkv(B, H, H, rows, Skv, d, 2600 + splits)
+    sc = float(np.float32(1.0 / math.sqrt(d)))
+    announce(f"split combine d={d} rows={rows} splits={splits}")
+    with forced_split_plan(32, 4, 1, splits):
+        o, lse = pa.attn_fwd(q.to(DEV), k.to(DEV), v.to(DEV), return_lse=True)
+        o16 = pa.attn_fwd(q.to(DEV), k.to(DEV), v.to(DEV), out_dtype=torch.bfloat16)
+    torch.cuda.synchronize()
+    ref, ref_lse = oracle.attn_gqa(q, k, v, B, H, H, rows, Skv, d, sc, False)
+    compare(o, ref, f"combine d={d} rows={rows} splits={splits}")
+    compare(lse, ref_lse, f"combine lse d={d} rows={rows} splits={splits}", max_abs=LSE_MAX_ABS,
+            mean_abs=LSE_MEAN_ABS)
+    assert torch.equal(o16.cpu(), o.cpu().to(torch.bfloat16))
