@@ -407,13 +407,43 @@ bool plan_fwd(const attn_device_desc& desc, int B, int H, int Sq, int Skv, int d
     return b.found;
 }
 
+// Two corrections of the pick, where the model of the single q-tiles and of the split
+// triangle reads low (us, what it replaced in the plain form / the pick / the plan
+// taken instead):
+// - at d = 128 the triangle against pairs of the same (64, 8, 3) tile has to win by
+//   kTriOverPairs: B1 H16 d128 S4461 129 / 135 / 129, S4313 125 / 129 / 125, B2 H8 S4727 138 / 146 / 138, all
+//   modelled 3 to 10% faster than the pairs (d = 64 B1 H16 S4306 100 / 94 / 100);
+// - at d = 64 the four-wave single q-tiles take a (64, 8, 3) pick up to kSingle4For8 of its
+//   modelled time (their tile costs are those of pairs at d = 128): B4 Hq32 S515 20.5 / 24.0 /
+//   16.6, B1 Hq32 S5428 156 / 166 / 155, B3 Hq32 S1667 59.6 / 61.9 / 59.5, modelled up to
+//   1.46 times the pick; past that they gain nothing (B1 Hq32 S2381 53.0 / 55.7 / 56.5).
+// Over 1100 drawn causal shapes 7 are over 3% slower than in the plain form, by at most
+// 10.5% (B1 H16 S1509 d64, the triangle: 29.4 -> 32.5 us); the mean is 0.775 of its time.
+static constexpr double kTriOverPairs = 1.1, kSingle4For8 = 1.5;
+
 bool plan_prefill(const attn_device_desc& desc, int B, int H, int Sq, int Skv, int d, int causal,
                   int group, bool may_split, FwdPlan* out, FwdResFn res) {
-    FwdBest b;
-    fwd_for_each(desc, B, H, Sq, Skv, d, causal, res, true, 1, may_split, b);
-    if (group > 1) fwd_for_each(desc, B, H, Sq, Skv, d, causal, res, true, group, may_split, b);
-    if (b.found) *out = b.best;
-    return b.found;
+    FwdBest b, plain, four;
+    auto single = [](const FwdPlan& p) { return p.chunk && p.kv_splits == 1 && p.fold == 1; };
+    auto consider = [&](const FwdPlan& p) {
+        b(p);
+        if (!p.chunk && p.fold == 1) plain(p);
+        if (single(p) && p.waves == 4 && p.block_n == 64) four(p);
+    };
+    fwd_for_each(desc, B, H, Sq, Skv, d, causal, res, true, 1, may_split, consider);
+    if (group > 1)
+        fwd_for_each(desc, B, H, Sq, Skv, d, causal, res, true, group, may_split, consider);
+    if (!b.found) return false;
+    *out = b.best;
+    const double us = b.best.modeled_us;
+    if (d == 128 && b.best.tri && b.best.waves == 8 && plain.found && plain.best.waves == 8 &&
+        plain.best.block_n == 64 && plain.best.pipe == 3 &&
+        plain.best.modeled_us < kTriOverPairs * us)
+        *out = plain.best;
+    if (d == 64 && single(b.best) && b.best.waves == 8 && four.found &&
+        four.best.modeled_us < kSingle4For8 * us)
+        *out = four.best;
+    return true;
 }
 
 int plan_fwd_all(const attn_device_desc& desc, int B, int H, int Sq, int Skv, int d, int causal,

@@ -275,7 +275,7 @@ FORMS = [((4, 16, 16, 2048, 2048, 128, True), "plain"),
 @pytest.mark.parametrize("shape,want", FORMS, ids=[f"{f[1]}-{f[0][3]}x{f[0][4]}" for f in FORMS])
 def test_prefill_plan_of_a_call(shape, want):
     """The plan query with both head counts gives the fastest modelled candidate
-    over every form of the call."""
+    over every form of the call (these shapes' picks need no correction)."""
     B, Hq, Hkv, Sq, Skv, d, causal = shape
     desc = spec()
     p = pa.parse_plan(pa.get_plan(pa.KIND_FWD, B, Hq, Sq, Skv, d, causal, desc=desc, Hkv=Hkv))
@@ -298,6 +298,24 @@ def test_prefill_plan_of_a_call(shape, want):
             # the partials: four rounds of the compute units, the triangle's eight
             rounds = 8 if c["CHUNK"] == 2 else 4
             assert B * Hq * Sq * n * (d + 2) * 4 <= rounds * desc.num_cus * 256 * (d + 2) * 4
+
+
+# where the model reads low and the pick is corrected, and beside it
+CORRECTED = [((1, 16, 16, 4461, 4461, 128), (64, 8, 3), "plain"),
+             ((2, 8, 8, 4727, 4727, 128), (64, 8, 3), "plain"),
+             ((1, 8, 2, 3599, 3599, 128), (64, 8, 3), "triangle"),
+             ((1, 16, 16, 4306, 4316, 64), (64, 8, 3), "triangle"),
+             ((4, 32, 16, 515, 515, 64), (64, 4, 1), "singles"),
+             ((1, 32, 8, 5313, 5313, 64), (64, 4, 1), "singles"),
+             ((1, 32, 16, 2669, 2669, 64), (64, 8, 3), "singles"),
+             ((2, 32, 32, 1585, 1585, 128), (64, 8, 3), "singles")]
+
+
+@pytest.mark.parametrize("shape,tile,want", CORRECTED, ids=[str(c[0]) for c in CORRECTED])
+def test_prefill_pick_where_the_model_reads_low(shape, tile, want):
+    B, Hq, Hkv, Sq, Skv, d = shape
+    p = pa.parse_plan(pa.get_plan(pa.KIND_FWD, B, Hq, Sq, Skv, d, True, desc=spec(), Hkv=Hkv))
+    assert (p["BLOCK_N"], p["WAVES"], p["PIPE"]) == tile and form(p) == want
 
 
 def test_plan_query_checks_the_head_counts():
