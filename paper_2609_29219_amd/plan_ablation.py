@@ -4,7 +4,8 @@
                                                  [--only-calibration] [--markdown FILE] [--gemm]
 
 For each workload every feasible prefill candidate (block sizes, waves,
-pipeline knob, key splits) is run through the ATTN_FORCE_PLAN hook and timed, and set
+pipeline knob, key splits, and the call's form: folded query heads, causal chunks, single
+q-tiles, the split triangle) is run through the ATTN_FORCE_PLAN hook and timed, and set
 against the planner's modelled time: where the planner's pick ranks among the
 measured times, how far it is from the measured best, how far the pick of the
 analytic model alone (without the per-variant tile costs) is from it, whether
@@ -20,10 +21,11 @@ paper validates its model the same way (top-k candidates and block-size
 neighbourhoods); measurement here validates, it never selects.
 
 --gemm runs the same validation for the GEMM over the paper's shape range
-(256 to 16384, square and skewed): every feasible tile (BM, BN, BK, wave
-grid, pipe) is timed; the report gives the planner pick's measured and
-modelled TFLOP/s, its rank, and its rank among the tiles one legal step away
-in BM, BN, BK and pipe (the paper's local block-size perturbation).
+(256 to 16384, square and skewed) and some shapes of few rows or few k-tiles: every
+feasible tile (BM, BN, BK, wave grid, pipe, K splits) of all three kernels is timed; the
+report gives the measured and modelled TFLOP/s of the plan that a call runs, its
+rank, and its rank among the same kernel's tiles one legal step away in BM, BN, BK, pipe
+and K splits (the paper's local block-size perturbation).
 
 --fit refits the four offline-calibrated fields of the device description
 (issue_cycles_per_score, valu_mfma_overlap, tile_sync_cycles,
@@ -48,7 +50,7 @@ sys.path.insert(0, ROOT)
 
 import paper_2609_29219_amd as pa  # noqa: E402
 
-# (name, B, H, Sq, Skv, d, causal)
+# (name, B, H, Sq, Skv, d, causal[, query heads to a key/value head])
 WORKLOADS = [
     # the calibration shapes: the analytic fields are fitted and the per-variant
     # tile costs characterised on these two only
@@ -66,6 +68,12 @@ WORKLOADS = [
     # few heads / few queries against many keys: key splits fill the CUs
     ("b1_h2_s8192_d128", 1, 2, 8192, 8192, 128, False),
     ("b1_h32_q256_kv32768_d128", 1, 32, 256, 32768, 128, False),
+    # the other forms: a grouped-query chunk behind a cache, a few tokens of one, grids of
+    # pairs that leave CUs idle, a causal call of few heads
+    ("b1_h32_kv8_q512_kv16384_d128_causal", 1, 32, 512, 16384, 128, True, 4),
+    ("b2_h16_kv2_q9_kv3000_d128", 2, 16, 9, 3000, 128, False, 8),
+    ("b2_h32_kv8_s1777_d128_causal", 2, 32, 1777, 1777, 128, True, 4),
+    ("b1_h8_s2048_d128_causal", 1, 8, 2048, 2048, 128, True),
 ]
 CALIBRATION = ("b2_h16_s4096_d128", "b2_h16_s4096_d128_causal")
 # the benchmarked decode workloads: (name, B, H, Skv, d)
@@ -77,8 +85,16 @@ CALIBRATED = ("issue_cycles_per_score", "valu_mfma_overlap", "tile_sync_cycles",
               "tile_latency_cycles")
 
 
+def group_of(w: tuple) -> int:
+    return w[7] if len(w) > 7 else 1
+
+
 def key(c: dict) -> tuple:
-    return (c["BLOCK_N"], c["WAVES"], c["PIPE"], c["KV_SPLITS"])
+    """Tile, key splits, folded heads and the form that ATTN_FORCE_PLAN names: 1 single
+    q-tiles, 2 the split triangle, 0 any other."""
+    form = 0 if not c["CHUNK"] else 2 if c["CHUNK"] == 2 else \
+        int(c["KV_SPLITS"] == 1 and c["FOLD"] == 1)
+    return (c["BLOCK_N"], c["WAVES"], c["PIPE"], c["KV_SPLITS"], c["FOLD"], form)
 
 
 def time_variant(w, variant, iters=10, reps=3) -> float:
@@ -86,19 +102,19 @@ def time_variant(w, variant, iters=10, reps=3) -> float:
     import torch
     from attn_inputs import random_bf16
     from attn_inputs import BY_NAME, make_inputs
-    name, B, H, Sq, Skv, d, causal = w
+    name, B, H, Sq, Skv, d, causal = w[:7]
     if not hasattr(time_variant, "cache") or time_variant.cache[0] != name:
         if name in BY_NAME:  # a benchmarked workload: its own inputs
             q, k, v = (t.cuda() for t in make_inputs(BY_NAME[name]))
         else:
             q = random_bf16((B, H, Sq, d), 11).cuda()
-            k = random_bf16((B, H, Skv, d), 12).cuda()
-            v = random_bf16((B, H, Skv, d), 13).cuda()
+            k = random_bf16((B, H // group_of(w), Skv, d), 12).cuda()
+            v = random_bf16((B, H // group_of(w), Skv, d), 13).cuda()
         o = torch.empty((B, H, Sq, d), dtype=torch.float32, device="cuda")
         time_variant.cache = (name, q, k, v, o)
     _, q, k, v, o = time_variant.cache
-    bn, nw, pipe, ns = variant
-    os.environ["ATTN_FORCE_PLAN"] = f"bn={bn},waves={nw},pipe={pipe},splits={ns}"
+    os.environ["ATTN_FORCE_PLAN"] = \
+        "bn=%d,waves=%d,pipe=%d,splits=%d,fold=%d,form=%d" % variant
     try:
         for _ in range(3):
             pa.attn_fwd(q, k, v, o=o, causal=causal)
@@ -122,6 +138,8 @@ def neighbours(pick: tuple, feasible: set) -> list:
     domains = ((32, 64, 128), (4, 8), (0, 1, 2, 3), SPLITS)
     out = []
     for c in feasible:
+        if c[4:] != pick[4:]:
+            continue
         steps = [abs(dom.index(a) - dom.index(b)) for dom, a, b in zip(domains, c, pick)]
         if max(steps) <= 1 and sum(steps) > 0:
             out.append(c)
@@ -149,7 +167,9 @@ def summarise(w, cands: list, meas: dict, analytic: list) -> dict:
     rows = [(c["modeled_us"], meas[key(c)], key(c)) for c in cands if key(c) in meas]
     by_model = sorted(rows)
     by_meas = sorted(rows, key=lambda r: r[1])
-    pick, best = by_model[0], by_meas[0]
+    # what a call runs (where the model of a form reads low, not always its least time)
+    plan = key(pa.parse_plan(pa.get_plan(pa.KIND_FWD, *w[1:6], w[6], Hkv=w[2] // group_of(w))))
+    pick, best = next(r for r in rows if r[2] == plan), by_meas[0]
     # the analytic model alone (without the per-variant tile costs)
     arows = sorted((c["modeled_us"], meas[key(c)], key(c)) for c in analytic if key(c) in meas)
     apick = arows[0]
@@ -190,7 +210,7 @@ def fit(data: dict) -> dict:
             meas = data.get(w[0])
             if not meas or w[0] not in CALIBRATION:
                 continue
-            for c in pa.fwd_candidates(*w[1:], desc=desc, device_footprint=True,
+            for c in pa.fwd_candidates(*w[1:7], desc=desc, device_footprint=True,
                                        analytic_only=True):
                 t = meas.get(key(c))
                 if t:
@@ -207,7 +227,7 @@ def fit(data: dict) -> dict:
 
 def markdown(summaries: list, fitted: dict | None, decode: list | None = None) -> str:
     out = ["| workload | role | candidates | analytic-only pick vs best | planner pick (BN, waves, "
-           "pipe, splits) | pick vs measured best | pick's measured rank | best in model top-5 | "
+           "pipe, splits, fold, form) | pick vs measured best | pick's measured rank | best in model top-5 | "
            "Spearman | pick's rank among its neighbours |",
            "|---|---|---|---|---|---|---|---|---|---|"]
     for s in summaries:
@@ -306,14 +326,15 @@ def decode_ablation(data: dict, load: bool) -> list:
 # (M, N, K): squares across the paper's range and its skewed shapes
 GEMM_SHAPES = [(256, 256, 256), (1024, 1024, 1024), (2048, 2048, 2048), (4096, 4096, 4096),
                (8192, 8192, 8192), (16384, 16384, 16384), (16384, 256, 2048), (256, 256, 2048),
-               (16384, 256, 16384), (2048, 2048, 16384)]
-GEMM_DOMAINS = ((64, 128, 256), (64, 128, 256), (32, 64), (0, 1, 2, 3),
-                (1, 2, 3, 4, 6, 8))  # BM, BN, BK, pipe, K splits
+               (16384, 256, 16384), (2048, 2048, 16384), (100, 4096, 4096), (195, 4072, 9216),
+               (6874, 264, 400)]
+GEMM_DOMAINS = ((64, 128, 256), (64, 128, 256), (32, 64), (0, 1, 2, 3, 4),
+                (1, 2, 3, 4, 6, 8, 12, 16, 24, 32))  # BM, BN, BK, pipe, K splits
 
 
 def gemm_key(c: dict) -> tuple:
     return (c["BLOCK_M"], c["BLOCK_N"], c["BLOCK_K"], c["WAVES_M"], c["WAVES_N"], c["PIPE"],
-            c.get("K_SPLITS", 1))
+            c["K_SPLITS"], c["DEEP"])
 
 
 def time_gemm(shape, variant, reps=3) -> float:
@@ -328,7 +349,8 @@ def time_gemm(shape, variant, reps=3) -> float:
         time_gemm.cache = (shape, a, b, c)
     _, a, b, c = time_gemm.cache
     iters = 3 if M * N * K > 2 ** 40 else 10
-    os.environ["ATTN_FORCE_GEMM"] = "bm=%d,bn=%d,bk=%d,wm=%d,wn=%d,pipe=%d,splits=%d" % variant
+    os.environ["ATTN_FORCE_GEMM"] = \
+        "bm=%d,bn=%d,bk=%d,wm=%d,wn=%d,pipe=%d,splits=%d,deep=%d" % variant
     try:
         for _ in range(3):
             pa.gemm(a, b, c)
@@ -348,10 +370,12 @@ def time_gemm(shape, variant, reps=3) -> float:
 
 
 def gemm_neighbours(pick: tuple, feasible: set) -> list:
-    """Feasible tiles whose BM, BN, BK, pipe and K split are each at most one
-    legal step from the pick's (the paper's local block-size perturbation)."""
+    """Feasible tiles of the pick's kernel whose BM, BN, BK, pipe and K split are each
+    at most one legal step from the pick's (the paper's local block-size perturbation)."""
     out = []
     for c in feasible:
+        if bool(c[7]) != bool(pick[7]):
+            continue
         steps = [abs(dom.index(x) - dom.index(y))
                  for dom, x, y in zip(GEMM_DOMAINS, (c[0], c[1], c[2], c[5], c[6]),
                                       (pick[0], pick[1], pick[2], pick[5], pick[6]))]
@@ -365,9 +389,11 @@ def gemm_summary(shape, cands: list, meas: dict) -> dict:
     flops = 2.0 * M * N * K
     rows = [(c["modeled_us"], meas[gemm_key(c)], gemm_key(c)) for c in cands
             if gemm_key(c) in meas]
-    by_model = sorted(rows)
     by_meas = sorted(rows, key=lambda r: r[1])
-    pick, best = by_model[0], by_meas[0]
+    # what a call runs: over few k-tiles, and against the hand-scheduled kernel, not
+    # always the least modelled time
+    plan = gemm_key(pa.parse_plan(pa.gemm_plan(M, N, K)))
+    pick, best = next(r for r in rows if r[2] == plan), by_meas[0]
     nb = gemm_neighbours(pick[2], {r[2] for r in rows})
     return {
         "shape": shape, "candidates": len(rows), "pick": pick[2], "pick_us": pick[1],
@@ -381,7 +407,7 @@ def gemm_summary(shape, cands: list, meas: dict) -> dict:
 
 
 def gemm_markdown(summaries: list) -> str:
-    out = ["| M, N, K | candidates | planner pick (BM, BN, BK, WM, WN, pipe) | measured TFLOP/s "
+    out = ["| M, N, K | candidates | planner pick (BM, BN, BK, WM, WN, pipe, K splits, deep) | measured TFLOP/s "
            "(modelled) | pick vs measured best | pick's measured rank | Spearman | pick's rank "
            "among its block-size neighbours |", "|---|---|---|---|---|---|---|---|"]
     for s in summaries:
@@ -397,9 +423,9 @@ def main_gemm(a):
     if a.load:
         with open(a.load) as f:
             raw = json.load(f)
-        data = {tuple(map(int, s.split(","))): {(tuple(map(int, k.split(","))) + (1,))[:7]: t
+        data = {tuple(map(int, s.split(","))): {tuple(map(int, k.split(","))): t
                                                for k, t in m.items()} for s, m in raw.items()}
-    cands = {shape: pa.gemm_candidates(*shape) for shape in GEMM_SHAPES}
+    cands = {shape: pa.gemm_candidates(*shape, deep=True) for shape in GEMM_SHAPES}
     if not a.load:
         for shape in GEMM_SHAPES:
             meas = {}
@@ -444,13 +470,12 @@ def main():
     if a.load:
         with open(a.load) as f:
             raw = json.load(f)
-        # keys "bn,waves,pipe[,splits]" (measurements from before key splits: 1 split)
-        data = {w: {(tuple(map(int, k.split(","))) + (1,))[:4]: t for k, t in m.items()}
+        data = {w: {tuple(map(int, k.split(","))): t for k, t in m.items()}
                 for w, m in raw.items() if w != "decode"}
     summaries = []
     workloads = [w for w in WORKLOADS if not a.only_calibration or w[0] in CALIBRATION]
     for w in workloads:
-        cands = pa.fwd_candidates(*w[1:])
+        cands = pa.fwd_candidates(*w[1:7], group=group_of(w))
         if not a.load:
             meas = {}
             for c in cands:
@@ -460,7 +485,8 @@ def main():
             data[w[0]] = meas
         if w[0] in data:
             summaries.append(summarise(w, cands, data[w[0]],
-                                       pa.fwd_candidates(*w[1:], analytic_only=True)))
+                                       pa.fwd_candidates(*w[1:7], analytic_only=True,
+                                                         group=group_of(w))))
     decode_data = {}
     if a.load and "decode" in raw:
         decode_data = {w: {int(n): t for n, t in m.items()} for w, m in raw["decode"].items()}
