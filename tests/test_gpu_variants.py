@@ -437,36 +437,37 @@ def test_fwd_causal_single_tiles(pa, tile, d):
                 mean_abs=LSE_MEAN_ABS)
 
 
-# B, Hq, Hkv, Sq, Skv, splits: a split per q-tile and one more row; splits that end
-# inside, at and one key past a q-tile's first row; a cache shorter than the chunk;
-# early q-tiles of one split and late ones of all; grouped heads
-TRIANGLES = [(1, 1, 1, 513, 513, 2), (2, 4, 2, 600, 600, 4), (1, 3, 1, 1100, 1100, 8),
-             (1, 2, 2, 700, 801, 3), (1, 1, 1, 1024, 1024, 16), (1, 2, 1, 640, 1000, 6)]
+# B, Hq, Hkv, Sq, Skv, splits, by the rows of a q-tile: a split per q-tile and one more
+# row; splits that end inside, at and past a q-tile's first row; a cache shorter than the
+# chunk; early q-tiles of one split and late ones of all; grouped heads; chains that the
+# combine walks in parallel (8 and 16 splits, up to 2048 rows and more)
+TRIANGLES = {256: [(1, 1, 1, 513, 513, 2), (2, 4, 2, 1100, 1100, 4), (1, 3, 1, 2048, 2048, 8),
+                   (1, 2, 2, 700, 900, 3), (1, 1, 1, 4096, 4096, 16), (1, 2, 1, 1400, 1790, 6)],
+             128: [(1, 1, 1, 257, 257, 2), (2, 4, 2, 650, 650, 4), (1, 3, 1, 1024, 1024, 8),
+                   (1, 2, 2, 400, 520, 3), (1, 1, 1, 2048, 2048, 16), (1, 2, 1, 700, 760, 6)]}
 
 
 @pytest.mark.parametrize("tile", [(64, 8, 3), (64, 4, 1), (32, 4, 1)])
 @pytest.mark.parametrize("d", [64, 128])
 def test_fwd_causal_split_triangle(pa, tile, d):
-    for i, (B, Hq, Hkv, Sq, Skv, splits) in enumerate(TRIANGLES):
-        per = -(-Skv // splits)
-        chunk = -(-per // tile[0]) * tile[0]
-        if -(-Skv // chunk) != splits or \
-                (splits - 1) * chunk > Skv - Sq + (Sq - 1) // (32 * tile[1]) * 32 * tile[1]:
-            continue  # an empty split, or one that no q-tile has
+    for i, (B, Hq, Hkv, Sq, Skv, splits) in enumerate(TRIANGLES[32 * tile[1]]):
         q, k, v = _qkv(B, Hq, Hkv, Sq, Skv, d, 2100 + 7 * i + d)
         qd, kd, vd = q.to(DEV), k.to(DEV), v.to(DEV)
         sc = float(np.float32(1.0 / math.sqrt(d)))
-        announce(f"attn_fwd_ex causal split triangle {tile} d={d} {TRIANGLES[i]}")
-        # NaN in the workspace where no split of a row writes
-        with forced_split_plan(*tile, 2):
-            pa.attn_fwd(torch.full_like(qd, float("nan")), kd, vd)
-        with forced_chunk_plan(*tile, splits, 1, form=2):
+        what = (B, Hq, Hkv, Sq, Skv, splits)
+        announce(f"attn_fwd_ex causal split triangle {tile} d={d} {what}")
+        # NaN in every partial of the workspace, laid out alike (the same rows and
+        # splits): where no split of a row writes, none may be read
+        with forced_split_plan(*tile, splits):
+            poison = pa.attn_fwd(torch.full_like(qd, float("nan")), kd, vd)
+        with forced_chunk_plan(*tile, splits, 1, form=2):  # (refused if it were infeasible)
             o, lse = pa.attn_fwd(qd, kd, vd, causal=True, return_lse=True)
             o16 = pa.attn_fwd(qd, kd, vd, causal=True, out_dtype=torch.bfloat16)
         torch.cuda.synchronize()
+        assert torch.isnan(poison).all()
         ref, ref_lse = oracle.attn_gqa(q, k, v, B, Hq, Hkv, Sq, Skv, d, sc, True)
-        compare(o, ref, f"triangle {tile} d={d} {TRIANGLES[i]}")
-        compare(lse, ref_lse, f"triangle {tile} d={d} {TRIANGLES[i]} lse", max_abs=LSE_MAX_ABS,
+        compare(o, ref, f"triangle {tile} d={d} {what}")
+        compare(lse, ref_lse, f"triangle {tile} d={d} {what} lse", max_abs=LSE_MAX_ABS,
                 mean_abs=LSE_MEAN_ABS)
         assert torch.equal(o16.cpu(), o.cpu().to(torch.bfloat16))
 
