@@ -83,16 +83,23 @@ int attn_fwd(const void* q, const void* k, const void* v, float* o, int B, int H
  *   exp(s_ij - lse_i) -- what a caller needs to merge partial attention
  *   results (split-KV, ring attention).
  * Split keys: when the heads and q-tiles are too few to fill the device,
- * the planner may split each head's keys (non-causal only) into chunks
- * handled by separate workgroups, as Flash Decode splits its reduction
- * dimension; their partial results (row max, sum, unnormalised output) go
- * to the per-stream workspace described under attn_decode, and a combine
- * kernel on the same stream writes o and lse.  Such a call may allocate or
- * grow that workspace (ATTN_ENOMEM on failure); the result equals the
- * unsplit one up to fp32 rounding.  Up to 256 splits, as long as the split
- * grid stays within four rounds of the device's compute units (which bounds
- * the workspace to rows * splits * (d + 2) * 4 bytes, at most ~136 MB).
- * attn_get_plan reports the choice (KV_SPLITS, KV_CHUNK).
+ * the planner may split each head's keys into chunks handled by separate
+ * workgroups, as Flash Decode splits its reduction dimension; their partial
+ * results (row max, sum, unnormalised output) go to the per-stream workspace
+ * described under attn_decode, and a combine kernel on the same stream writes
+ * o and lse.  Without a mask, and for a causal chunk of queries behind a cache
+ * at least as long (Skv >= 2 Sq), every row has all splits; under a causal mask
+ * with a shorter cache, early rows have fewer (the triangle).  Each split
+ * rounds its probabilities to bf16 against its own maximum, so the result
+ * equals the unsplit one up to that rounding (the error against exact results
+ * is the same).  Up to 256 splits, as long as the split grid stays within four
+ * rounds of the device's compute units, the triangle's within eight: the
+ * workspace, rows * splits * (d + 2) * 4 bytes, is at most ~136 MB, the
+ * triangle's ~272 MB (allocated as the next power of two and kept, see there).
+ * Such a call may allocate or grow the workspace; without memory for it, and
+ * under stream capture (a graph keeps pointers that a later call may replace),
+ * the call runs without splits and uses no workspace.
+ * attn_get_plan_ex reports the choice (KV_SPLITS, KV_CHUNK, CHUNK).
  * Errors as attn_fwd; EINVAL also for Hkv not dividing Hq, unknown flags or
  * a misaligned lse; EUNSUPPORTED if one head's K or V exceeds 2 GiB.
  */
@@ -112,8 +119,9 @@ int attn_fwd_ex(const void* q, const void* k, const void* v, void* o, float* lse
  *   launched).  Every split count gives the same result up to fp32
  *   rounding.
  * Workspace: B*H*n*(d+2)*4 bytes of device memory that the library owns and
- * keeps per stream, reused by every later call on that stream (decode and
- * split-key prefill; stream order serialises them) until the process ends.
+ * keeps per stream, reused by every later call on that stream (decode,
+ * split-key prefill, split-K GEMM; stream order serialises them) until the
+ * process ends.
  * A call that needs more than the stream's current workspace allocates the
  * next power of two in stream order (hipMallocAsync) and releases the old
  * buffer in stream order (hipFreeAsync) behind the work already enqueued
@@ -278,15 +286,17 @@ int attn_get_plan_ex(const attn_device_desc* desc, int kind, int B, int Hq, int 
  * Work: bf16 MFMA products with fp32 accumulation (blocked summation order),
  * rounded once to the output type.  When the plan splits K (K_SPLITS > 1 in
  * attn_gemm_plan: few output tiles, long K), each split's fp32 partial goes
- * to the library's per-stream workspace (stream-ordered allocation, grown
- * as for decode) and a second kernel sums the partials in split order, so
- * the result is the same for every call with that plan.  Supported: M >= 1,
+ * to the library's per-stream workspace (at most 1 GiB; stream-ordered
+ * allocation, grown as for decode) and a second kernel sums the partials in
+ * split order, so the result is the same for every call with that plan.
+ * Without memory for it, and under stream capture (a graph keeps pointers that
+ * a later call may replace), the call runs unsplit and uses no workspace (the
+ * sums then differ by fp32 rounding).  Supported: M >= 1,
  * N and K multiples of 8 (16-byte rows), A and B each at most 2 GiB.
  * Asynchronous on the thread's stream.
  * Errors: EINVAL for null or misaligned pointers, dims <= 0 or unknown
  * flags; EUNSUPPORTED for N or K not a multiple of 8, operands over 2 GiB,
- * or a device that is not gfx950; ENOMEM if a split plan's workspace cannot
- * be allocated; EHIP for launch errors.
+ * or a device that is not gfx950; EHIP for launch errors.
  */
 int attn_gemm(const void* a, const void* b, void* c, int M, int N, int K, int flags);
 

@@ -59,7 +59,7 @@ struct GemmPlan {
     int vgprs = 0;
     int wg_per_cu = 0;
     int tiles_m = 0, tiles_n = 0;
-    // K split (hand-scheduled tiles only): k_splits workgroups per tile each
+    // K split (hand-scheduled and deep-pipeline tiles): k_splits workgroups per tile each
     // take k_chunk values of k (whole k-tiles; the last split may hold fewer)
     // and write an fp32 partial tile to the workspace; a reduction then sums
     // the partials in split order into C
@@ -159,8 +159,11 @@ struct KernelRes {
 // causal: 0 no mask, 1 causal q-tile pairs, 2 the causal chunk kernel
 typedef bool (*FwdResFn)(int d, int bn, int waves, int pipe, int causal, KernelRes* out);
 
-// Tiles of the causal chunk kernel (the others would only add code: these are
-// the ones that the non-causal key splits choose, with 8 and with 4 waves).
+// Tiles of the causal chunk kernel: three, to bound the code -- the software-pipelined
+// eight-wave tile, which long chunks and large grids take, and two four-wave tiles with
+// one K/V tile in flight, which short ones take.  The four-wave software-pipelined tiles
+// (64, 4, 3) and (32, 4, 3), which key splits without a mask mostly take, are not
+// compiled for it and have not been measured as chunk kernels.
 constexpr bool fwd_chunk_tile(int bn, int waves, int pipe) {
     return (bn == 64 && waves == 8 && pipe == 3) || (bn == 64 && waves == 4 && pipe == 1) ||
            (bn == 32 && waves == 4 && pipe == 1);
@@ -172,7 +175,8 @@ void default_desc(attn_device_desc* out);
 bool plan_fwd(const attn_device_desc& desc, int B, int H, int Sq, int Skv, int d, int causal,
               FwdPlan* out, FwdResFn res = nullptr);
 // The plan of a call: the fastest of plan_fwd's candidates, causal chunks, and
-// (H query heads, group of them to a key/value head) folded heads.  may_split
+// (H query heads, group of them to a key/value head) folded heads, but for two
+// corrections where the model of a causal form reads low.  may_split
 // false: no form splits the keys, so that the call needs no workspace (such a plan
 // exists whenever one with splits does).
 bool plan_prefill(const attn_device_desc& desc, int B, int H, int Sq, int Skv, int d, int causal,
@@ -184,12 +188,14 @@ bool plan_prefill(const attn_device_desc& desc, int B, int H, int Sq, int Skv, i
 bool plan_fwd_fixed(const attn_device_desc& desc, int B, int H, int Sq, int Skv, int d,
                     int causal, int bn, int waves, int pipe, FwdPlan* out,
                     FwdResFn res = nullptr, int kv_splits = 1, int fold = 1, int form = 0);
-// Key-split counts tried for prefill without a mask and for causal chunks
-// (each must leave every split non-empty with a chunk that is a multiple of
-// the tile width, and the split grid must stay within kFwdSplitRounds rounds
-// of the CUs).
+// Key-split counts tried for prefill without a mask, for causal chunks and for the
+// causal triangle (each must leave every split non-empty with a chunk that is a
+// multiple of the tile width, and the split grid must stay within kFwdSplitRounds
+// rounds of the CUs, the triangle's, of which about half the workgroups have work,
+// within twice that).
 constexpr int kFwdKvSplits[] = {1, 2, 3, 4, 6, 8, 12, 16, 24, 32, 48, 64, 96, 128, 192, 256};
-// GEMM K splits (hand-scheduled tiles) and the workspace they may use
+// GEMM K splits of the hand-scheduled and of the deep-pipeline tiles, and the
+// workspace they may use
 constexpr int kGemmKSplits[] = {1, 2, 3, 4, 6, 8};
 constexpr int kGemmDeepKSplits[] = {1, 2, 3, 4, 6, 8, 12, 16, 24, 32};
 constexpr long long kGemmMaxWorkspaceBytes = 1LL << 30;

@@ -769,9 +769,11 @@ __global__ __launch_bounds__(256, 1) void gemm_sched_kernel(const GemmArgs args)
 // Measured (cold operands; before: the generic kernel, and this one with padded
 // slots, 32 x 32 MFMAs and no operand prefetch): 2048^3 27.6 -> 22.3 us (770
 // TFLOP/s), 2950 x 5944 x 4224 230 -> 178, 100 x 4096 x 4096 27.8 -> 12.2 (35 MB in
-// 2.9 TB/s, with the split sum), 16384 x 256 x 2048 26.4 -> 22.4.  128 x 128 tiles
-// by one group: 28.0 us at 2048^3.  There the matrix core is busy 45% of the time
-// and waves wait for k-tiles 39% of theirs; bank conflicts are 2% of LDS cycles.
+// 2.9 TB/s, with the split sum), 16384 x 256 x 2048 26.4 -> 22.4.  At 2048^3 (two
+// groups, one workgroup per CU) the matrix core is busy 43 to 46% of the cycles of
+// busy CUs, 26 to 28% of all while the GPU is active, waves wait 35% of their time,
+// and bank conflicts are 2.5% of LDS cycles; one group on four slots took 28.0 us there
+// (not compiled).
 constexpr int kDeepBK = 64;
 
 // Place of 16-column granule 0 of row k of a B tile stored [K][N].

@@ -114,7 +114,8 @@ int fwd_vgprs(int d, int bn, int waves, int pipe) {
 // 0 the load latency is exposed, shared by the g resident workgroups.  A
 // q-tile adds one exposed latency (Q and the first tile) to its loop.
 //
-// Split keys (no mask or a causal chunk, not with the ping-pong schedule; the Flash Decode
+// Split keys (no mask, a causal chunk or the causal triangle, not with the ping-pong
+// schedule; the Flash Decode
 // split of the reduction dimension, Evaluation, applied to prefill): with n
 // splits every (head, q-tile) becomes n workgroups over chunks of ceil(Skv/n) keys rounded up to whole
 // tiles, which fills the CUs when B*H*q-tiles is small; the price is Q read n

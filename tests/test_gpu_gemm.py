@@ -347,8 +347,9 @@ def test_gemm_deep_refuses_an_empty_split(pa):
 
 
 def test_gemm_few_rows_in_a_graph(pa):
-    # captured, the call does not use the workspace that eager calls of the
-    # stream grow (replace) between the replays
+    # replays between eager calls that grow the stream's workspace give the right
+    # result (that the captured call uses no workspace is checked on its plan, in
+    # test_gemm_in_a_graph_uses_no_workspace)
     M, N, K = 70, 512, 4096
     a, b = _inputs(M, N, K, True, 4800)
     ad, bd = a.to(DEV), b.to(DEV)

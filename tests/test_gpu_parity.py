@@ -268,8 +268,8 @@ def test_fwd_largest_key_range(pa):
     # The largest K/V slab one head may have: the tile loads address a head's
     # keys with 31-bit buffer offsets, so Skv * d * 2 bytes must stay below
     # 2^31 (one key more is rejected on the host).  Ragged against every tile
-    # width; few queries, so the non-causal launch splits the key range; the
-    # causal one (bottom-right aligned) runs unsplit.  The outputs are small
+    # width; few queries, so both launches split the key range (the causal
+    # one, bottom-right aligned, as a chunk behind a cache).  The outputs are small
     # (softmax over 8M keys), so the relative error carries the check.
     d = 128
     Skv = 0x7FFFFFFF // (2 * d)  # 8,388,607 keys, 2^31 - 256 bytes per tensor

@@ -490,8 +490,9 @@ def test_fwd_folded_heads_by_plan(pa, causal):
 
 
 def test_fwd_causal_chunk_in_a_graph(pa):
-    # captured, the call needs no workspace: replays stay right after an eager
-    # call of the same stream has grown (replaced) it
+    # replays stay right after an eager call of the same stream has grown the
+    # workspace (that the captured call uses none is checked on its plan, in
+    # test_fwd_in_a_graph_uses_no_workspace)
     B, Hq, Hkv, Sq, Skv, d = 1, 4, 1, 64, 4096, 128
     q, k, v = _qkv(B, Hq, Hkv, Sq, Skv, d, 1800)
     qd, kd, vd = q.to(DEV), k.to(DEV), v.to(DEV)
