@@ -172,6 +172,7 @@ constexpr bool fwd_chunk_tile(int bn, int waves, int pipe) {
 // Planner (host only, pure arithmetic on the device description).  With
 // res == nullptr (no device) the register footprint is estimated.
 void default_desc(attn_device_desc* out);
+// plan_fwd: the fastest of the plain form alone (a call's plan is plan_prefill's).
 bool plan_fwd(const attn_device_desc& desc, int B, int H, int Sq, int Skv, int d, int causal,
               FwdPlan* out, FwdResFn res = nullptr);
 // The plan of a call: the fastest of plan_fwd's candidates, causal chunks, and
@@ -223,6 +224,8 @@ typedef bool (*GemmResFn)(const GemmPlan& p, KernelRes* out);
 bool plan_gemm_fixed(const attn_device_desc& desc, int M, int N, int K, int b_nk, int bm, int bn,
                      int bk, int wm, int wn, int pipe, GemmPlan* out, GemmResFn res = nullptr,
                      int k_splits = 1);
+// The fastest of the generic and the hand-scheduled kernel alone (a call's plan is
+// plan_gemm_call's).
 bool plan_gemm(const attn_device_desc& desc, int M, int N, int K, int b_nk, GemmPlan* out,
                GemmResFn res = nullptr);
 // Candidates of plan_gemm (the generic and the hand-scheduled kernel), and with

@@ -3,7 +3,8 @@
 //
 // Sweeps seeded pseudo-random problem shapes through plan_fwd, plan_fwd_all,
 // plan_decode, plan_gemm, plan_prefill and plan_gemm_call (the last two as a call
-// plans, and as a call that may use no workspace does) with the built-in gfx950 description (register
+// plans, and as a call that may use no workspace does; a tenth of the shapes through
+// their full candidate lists, too) with the built-in gfx950 description (register
 // footprints estimated, no device), and checks that every plan satisfies the
 // legality rules the kernels rely on -- tile symbols from the compiled
 // domains, LDS within capacity, the grid the launch will use, key splits that
@@ -322,6 +323,22 @@ int main(int argc, char** argv) {
         if (!check_gemm_call(desc, M, N, K, (int)(next() & 1))) break;
         if (!check_prefill_call(desc, B, Hkv * group, group, Sq, Skv, d, causal)) break;
         plans += 4;
+        if (it % 10) continue;
+        // every candidate of every form and kernel, as the ablation lists them
+        std::vector<FwdPlan> forms(2048);
+        const int nf = plan_fwd_all(desc, B, Hkv * group, Sq, Skv, d, causal, forms.data(),
+                                    (int)forms.size(), nullptr, group);
+        CHECK(nf >= 1 && nf <= (int)forms.size(), "forms %d", nf);
+        for (int i = 0; i < nf && failures == 0; ++i) {
+            const FwdPlan& f = forms[(size_t)i];
+            check_fwd(desc, f, B, Hkv * group / f.fold, Sq * f.fold, Skv, d, causal, Sq);
+        }
+        std::vector<GemmPlan> kernels(256);
+        const int ng = plan_gemm_all(desc, M, N, K, 0, kernels.data(), (int)kernels.size(), nullptr,
+                                     true);
+        CHECK(ng >= 1 && ng <= (int)kernels.size(), "kernels %d", ng);
+        for (int i = 0; i < ng && failures == 0; ++i) check_gemm(desc, kernels[(size_t)i], M, N, K);
+        plans += nf + ng;
     }
     // shapes whose unsplit plan once fell back to a kernel that splits K itself
     const int split_shapes[][4] = {{195, 4072, 9216, 0}, {1053, 4288, 3232, 1},
